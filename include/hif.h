@@ -384,20 +384,15 @@ hif_status hif_factor_batch(const hif_problem* problems, int32_t count, const hi
  *   lu_panel_threads[b]: threads of the register-resident LU panel (partial
  *     pivoting, Lemma 2.1) for panels of at most 512 (b = 0) and 1024 (b = 1)
  *     rows; allowed 256, 512 or 1024 for b = 0, 512 or 1024 for b = 1.
- *   rowqr_update_waves: waves (16 columns each) per workgroup of the
- *     trailing update that the row compression (Householder QR of Y before
- *     each ID) runs beside the factorization of the next panel; 4 or 8.
- *   rowqr_update_kind: 0 holds each wave's 256 rows x 16 columns of Y in
- *     registers and reads the chunk's reflectors from memory inside the
- *     products, 1 stages the reflectors in LDS first, 2 splits the rows
- *     between two waves per 16 columns (half the registers per wave, the
- *     partial products added through LDS).
+ *   rowqr_update_waves, rowqr_update_kind: checked (4 or 8; 0, 1 or 2) and
+ *     kept for callers that set them; the row compression's trailing update
+ *     has one shape, so they change nothing.
  *   sweep_many_threads: threads per record of the solve's sweeps on
  *     sub-levels of at least 1024 records (the many small records of the
  *     lower levels); 64, 128 or 256.
  * The built-in table comes from paper_1307_2666_amd/tune.py, which times the
- * candidates with hif_id_batched and hif_lu_batched, the row-compression
- * shapes on whole factorizations and the sweep shapes on solves.  hif_tuning_set(NULL)
+ * candidates with hif_id_batched and hif_lu_batched, the sweep shapes on
+ * solves.  hif_tuning_set(NULL)
  * restores it; any other call replaces the table for the whole process (calls
  * already queued keep the shapes they were launched with).  HIF_EINVAL for an
  * entry outside the allowed values (the table is then unchanged).

@@ -29,26 +29,33 @@ void launch_rowqr_split(double* base, const std::vector<int64_t>& moff, const st
                         const std::vector<int32_t>& rows, const std::vector<int32_t>& cols, MemTracker* mt,
                         hipStream_t s);
 
-// Communication-avoiding panels of the row compression: panel width, rows per
-// chunk (one per thread) and the largest stack of chunk R factors.
+// Communication-avoiding panels of the row compression (tsqr.hip): panel
+// width, rows per chunk, chunk factors per group, and the tallest problem.
 constexpr int kTsqrNb = 32;
 constexpr int kTsqrRows = 256;
-constexpr int kTsqrStack = 1024;
+constexpr int kTsqrFan = 16;
+constexpr int kTsqrMaxRows = 32768;
+static_assert(kTsqrMaxRows <= kTsqrRows * kTsqrFan * kTsqrFan, "three tree levels");
 __host__ __device__ inline int tsqr_chunks(int mp) { return (mp + kTsqrRows - 1) / kTsqrRows; }
-// Scratch of one problem with m rows (doubles): V (m x nb) | T per chunk |
-// stacked R | stacked V | stack T.
+__host__ __device__ inline int tsqr_groups(int nck) { return (nck + kTsqrFan - 1) / kTsqrFan; }
+// Problems of at most kTsqrMaxRows rows.
+void launch_tsqr(const QrBatch& A, int max_rows, int max_cols, hipStream_t s);
+// Scratch of one problem with m rows (doubles): V of the chunks (m x nb) | T
+// per chunk | stacked chunk R, replaced by V of the groups | T per group |
+// with several groups, their stacked R, replaced by V of the root, and its T.
 struct TsqrLayout {
-  int64_t V, Tc, S, Vs, Ts, total;
+  int64_t V, Tc, S, T1, S2, T2, total;
 };
 __host__ __device__ inline TsqrLayout tsqr_layout(int m) {
-  const int64_t nm = tsqr_chunks(m), b2 = int64_t(kTsqrNb) * kTsqrNb;
+  const int64_t nm = tsqr_chunks(m), ng = tsqr_groups(int(nm)), b2 = int64_t(kTsqrNb) * kTsqrNb;
   TsqrLayout L;
   L.V = 0;
   L.Tc = int64_t(m) * kTsqrNb;
   L.S = L.Tc + nm * b2;
-  L.Vs = L.S + nm * b2;
-  L.Ts = L.Vs + nm * b2;
-  L.total = L.Ts + b2;
+  L.T1 = L.S + nm * b2;
+  L.S2 = L.T1 + ng * b2;
+  L.T2 = L.S2 + (ng > 1 ? ng * b2 : 0);
+  L.total = L.T2 + (ng > 1 ? b2 : 0);
   return L;
 }
 // Scratch doubles every row-compression path needs for an m x n problem

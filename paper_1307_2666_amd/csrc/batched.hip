@@ -7,7 +7,6 @@
 // updates run on the matrix cores (v_mfma_f64_16x16x4f64) with operands read
 // straight from device memory in the instruction's lane layout.
 #include <algorithm>
-#include <map>
 #include <climits>
 #include <vector>
 
@@ -315,781 +314,6 @@ __global__ void k_qr_clear_lower(QrBatch A) {
     const int r = int(e / n), c = int(e % n);
     if (c < r) M[int64_t(r) * ld + c] = 0.0;
   }
-}
-
-// ---------------------------------------------------------------------------
-// Communication-avoiding row compression (TSQR panels).  Panel j0 (columns
-// j0..j0+jb-1, rows j0..m-1) is split into nck balanced chunks of at most
-// kTsqrRows rows.  Each chunk is factored by its own workgroup (one row per
-// thread, in registers); with nck > 1 the chunk R factors are stacked and the
-// stack is factored again.  The trailing columns are then updated chunk by
-// chunk with the chunk's compact WY form, and the chunk top rows with the
-// stack's.  The final R rows of the panel land in rows j0..j0+jb-1; all that
-// later steps read is R (the orthogonal factor is never formed).
-// ---------------------------------------------------------------------------
-constexpr int kTb = kTsqrNb;
-static_assert(kTb == kRs, "the panel width is the reduce-scatter width");
-
-struct PanelGeom {
-  int mp, jb, nck;
-};
-__device__ __forceinline__ PanelGeom panel_geom(int m, int n, int j0, int cr) {
-  PanelGeom g;
-  g.mp = m - j0;
-  g.jb = min(kTb, n - j0);
-  g.nck = (g.mp + cr - 1) / cr;
-  return g;
-}
-__device__ __forceinline__ int chunk_lo(int c, int mp, int nck) { return (c * mp) / nck; }
-
-__device__ __forceinline__ double pick(const double (&y)[kTb], int j) {
-  double r = 0.0;
-#pragma unroll
-  for (int c = 0; c < kTb; ++c)
-    if (c == j) r = y[c];
-  return r;
-}
-
-
-// Householder QR of a block of at most RPT * blockDim.x rows and jb <= kTb
-// columns held RPT rows per thread (thread t: rows t + u * blockDim.x; rows
-// past the block are zero).  Per column one reduction round gives, over the
-// rows below the diagonal, the squared norm and the products with the later
-// columns; the first kTb threads then turn them into the reflector (alpha,
-// v0, beta) and the update coefficient of every column, which all threads
-// read back from LDS.  On return rows < jb hold R (upper part) and rows > jj
-// hold the Householder vector of column jj below the diagonal; v0 (its
-// diagonal entry) and beta = 2 / v^T v are in sv0 / sbeta.
-// LDS: sred [2][NW][kTb], srow [2][kTb], scf [2][kTb + 2].
-template <int NW, int RPT>
-__device__ void rowblock_qr(double (&y)[RPT][kTb], int jb, double* sred, double* srow, double* scf, double* sv0,
-                            double* sbeta, double* sG) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int t0 = threadIdx.x, B = blockDim.x;
-  if (t0 >= jb && t0 < kTb) {  // columns past a partial panel: no reflector
-    sv0[t0] = 0.0;
-    sbeta[t0] = 0.0;
-  }
-  for (int jj = 0; jj < jb; ++jj) {
-    const int b = jj & 1;  // double-buffered: one barrier pair per column
-    double* red = sred + b * NW * kTb;
-    double* row = srow + b * kTb;
-    double* cf = scf + b * (kTb + 2);
-    double yj[RPT];
-#pragma unroll
-    for (int u = 0; u < RPT; ++u) yj[u] = pick(y[u], jj);
-    if (t0 == jj) {  // jj < kTb <= B: row jj is slot 0 of thread jj
-#pragma unroll
-      for (int c = 0; c < kTb; ++c) row[c] = y[0][c];
-    }
-    double p[kTb];
-    {
-      double e[RPT];
-#pragma unroll
-      for (int u = 0; u < RPT; ++u) e[u] = t0 + u * B > jj ? yj[u] : 0.0;
-#pragma unroll
-      for (int c = 0; c < kTb; ++c) {
-        double acc = 0.0;
-#pragma unroll
-        for (int u = 0; u < RPT; ++u) acc += e[u] * y[u][c];
-        p[c] = acc;
-      }
-    }
-    const double w = wave_rs32(p);
-    if ((lane & 1) == 0) red[wv * kTb + (lane >> 1)] = w;
-    __syncthreads();
-    if (t0 < kTb) {
-      const int c = t0;
-      double sc = 0.0, sj = 0.0;
-#pragma unroll
-      for (int w2 = 0; w2 < NW; ++w2) {
-        sc += red[w2 * kTb + c];
-        sj += red[w2 * kTb + jj];
-      }
-      const double x0 = row[jj];
-      const double ss = sj + x0 * x0;
-      const double nrm = sqrt(ss);
-      const double alpha = nrm > 0.0 ? -copysign(nrm, x0) : 0.0;
-      const double v0 = x0 - alpha;
-      const double vtv = sj + v0 * v0;
-      const double beta = vtv > 0.0 ? 2.0 / vtv : 0.0;
-      cf[c] = (c > jj && c < jb) ? beta * (v0 * row[c] + sc) : 0.0;
-      // column jj of G = V^T V above the diagonal: rows > jj of column c < jj
-      // hold its reflector, row jj its entry V(jj, c)
-      if (c < jj) sG[c * (kTb + 1) + jj] = sc + row[c] * v0;
-      if (c == 0) {
-        cf[kTb] = alpha;
-        cf[kTb + 1] = v0;
-        sv0[jj] = v0;
-        sbeta[jj] = beta;
-      }
-    }
-    __syncthreads();
-    const double alpha = cf[kTb], v0 = cf[kTb + 1];
-    double coef[kTb];
-#pragma unroll
-    for (int c = 0; c < kTb; ++c) coef[c] = cf[c];
-#pragma unroll
-    for (int u = 0; u < RPT; ++u) {
-      const int t = t0 + u * B;
-      if (t >= jj) {
-        const double vt = t == jj ? v0 : yj[u];
-#pragma unroll
-        for (int c = 0; c < kTb; ++c) y[u][c] -= coef[c] * vt;
-        if (u == 0 && t == jj) {  // row jj < kTb lives in slot 0
-#pragma unroll
-          for (int c = 0; c < kTb; ++c)
-            if (c == jj) y[u][c] = alpha;
-        }
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Row t of V (rows x kTb, zero above the diagonal and past column jb).
-__device__ __forceinline__ void store_vrow(const double (&y)[kTb], int t, int jb, const double* sv0, double* Vrow) {
-#pragma unroll
-  for (int c = 0; c < kTb; ++c) Vrow[c] = (c < jb && t > c) ? y[c] : ((c < jb && t == c) ? sv0[c] : 0.0);
-}
-
-// T of the compact WY form I - V T V^T (T upper triangular) from beta and the
-// upper part of G = V^T V that rowblock_qr left in sG.
-__device__ void build_T(const double* sbeta, const double* sG, double* Tout) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  // T(p, i) = -beta_i sum_{l < i} T(p, l) G(l, i) for p < i, T(i, i) = beta_i:
-  // one wave, lane p keeps row p of T in registers (no barriers)
-  if (wv == 0) {
-    const int p = lane & (kTb - 1);
-    double trow[kTb];
-#pragma unroll
-    for (int l = 0; l < kTb; ++l) trow[l] = 0.0;
-#pragma unroll
-    for (int i = 0; i < kTb; ++i) {
-      const double b = sbeta[i];
-      // no branch on b, so that the G reads can be issued ahead of the
-      // chain; for b == 0 (no reflector, G unset) acc is discarded below
-      double acc = 0.0;
-#pragma unroll
-      for (int l = 0; l < i; ++l) acc += trow[l] * sG[l * (kTb + 1) + i];
-      trow[i] = p == i ? b : ((p < i && b != 0.0) ? -b * acc : 0.0);
-    }
-    if (lane < kTb)
-#pragma unroll
-      for (int l = 0; l < kTb; ++l) Tout[p * kTb + l] = trow[l];
-  }
-}
-
-// K1: QR of one chunk of the panel (chunks of at most cr = BS * RPT rows).
-template <int BS, int RPT>
-__global__ __launch_bounds__(BS) void k_tsqr_chunk(QrBatch A, int j0, int cr, int half) {
-  const int q = blockIdx.y, c = blockIdx.x;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const PanelGeom g = panel_geom(m, n, j0, cr);
-  if (c >= g.nck) return;
-  const int lo = chunk_lo(c, g.mp, g.nck), rows = chunk_lo(c + 1, g.mp, g.nck) - lo;
-  double* M = A.base + A.moff[q];
-  const int ld = A.ld[q];
-  const TsqrLayout L = tsqr_layout(m);
-  double* S0 = A.scratch + A.soff[q] + half * L.total;
-  const int t0 = threadIdx.x;
-  __shared__ double sred[2 * (BS / 64) * kTb], srow[2 * kTb], scf[2 * (kTb + 2)], sv0[kTb], sbeta[kTb];
-  __shared__ double sG[kTb * (kTb + 1)];
-  double y[RPT][kTb];
-#pragma unroll
-  for (int u = 0; u < RPT; ++u) {
-    const int t = t0 + u * BS;
-    const double* src = M + int64_t(j0 + lo + (t < rows ? t : 0)) * ld + j0;
-#pragma unroll
-    for (int cc = 0; cc < kTb; ++cc) y[u][cc] = (t < rows && cc < g.jb) ? src[cc] : 0.0;
-  }
-  rowblock_qr<BS / 64, RPT>(y, g.jb, sred, srow, scf, sv0, sbeta, sG);
-  double* V = S0 + L.V + int64_t(lo) * kTb;
-#pragma unroll
-  for (int u = 0; u < RPT; ++u) {
-    const int t = t0 + u * BS;
-    if (t < rows) store_vrow(y[u], t, g.jb, sv0, V + int64_t(t) * kTb);
-  }
-  if (g.nck == 1) {
-    if (t0 < g.jb) {
-      double* dst = M + int64_t(j0 + t0) * ld + j0;
-#pragma unroll
-      for (int cc = 0; cc < kTb; ++cc)
-        if (cc < g.jb) dst[cc] = cc >= t0 ? y[0][cc] : 0.0;
-    }
-  } else if (t0 < kTb) {
-    double* dst = S0 + L.S + int64_t(c * kTb + t0) * kTb;
-#pragma unroll
-    for (int cc = 0; cc < kTb; ++cc) dst[cc] = (t0 < g.jb && cc >= t0 && cc < g.jb) ? y[0][cc] : 0.0;
-  }
-  __syncthreads();
-  build_T(sbeta, sG, S0 + L.Tc + int64_t(c) * kTb * kTb);
-}
-
-// K2: QR of the stacked chunk R factors (nck > 1); writes the panel's R.
-template <int BS, int RPT>
-__global__ __launch_bounds__(BS) void k_tsqr_stack(QrBatch A, int j0, int cr, int half) {
-  const int q = blockIdx.x;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const PanelGeom g = panel_geom(m, n, j0, cr);
-  if (g.nck < 2) return;
-  const int srows = g.nck * kTb;
-  double* M = A.base + A.moff[q];
-  const int ld = A.ld[q];
-  const TsqrLayout L = tsqr_layout(m);
-  double* S0 = A.scratch + A.soff[q] + half * L.total;
-  const int t = threadIdx.x;
-  __shared__ double sred[2 * (BS / 64) * kTb], srow[2 * kTb], scf[2 * (kTb + 2)], sv0[kTb], sbeta[kTb];
-  __shared__ double sG[kTb * (kTb + 1)];
-  double y[RPT][kTb];
-#pragma unroll
-  for (int u = 0; u < RPT; ++u) {
-    const int tu = t + u * BS;
-    const double* src = S0 + L.S + int64_t(tu < srows ? tu : 0) * kTb;
-#pragma unroll
-    for (int cc = 0; cc < kTb; ++cc) y[u][cc] = tu < srows ? src[cc] : 0.0;
-  }
-  rowblock_qr<BS / 64, RPT>(y, g.jb, sred, srow, scf, sv0, sbeta, sG);
-  double* V = S0 + L.Vs;
-#pragma unroll
-  for (int u = 0; u < RPT; ++u) {
-    const int tu = t + u * BS;
-    if (tu < srows) store_vrow(y[u], tu, g.jb, sv0, V + int64_t(tu) * kTb);
-  }
-  if (t < g.jb) {
-    double* dst = M + int64_t(j0 + t) * ld + j0;
-#pragma unroll
-    for (int cc = 0; cc < kTb; ++cc)
-      if (cc < g.jb) dst[cc] = cc >= t ? y[0][cc] : 0.0;
-  }
-  __syncthreads();
-  build_T(sbeta, sG, S0 + L.Ts);
-}
-
-// Y <- (I - V T V^T)^T Y for one 64-column tile: P = V^T Y, W = T^T P,
-// Y -= V W.  rowp(r) gives the address of row r of the tile.  256 threads;
-// wave w owns columns 16w..16w+15 and needs nothing from the other waves:
-// in the 16x16x4 FP64 MFMA layout, element v of an accumulator tile holds
-// rows 4v + (lane / 16) of column lane % 16, which is exactly the B operand
-// of K-step v, so P feeds W = T^T P and W feeds Y -= V W from registers.
-template <class RowP>
-__device__ void apply_wy_tile(const double* V, int rows, const double* Tm, RowP rowp, int nt) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int ct = wv * 16;
-  const bool colok = ct + li < nt;
-  // 1. P (kTb x 16): rows 0-15 in p0, 16-31 in p1, from one read of Y
-  double4_t p0 = {0.0, 0.0, 0.0, 0.0}, p1 = {0.0, 0.0, 0.0, 0.0};
-  for (int kb = 0; kb < rows; kb += 32) {  // 8 steps of 4 rows, loads issued first
-    double a0[8], a1[8], b[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int r = kb + 4 * u + lk;
-      const bool ok = r < rows;
-      a0[u] = ok ? V[int64_t(r) * kTb + li] : 0.0;
-      a1[u] = ok ? V[int64_t(r) * kTb + 16 + li] : 0.0;
-      b[u] = (ok && colok) ? rowp(r)[ct + li] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      p0 = mfma_f64(a0[u], b[u], p0);
-      p1 = mfma_f64(a1[u], b[u], p1);
-    }
-  }
-  // 2. W = T^T P (T upper triangular, zero below the diagonal): A(i, k) = T(k, i)
-  double4_t w0 = {0.0, 0.0, 0.0, 0.0}, w1 = {0.0, 0.0, 0.0, 0.0};
-  {
-    double t0[8], t1[8];
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      t0[s2] = Tm[(4 * s2 + lk) * kTb + li];
-      t1[s2] = Tm[(4 * s2 + lk) * kTb + 16 + li];
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      const double bp = s2 < 4 ? p0[s2 & 3] : p1[s2 & 3];
-      w0 = mfma_f64(t0[s2], bp, w0);
-      w1 = mfma_f64(t1[s2], bp, w1);
-    }
-  }
-  // 3. Y -= V W over 16-row tiles
-  for (int rt = 0; rt < rows; rt += 16) {
-    double a[8], y[4];
-    const int ra = rt + li;
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) a[s2] = ra < rows ? V[int64_t(ra) * kTb + 4 * s2 + lk] : 0.0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = rt + 4 * v + lk;
-      y[v] = (r < rows && colok) ? rowp(r)[ct + li] : 0.0;
-    }
-    double4_t d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) d = mfma_f64(a[s2], s2 < 4 ? w0[s2 & 3] : w1[s2 & 3], d);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = rt + 4 * v + lk;
-      if (r < rows && colok) rowp(r)[ct + li] = y[v] - d[v];
-    }
-  }
-}
-
-// The same update for chunks of at most 256 rows with the wave's 256 x 16
-// slice of Y held in registers from the first product to the write-back, so
-// that Y is read once and written once (element v of row tile t is row
-// 16t + 4v + lane / 16, column lane % 16: the B operand of K-step 4t + v).
-__device__ __forceinline__ void apply_wy_tile_reg(const double* V, int rows, const double* Tm, double* Y0, int64_t ld, int nt) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int ct = wv * 16;
-  const bool colok = ct + li < nt;
-  double yv[16][4];
-#pragma unroll
-  for (int t = 0; t < 16; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * t + 4 * v + lk;
-      yv[t][v] = (r < rows && colok) ? Y0[int64_t(r) * ld + ct + li] : 0.0;
-    }
-  // 1. P = V^T Y (rows past the chunk are zero in yv; V rows there are not read)
-  double4_t p0 = {0.0, 0.0, 0.0, 0.0}, p1 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    if (16 * t >= rows) break;
-    double a0[4], a1[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * t + 4 * v + lk;
-      a0[v] = r < rows ? V[int64_t(r) * kTb + li] : 0.0;
-      a1[v] = r < rows ? V[int64_t(r) * kTb + 16 + li] : 0.0;
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      p0 = mfma_f64(a0[v], yv[t][v], p0);
-      p1 = mfma_f64(a1[v], yv[t][v], p1);
-    }
-  }
-  // 2. W = T^T P
-  double4_t w0 = {0.0, 0.0, 0.0, 0.0}, w1 = {0.0, 0.0, 0.0, 0.0};
-  {
-    double t0[8], t1[8];
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      t0[s2] = Tm[(4 * s2 + lk) * kTb + li];
-      t1[s2] = Tm[(4 * s2 + lk) * kTb + 16 + li];
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      const double bp = s2 < 4 ? p0[s2 & 3] : p1[s2 & 3];
-      w0 = mfma_f64(t0[s2], bp, w0);
-      w1 = mfma_f64(t1[s2], bp, w1);
-    }
-  }
-  // 3. Y -= V W, written back
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    if (16 * t >= rows) break;
-    double a[8];
-    const int ra = 16 * t + li;
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) a[s2] = ra < rows ? V[int64_t(ra) * kTb + 4 * s2 + lk] : 0.0;
-    double4_t d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) d = mfma_f64(a[s2], s2 < 4 ? w0[s2 & 3] : w1[s2 & 3], d);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * t + 4 * v + lk;
-      if (r < rows && colok) Y0[int64_t(r) * ld + ct + li] = yv[t][v] - d[v];
-    }
-  }
-}
-
-// The same update with the chunk's V and T staged in LDS first (one coalesced
-// pass per workgroup), so that the fragments the matrix cores consume come
-// from LDS rather than from scattered global loads inside the product loops.
-// sV holds V with row stride kVs = kTb + 1 doubles: a Y-phase fragment reads
-// 16 rows at one column offset, which then fall on different banks.
-constexpr int kVs = kTb + 1;
-constexpr size_t kApplyLds = (size_t(kTsqrRows) * kVs + kTb * kTb) * sizeof(double);
-__device__ __forceinline__ void apply_wy_tile_lds(const double* sV, int rows, const double* sT, double* Y0, int64_t ld, int nt) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int ct = wv * 16;
-  const bool colok = ct + li < nt;
-  double yv[16][4];
-#pragma unroll
-  for (int t = 0; t < 16; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * t + 4 * v + lk;
-      yv[t][v] = (r < rows && colok) ? Y0[int64_t(r) * ld + ct + li] : 0.0;
-    }
-  // 1. P = V^T Y.  The fragments of row tile t + 1 are read while tile t is
-  // multiplied (one tile ahead, no further: the scheduling barrier keeps the
-  // compiler from hoisting every tile's reads and spilling).
-  double4_t p0 = {0.0, 0.0, 0.0, 0.0}, p1 = {0.0, 0.0, 0.0, 0.0};
-  double a0[4], a1[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int r = 4 * v + lk;
-    a0[v] = r < rows ? sV[r * kVs + li] : 0.0;
-    a1[v] = r < rows ? sV[r * kVs + 16 + li] : 0.0;
-  }
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    if (16 * t < rows) {  // guarded, not broken out of: the loop must unroll fully
-    double b0[4], b1[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * (t + 1) + 4 * v + lk;
-      b0[v] = (t < 15 && r < rows) ? sV[r * kVs + li] : 0.0;
-      b1[v] = (t < 15 && r < rows) ? sV[r * kVs + 16 + li] : 0.0;
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      p0 = mfma_f64(a0[v], yv[t][v], p0);
-      p1 = mfma_f64(a1[v], yv[t][v], p1);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      a0[v] = b0[v];
-      a1[v] = b1[v];
-    }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  // 2. W = T^T P
-  double4_t w0 = {0.0, 0.0, 0.0, 0.0}, w1 = {0.0, 0.0, 0.0, 0.0};
-  {
-    double t0[8], t1[8];
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      t0[s2] = sT[(4 * s2 + lk) * kTb + li];
-      t1[s2] = sT[(4 * s2 + lk) * kTb + 16 + li];
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      const double bp = s2 < 4 ? p0[s2 & 3] : p1[s2 & 3];
-      w0 = mfma_f64(t0[s2], bp, w0);
-      w1 = mfma_f64(t1[s2], bp, w1);
-    }
-  }
-  // 3. Y -= V W, written back; fragments one row tile ahead as in 1.
-  double a[8];
-#pragma unroll
-  for (int s2 = 0; s2 < 8; ++s2) a[s2] = li < rows ? sV[li * kVs + 4 * s2 + lk] : 0.0;
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    if (16 * t < rows) {
-    double b[8];
-    const int rb = 16 * (t + 1) + li;
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) b[s2] = (t < 15 && rb < rows) ? sV[rb * kVs + 4 * s2 + lk] : 0.0;
-    double4_t d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) d = mfma_f64(a[s2], s2 < 4 ? w0[s2 & 3] : w1[s2 & 3], d);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * t + 4 * v + lk;
-      if (r < rows && colok) Y0[int64_t(r) * ld + ct + li] = yv[t][v] - d[v];
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) a[s2] = b[s2];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// The same update with the chunk's rows split between two waves per 16
-// columns (wave w: columns 16 (w % CG), rows 128 (w / CG) .. + 127), so that
-// each wave holds half the slice of Y and more waves fit per SIMD; the two
-// halves add their partial products V^T Y through LDS before both form W.
-template <int CG>
-__device__ __forceinline__ void apply_wy_tile_split(const double* V, int rows, const double* Tm, double* Y0,
-                                                    int64_t ld, int nt, double* sP) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int cg = wv % CG, hf = wv / CG;
-  const int li = lane & 15, lk = lane >> 4;
-  const int ct = cg * 16, r0 = hf * 128;
-  const bool colok = ct + li < nt;
-  double yv[8][4];
-#pragma unroll
-  for (int t = 0; t < 8; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = r0 + 16 * t + 4 * v + lk;
-      yv[t][v] = (r < rows && colok) ? Y0[int64_t(r) * ld + ct + li] : 0.0;
-    }
-  double4_t p0 = {0.0, 0.0, 0.0, 0.0}, p1 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    if (r0 + 16 * t < rows) {
-      double a0[4], a1[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int r = r0 + 16 * t + 4 * v + lk;
-        a0[v] = r < rows ? V[int64_t(r) * kTb + li] : 0.0;
-        a1[v] = r < rows ? V[int64_t(r) * kTb + 16 + li] : 0.0;
-      }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        p0 = mfma_f64(a0[v], yv[t][v], p0);
-        p1 = mfma_f64(a1[v], yv[t][v], p1);
-      }
-    }
-  }
-  // sP[cg][hf][8][64]: each lane's 8 accumulator entries, by lane
-  double* mine = sP + (cg * 2 + hf) * 8 * 64;
-  const double* other = sP + (cg * 2 + (1 - hf)) * 8 * 64;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    mine[e * 64 + lane] = p0[e];
-    mine[(4 + e) * 64 + lane] = p1[e];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    p0[e] += other[e * 64 + lane];
-    p1[e] += other[(4 + e) * 64 + lane];
-  }
-  double4_t w0 = {0.0, 0.0, 0.0, 0.0}, w1 = {0.0, 0.0, 0.0, 0.0};
-  {
-    double t0[8], t1[8];
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      t0[s2] = Tm[(4 * s2 + lk) * kTb + li];
-      t1[s2] = Tm[(4 * s2 + lk) * kTb + 16 + li];
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      const double bp = s2 < 4 ? p0[s2 & 3] : p1[s2 & 3];
-      w0 = mfma_f64(t0[s2], bp, w0);
-      w1 = mfma_f64(t1[s2], bp, w1);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    if (r0 + 16 * t < rows) {
-      double a[8];
-      const int ra = r0 + 16 * t + li;
-#pragma unroll
-      for (int s2 = 0; s2 < 8; ++s2) a[s2] = ra < rows ? V[int64_t(ra) * kTb + 4 * s2 + lk] : 0.0;
-      double4_t d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int s2 = 0; s2 < 8; ++s2) d = mfma_f64(a[s2], s2 < 4 ? w0[s2 & 3] : w1[s2 & 3], d);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int r = r0 + 16 * t + 4 * v + lk;
-        if (r < rows && colok) Y0[int64_t(r) * ld + ct + li] = yv[t][v] - d[v];
-      }
-    }
-  }
-}
-
-// K3 for chunks of at most 256 rows, rows split over two waves per 16 columns
-// (CG groups of 16 columns per workgroup, 2 CG waves).
-template <int CG>
-__global__ __launch_bounds__(128 * CG) void k_tsqr_apply_chunk_split(QrBatch A, int j0, int cr, int half, int cbeg,
-                                                                    int cend) {
-  const int q = blockIdx.z, c = blockIdx.y;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const PanelGeom g = panel_geom(m, n, j0, cr);
-  if (c >= g.nck) return;
-  const int c0 = cbeg + blockIdx.x * 16 * CG, ce = min(n, cend);
-  if (c0 >= ce) return;
-  const int nt = min(16 * CG, ce - c0);
-  const int lo = chunk_lo(c, g.mp, g.nck), rows = chunk_lo(c + 1, g.mp, g.nck) - lo;
-  double* M = A.base + A.moff[q];
-  const int ld = A.ld[q];
-  const TsqrLayout L = tsqr_layout(m);
-  const double* S0 = A.scratch + A.soff[q] + half * L.total;
-  __shared__ double sP[CG * 2 * 8 * 64];
-  apply_wy_tile_split<CG>(S0 + L.V + int64_t(lo) * kTb, rows, S0 + L.Tc + int64_t(c) * kTb * kTb,
-                          M + int64_t(j0 + lo) * ld + c0, ld, nt, sP);
-}
-
-// K3 for chunks of at most 256 rows, V and T in LDS (kApplyLds bytes of
-// dynamic LDS), NW waves of 16 columns each: workgroup (x, chunk, problem)
-// updates columns cbeg + 16 NW x .. + 16 NW - 1.
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_tsqr_apply_chunk_lds(QrBatch A, int j0, int cr, int half, int cbeg,
-                                                                  int cend) {
-  const int q = blockIdx.z, c = blockIdx.y;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const PanelGeom g = panel_geom(m, n, j0, cr);
-  if (c >= g.nck) return;
-  const int c0 = cbeg + blockIdx.x * 16 * NW, ce = min(n, cend);
-  if (c0 >= ce) return;
-  const int nt = min(16 * NW, ce - c0);
-  const int lo = chunk_lo(c, g.mp, g.nck), rows = chunk_lo(c + 1, g.mp, g.nck) - lo;
-  double* M = A.base + A.moff[q];
-  const int ld = A.ld[q];
-  const TsqrLayout L = tsqr_layout(m);
-  const double* S0 = A.scratch + A.soff[q] + half * L.total;
-  extern __shared__ double smem[];
-  double* sV = smem;
-  double* sT = smem + kTsqrRows * kVs;
-  const double* V = S0 + L.V + int64_t(lo) * kTb;
-  const double* Tm = S0 + L.Tc + int64_t(c) * kTb * kTb;
-  for (int e = threadIdx.x; e < rows * kTb; e += 64 * NW) sV[(e / kTb) * kVs + e % kTb] = V[e];
-  for (int e = threadIdx.x; e < kTb * kTb; e += 64 * NW) sT[e] = Tm[e];
-  __syncthreads();
-  apply_wy_tile_lds(sV, rows, sT, M + int64_t(j0 + lo) * ld + c0, ld, nt);
-}
-
-// K3: trailing update of chunk blockIdx.y, column tile blockIdx.x.
-__global__ __launch_bounds__(256) void k_tsqr_apply_chunk(QrBatch A, int j0, int cr, int half, int cbeg, int cend) {
-  const int q = blockIdx.z, c = blockIdx.y;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const PanelGeom g = panel_geom(m, n, j0, cr);
-  if (c >= g.nck) return;
-  const int c0 = cbeg + blockIdx.x * 64, ce = min(n, cend);
-  if (c0 >= ce) return;
-  const int nt = min(64, ce - c0);
-  const int lo = chunk_lo(c, g.mp, g.nck), rows = chunk_lo(c + 1, g.mp, g.nck) - lo;
-  double* M = A.base + A.moff[q];
-  const int ld = A.ld[q];
-  const TsqrLayout L = tsqr_layout(m);
-  const double* S0 = A.scratch + A.soff[q] + half * L.total;
-  double* Y0 = M + int64_t(j0 + lo) * ld + c0;
-  apply_wy_tile(S0 + L.V + int64_t(lo) * kTb, rows, S0 + L.Tc + int64_t(c) * kTb * kTb,
-                [=](int r) { return Y0 + int64_t(r) * ld; }, nt);
-}
-
-// K3 for chunks of at most 256 rows, Y held in registers; NW waves of 16
-// columns each.
-template <int NW>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void k_tsqr_apply_chunk_reg(QrBatch A, int j0, int cr, int half, int cbeg,
-                                                                          int cend) {
-  const int q = blockIdx.z, c = blockIdx.y;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const PanelGeom g = panel_geom(m, n, j0, cr);
-  if (c >= g.nck) return;
-  const int c0 = cbeg + blockIdx.x * 16 * NW, ce = min(n, cend);
-  if (c0 >= ce) return;
-  const int nt = min(16 * NW, ce - c0);
-  const int lo = chunk_lo(c, g.mp, g.nck), rows = chunk_lo(c + 1, g.mp, g.nck) - lo;
-  double* M = A.base + A.moff[q];
-  const int ld = A.ld[q];
-  const TsqrLayout L = tsqr_layout(m);
-  const double* S0 = A.scratch + A.soff[q] + half * L.total;
-  apply_wy_tile_reg(S0 + L.V + int64_t(lo) * kTb, rows, S0 + L.Tc + int64_t(c) * kTb * kTb,
-                    M + int64_t(j0 + lo) * ld + c0, ld, nt);
-}
-
-
-// The stack update with the rows split between RG waves per 16 columns
-// (wave w: columns 16 (w % CG), row blocks of 32 taken round-robin by the RG
-// waves w / CG): each wave forms a partial V^T Y over its rows, the RG
-// partials are added through LDS, and every wave then forms W and updates its
-// own rows.  rowp(r) gives the address of row r of the tile.
-template <int CG, int RG, class RowP>
-__device__ __forceinline__ void apply_wy_tile_rg(const double* V, int rows, const double* Tm, RowP rowp, int nt,
-                                                 double* sP) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int cg = wv % CG, rg = wv / CG;
-  const int li = lane & 15, lk = lane >> 4;
-  const int ct = cg * 16;
-  const bool colok = ct + li < nt;
-  double4_t p0 = {0.0, 0.0, 0.0, 0.0}, p1 = {0.0, 0.0, 0.0, 0.0};
-  for (int kb = 32 * rg; kb < rows; kb += 32 * RG) {
-    double a0[8], a1[8], b[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int r = kb + 4 * u + lk;
-      const bool ok = r < rows;
-      a0[u] = ok ? V[int64_t(r) * kTb + li] : 0.0;
-      a1[u] = ok ? V[int64_t(r) * kTb + 16 + li] : 0.0;
-      b[u] = (ok && colok) ? rowp(r)[ct + li] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      p0 = mfma_f64(a0[u], b[u], p0);
-      p1 = mfma_f64(a1[u], b[u], p1);
-    }
-  }
-  double* mine = sP + (cg * RG + rg) * 8 * 64;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    mine[e * 64 + lane] = p0[e];
-    mine[(4 + e) * 64 + lane] = p1[e];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-    for (int g = 0; g < RG; ++g) {
-      s0 += sP[(cg * RG + g) * 8 * 64 + e * 64 + lane];
-      s1 += sP[(cg * RG + g) * 8 * 64 + (4 + e) * 64 + lane];
-    }
-    p0[e] = s0;
-    p1[e] = s1;
-  }
-  double4_t w0 = {0.0, 0.0, 0.0, 0.0}, w1 = {0.0, 0.0, 0.0, 0.0};
-  {
-    double t0[8], t1[8];
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      t0[s2] = Tm[(4 * s2 + lk) * kTb + li];
-      t1[s2] = Tm[(4 * s2 + lk) * kTb + 16 + li];
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) {
-      const double bp = s2 < 4 ? p0[s2 & 3] : p1[s2 & 3];
-      w0 = mfma_f64(t0[s2], bp, w0);
-      w1 = mfma_f64(t1[s2], bp, w1);
-    }
-  }
-  for (int rt = 16 * rg; rt < rows; rt += 16 * RG) {
-    double a[8], y[4];
-    const int ra = rt + li;
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) a[s2] = ra < rows ? V[int64_t(ra) * kTb + 4 * s2 + lk] : 0.0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = rt + 4 * v + lk;
-      y[v] = (r < rows && colok) ? rowp(r)[ct + li] : 0.0;
-    }
-    double4_t d = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) d = mfma_f64(a[s2], s2 < 4 ? w0[s2 & 3] : w1[s2 & 3], d);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = rt + 4 * v + lk;
-      if (r < rows && colok) rowp(r)[ct + li] = y[v] - d[v];
-    }
-  }
-}
-
-// K4 with the rows split between RG waves: the stack's WY form applied to the
-// chunk top rows of 16 CG columns per workgroup (CG RG waves).
-template <int CG, int RG>
-__global__ __launch_bounds__(64 * CG * RG) void k_tsqr_apply_stack_rg(QrBatch A, int j0, int cr, int half, int cbeg,
-                                                                     int cend) {
-  const int q = blockIdx.y;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const PanelGeom g = panel_geom(m, n, j0, cr);
-  if (g.nck < 2) return;
-  const int c0 = cbeg + blockIdx.x * 16 * CG, ce = min(n, cend);
-  if (c0 >= ce) return;
-  const int nt = min(16 * CG, ce - c0);
-  double* M = A.base + A.moff[q];
-  const int ld = A.ld[q];
-  const TsqrLayout L = tsqr_layout(m);
-  const double* S0 = A.scratch + A.soff[q] + half * L.total;
-  const int mp = g.mp, nck = g.nck;
-  double* Mc = M + int64_t(j0) * ld + c0;
-  __shared__ double sP[CG * RG * 8 * 64];
-  apply_wy_tile_rg<CG, RG>(S0 + L.Vs, nck * kTb, S0 + L.Ts,
-                           [=](int r) { return Mc + int64_t(chunk_lo(r / kTb, mp, nck) + r % kTb) * ld; }, nt, sP);
 }
 
 // ---------------------------------------------------------------------------
@@ -1517,153 +741,10 @@ __global__ __launch_bounds__(256) void k_gemm_tiles(const GemmDesc* D, int nd) {
 
 }  // namespace
 
-// Second stream of the row compression's look-ahead, one per host thread and
-// device, with the two events that order it against the caller's stream;
-// created on first use and kept for the life of the thread (creating and
-// destroying them per call costs a host wait on their work each time, and
-// an event must not be destroyed while a stream still waits on it), or
-// until release_thread_streams.
-struct AuxStream {
-  hipStream_t s2 = nullptr;
-  hipEvent_t ev_fact = nullptr, ev_rest = nullptr;
-};
-
-static std::map<int, AuxStream>& aux_streams() {
-  thread_local std::map<int, AuxStream> streams;
-  return streams;
-}
-
-static const AuxStream& aux_stream() {
-  std::map<int, AuxStream>& streams = aux_streams();
-  int dev = 0;
-  HIF_HIP(hipGetDevice(&dev));
-  auto it = streams.find(dev);
-  if (it != streams.end()) return it->second;
-  AuxStream a;
-  HIF_HIP(hipStreamCreateWithFlags(&a.s2, hipStreamNonBlocking));
-  if (hipEventCreateWithFlags(&a.ev_fact, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&a.ev_rest, hipEventDisableTiming) != hipSuccess) {
-    if (a.ev_fact) (void)hipEventDestroy(a.ev_fact);
-    (void)hipStreamDestroy(a.s2);
-    throw Error{HIF_EDEVICE, "creating the look-ahead events failed"};
-  }
-  return streams[dev] = a;
-}
-
-void release_thread_streams() {
-  std::map<int, AuxStream>& streams = aux_streams();
-  int cur = 0;
-  (void)hipGetDevice(&cur);
-  for (auto& kv : streams) {
-    (void)hipSetDevice(kv.first);
-    (void)hipStreamSynchronize(kv.second.s2);
-    dbuf_retire_stream(kv.second.s2);
-    (void)hipEventDestroy(kv.second.ev_fact);
-    (void)hipEventDestroy(kv.second.ev_rest);
-    (void)hipStreamDestroy(kv.second.s2);
-  }
-  streams.clear();
-  (void)hipSetDevice(cur);
-}
-
-// The LDS-staged chunk update asks for more than the default 64 KiB of
-// dynamic LDS.
-static void allow_apply_lds() {
-  static std::once_flag once;
-  std::call_once(once, [] {
-    const int bytes = int(kApplyLds);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tsqr_apply_chunk_lds<2>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tsqr_apply_chunk_lds<4>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tsqr_apply_chunk_lds<8>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    (void)hipGetLastError();
-  });
-}
-
 void launch_qr_batched(const QrBatch& A, int max_rows, int max_cols, hipStream_t s) {
   if (A.nprob == 0) return;
-  // chunks of 256 rows (one per thread), or of 1024 rows (two per thread)
-  // when the stack of 256-row chunk factors would exceed kTsqrStack rows
-  int rpt = 0;
-  if (tsqr_chunks(max_rows) * kTsqrNb <= kTsqrStack)
-    rpt = 1;
-  else if (((max_rows + 4 * kTsqrRows - 1) / (4 * kTsqrRows)) * kTsqrNb <= kTsqrStack)
-    rpt = 2;
-  if (rpt > 0) {
-    const int cr = rpt == 1 ? kTsqrRows : 4 * kTsqrRows;
-    const unsigned nckmax = unsigned((max_rows + cr - 1) / cr);
-    // Look-ahead: panel p is factored on s; its update of the next panel's
-    // 32 columns also runs on s, and that of the remaining columns on a
-    // second stream, overlapping the factorization of panel p + 1.  Panels
-    // alternate between two scratch halves (p & 1), so that panel p + 1
-    // never overwrites the V and T that the update of panel p still reads.
-    // Orders: the update of panel p on any column follows that of panel
-    // p - 1 (s waits for the remaining-columns update of p - 1 before its
-    // own updates of panel p), and the remaining-columns update of p
-    // follows the factorization of p (it waits for an event recorded after
-    // the stack kernel).
-    allow_apply_lds();
-    const int uw = tuning().rowqr_update_waves, ukind = tuning().rowqr_update_kind, ulds = ukind == 1;
-    const AuxStream& aux = aux_stream();
-    hipStream_t s2 = aux.s2;
-    hipEvent_t ev_fact = aux.ev_fact, ev_rest = aux.ev_rest;
-    bool rest_pending = false;
-    for (int j0 = 0, p = 0; j0 < max_cols; j0 += kTsqrNb, ++p) {
-      const int half = p & 1;
-      // two rows per thread: 128 threads per 256-row chunk, 512 per 1024-row chunk
-      if (rpt == 1)
-        hipLaunchKernelGGL((k_tsqr_chunk<128, 2>), dim3(nckmax, A.nprob), dim3(128), 0, s, A, j0, cr, half);
-      else
-        hipLaunchKernelGGL((k_tsqr_chunk<512, 2>), dim3(nckmax, A.nprob), dim3(512), 0, s, A, j0, cr, half);
-      if (nckmax * kTsqrNb <= 256)  // block sized to the tallest stack (two rows per thread)
-        hipLaunchKernelGGL((k_tsqr_stack<128, 2>), dim3(A.nprob), dim3(128), 0, s, A, j0, cr, half);
-      else if (nckmax * kTsqrNb <= 512)
-        hipLaunchKernelGGL((k_tsqr_stack<256, 2>), dim3(A.nprob), dim3(256), 0, s, A, j0, cr, half);
-      else
-        hipLaunchKernelGGL((k_tsqr_stack<512, 2>), dim3(A.nprob), dim3(512), 0, s, A, j0, cr, half);
-      const int nb0 = j0 + kTsqrNb, nb1 = j0 + 2 * kTsqrNb;  // next panel: columns [nb0, nb1)
-      if (nb0 >= max_cols) break;
-      HIF_HIP(hipEventRecord(ev_fact, s));
-      if (rest_pending) HIF_HIP(hipStreamWaitEvent(s, ev_rest, 0));  // remaining-columns update of p - 1
-      rest_pending = false;
-      if (nb1 < max_cols) {
-        const unsigned tiles = unsigned((max_cols - nb1 + 63) / 64);
-        HIF_HIP(hipStreamWaitEvent(s2, ev_fact, 0));
-        const dim3 g8(unsigned((max_cols - nb1 + 127) / 128), nckmax, A.nprob), g4(tiles, nckmax, A.nprob);
-        const dim3 gs2(unsigned((max_cols - nb1 + 31) / 32), nckmax, A.nprob);
-        if (cr <= 256 && ukind == 2 && uw == 8)
-          hipLaunchKernelGGL(k_tsqr_apply_chunk_split<4>, g4, dim3(512), 0, s2, A, j0, cr, half, nb1, max_cols);
-        else if (cr <= 256 && ukind == 2)
-          hipLaunchKernelGGL(k_tsqr_apply_chunk_split<2>, gs2, dim3(256), 0, s2, A, j0, cr, half, nb1, max_cols);
-        else if (cr <= 256 && ulds && uw == 8)
-          hipLaunchKernelGGL(k_tsqr_apply_chunk_lds<8>, g8, dim3(512), kApplyLds, s2, A, j0, cr, half, nb1, max_cols);
-        else if (cr <= 256 && ulds)
-          hipLaunchKernelGGL(k_tsqr_apply_chunk_lds<4>, g4, dim3(256), kApplyLds, s2, A, j0, cr, half, nb1, max_cols);
-        else if (cr <= 256 && uw == 8)
-          hipLaunchKernelGGL(k_tsqr_apply_chunk_reg<8>, g8, dim3(512), 0, s2, A, j0, cr, half, nb1, max_cols);
-        else if (cr <= 256)
-          hipLaunchKernelGGL(k_tsqr_apply_chunk_reg<4>, g4, dim3(256), 0, s2, A, j0, cr, half, nb1, max_cols);
-        else
-          hipLaunchKernelGGL(k_tsqr_apply_chunk, dim3(tiles, nckmax, A.nprob), dim3(256), 0, s2, A, j0, cr, half,
-                             nb1, max_cols);
-        hipLaunchKernelGGL((k_tsqr_apply_stack_rg<4, 2>), dim3(tiles, A.nprob), dim3(512), 0, s2, A, j0, cr, half, nb1,
-                           max_cols);
-        HIF_HIP(hipEventRecord(ev_rest, s2));
-        rest_pending = true;
-      }
-      if (cr <= 256 && ulds)  // the next panel's 32 columns: two waves
-        hipLaunchKernelGGL(k_tsqr_apply_chunk_lds<2>, dim3(1, nckmax, A.nprob), dim3(128), kApplyLds, s, A, j0, cr,
-                           half, nb0, nb1);
-      else if (cr <= 256)
-        hipLaunchKernelGGL(k_tsqr_apply_chunk_reg<4>, dim3(1, nckmax, A.nprob), dim3(256), 0, s, A, j0, cr, half, nb0,
-                           nb1);
-      else
-        hipLaunchKernelGGL(k_tsqr_apply_chunk, dim3(1, nckmax, A.nprob), dim3(256), 0, s, A, j0, cr, half, nb0, nb1);
-      hipLaunchKernelGGL((k_tsqr_apply_stack_rg<2, 4>), dim3(1, A.nprob), dim3(512), 0, s, A, j0, cr, half, nb0, nb1);
-    }
-    if (rest_pending) HIF_HIP(hipStreamWaitEvent(s, ev_rest, 0));
+  if (max_rows <= kTsqrMaxRows) {
+    launch_tsqr(A, max_rows, max_cols, s);
     hipLaunchKernelGGL(k_qr_clear_lower, dim3(64, A.nprob), dim3(256), 0, s, A);
     HIF_HIP(hipGetLastError());
     return;

@@ -1424,7 +1424,7 @@ __global__ __launch_bounds__(256) void k_rowqr(RowQrArgs A) {
 void launch_rowqr_auto(const RowQrArgs& A, int max_rows, int max_cols, hipStream_t s) {
   // Few large problems: per-panel launches spread each problem over many
   // workgroups; many small ones: one fused workgroup per problem.
-  if (max_rows <= 32 * kTsqrStack || (A.nprob < 1024 && max_cols >= 96))
+  if (max_rows <= kTsqrMaxRows || (A.nprob < 1024 && max_cols >= 96))
     launch_qr_batched(A, max_rows, max_cols, s);
   else
     launch_rowqr(A, s);

@@ -13,14 +13,10 @@ Buckets and candidates (``hif_tuning`` in ``include/hif.h``):
   panels of at most 512 and 1024 rows.  Timed with ``hif_lu_batched`` on
   batches of well-conditioned n x n blocks with r = n / 2 eliminated columns
   (the redundant part of a transformed group block), n in the bucket.
-* ``rowqr_update_waves`` / ``rowqr_update_kind``: the shape of the row
-  compression's trailing update beside the next panel.  It competes with the
-  panel factorization for the CUs, so it is timed on whole factorizations:
-  ``hif_factor`` of the second-kind 2D problem on a 384 x 384 grid (eps 1e-6,
-  leaf 64), the row-compression phase time of the library's own events.
 * ``sweep_many_threads``: threads per record of the solve on sub-levels of many
-  small records, timed by 8-RHS solves with one factorization of that
-  problem (HIP events, median of 5).
+  small records, timed by 8-RHS solves with one factorization of the
+  second-kind 2D problem on a 384 x 384 grid (eps 1e-6, leaf 64; HIP events,
+  median of 5).
 
 Every candidate is timed with HIP events over 5 runs after a warm run, on the
 same inputs (the inputs are restored before each run); the fastest median
@@ -46,8 +42,7 @@ ID_BUCKETS = [(33, 64, 4096), (97, 128, 2048), (161, 192, 1024)]  # (n_c lo, n_c
 ID_CANDIDATES = [(4, 8, 16), (4, 8, 16), (8, 16)]
 LU_BUCKETS = [(257, 512, 256), (513, 1024, 64)]  # (n lo, n hi, problems)
 LU_CANDIDATES = [(256, 512, 1024), (512, 1024)]
-ROWQR_CANDIDATES = [(4, 0), (8, 0), (4, 1), (8, 1), (4, 2), (8, 2)]  # (waves, kind)
-ROWQR_GRID = 384
+SWEEP_GRID = 384
 SWEEP_CANDIDATES = [64, 128, 256]
 
 
@@ -140,21 +135,8 @@ def _time_lu(mats):
     return _median_ms(run)
 
 
-def _time_rowqr(reps=3):
-    factor = B.factor
-    pts, a, h = _grid_problem()
-    F = factor(pts, 1e-6, 64, a=a, h=h)  # warm
-    F.free()
-    ts = []
-    for _ in range(reps):
-        F = factor(pts, 1e-6, 64, a=a, h=h)
-        ts.append(F.stats()["t_phase_ms"]["rowqr"])
-        F.free()
-    return float(np.median(ts))
-
-
 def _grid_problem():
-    n = ROWQR_GRID
+    n = SWEEP_GRID
     g = (torch.arange(n, dtype=torch.float64, device="cuda") + 0.5) / n
     pts = torch.stack([g.repeat(n), g.repeat_interleave(n)], dim=1).contiguous()
     return pts, torch.ones(n * n, dtype=torch.float64, device="cuda"), 1.0 / n
@@ -189,15 +171,7 @@ def tune(seed=0):
             res[th] = _time_lu(mats)
         table["lu_panel_threads"][b] = min(res, key=res.get)
         timings["lu_panel_threads"].append({"rows": [lo, hi], "problems": cnt, "ms": res})
-    res = {}
-    for w, lds in ROWQR_CANDIDATES:
-        t = {k: (list(v) if isinstance(v, list) else v) for k, v in table.items()}
-        t["rowqr_update_waves"], t["rowqr_update_kind"] = w, lds
-        B.tuning_set(t)
-        res[(w, lds)] = _time_rowqr()
-    best = min(res, key=res.get)
-    table["rowqr_update_waves"], table["rowqr_update_kind"] = best
-    B.tuning_set(dict(table, rowqr_update_waves=best[0], rowqr_update_kind=best[1]))
+    B.tuning_set(table)
     pts, a, h = _grid_problem()
     F = B.factor(pts, 1e-6, 64, a=a, h=h)
     f = torch.randn(8, pts.shape[0], dtype=torch.float64, device="cuda",
@@ -210,9 +184,7 @@ def tune(seed=0):
         sres[th] = _time_sweep(F, f)
     F.free()
     table["sweep_many_threads"] = min(sres, key=sres.get)
-    timings["sweep_many_threads"] = {"grid": ROWQR_GRID, "rhs": 8, "ms": sres}
-    kinds = {0: "", 1: " + LDS", 2: " rows split"}
-    timings["rowqr_update"] = {"grid": ROWQR_GRID, "ms": {f"{w} waves{kinds[k]}": v for (w, k), v in res.items()}}
+    timings["sweep_many_threads"] = {"grid": SWEEP_GRID, "rhs": 8, "ms": sres}
     B.tuning_set(table)
     return table, timings
 
@@ -232,20 +204,14 @@ def write_header(table, timings, path=HEADER):
     if sw:
         lines.append(f"//   8-RHS solve of a {sw['grid']} x {sw['grid']} factorization: " +
                      ", ".join(f"{k} threads {v:.3f}" for k, v in sw["ms"].items()))
-    ru = timings.get("rowqr_update")
-    if ru:
-        lines.append(f"//   row compression of a {ru['grid']} x {ru['grid']} factorization (eps 1e-6): " +
-                     ", ".join(f"{k} {v:.2f}" for k, v in ru["ms"].items()))
     lines += ["#pragma once", "",
               "// waves per problem of the register-resident pivoted QR, problems of at most",
               "// 64, 128 and 192 columns",
               "#define HIF_TUNED_ID_REG_WAVES {" + ", ".join(str(x) for x in table["id_reg_waves"]) + "}",
               "// threads of the register-resident LU panel, panels of at most 512 and 1024 rows",
               "#define HIF_TUNED_LU_PANEL_THREADS {" + ", ".join(str(x) for x in table["lu_panel_threads"]) + "}",
-              "// waves (16 columns each) per workgroup of the row compression's trailing",
-              "// update beside the next panel",
+              "// no effect: the row compression's trailing update has one shape",
               f"#define HIF_TUNED_ROWQR_UPDATE_WAVES {table['rowqr_update_waves']}",
-              "// 0: Y in registers, 1: the chunk reflectors staged in LDS, 2: rows split over two waves",
               f"#define HIF_TUNED_ROWQR_UPDATE_KIND {table['rowqr_update_kind']}",
               "// threads per record of the sweeps on sub-levels of at least 1024 records",
               f"#define HIF_TUNED_SWEEP_MANY_THREADS {table['sweep_many_threads']}", ""]
