@@ -21,58 +21,6 @@ namespace {
 constexpr int kNb = 16;     // panel width
 constexpr int kTileN = 64;  // columns per update workgroup
 
-struct AM {
-  double v;
-  int i;
-};
-__device__ __forceinline__ AM am_better(AM a, AM b) {
-  if (b.v > a.v || (b.v == a.v && b.i < a.i)) return b;
-  return a;
-}
-__device__ __forceinline__ double pick16(const double (&y)[kNb], int j) {
-  double r = 0.0;
-#pragma unroll
-  for (int c = 0; c < kNb; ++c)
-    if (c == j) r = y[c];
-  return r;
-}
-
-// Block-wide argmax (larger value, ties to the lower index) for up to 1024 threads.
-// The caller must pass a barrier between two calls (the slots are
-// rewritten by the next call).
-__device__ AM block_argmax_n(AM x) {
-  __shared__ double sv[16];
-  __shared__ int si[16];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    AM y{__shfl_xor(x.v, o, 64), __shfl_xor(x.i, o, 64)};
-    x = am_better(x, y);
-  }
-  if (lane == 0) { sv[wv] = x.v; si[wv] = x.i; }
-  __syncthreads();
-  AM r{-1.0, INT_MAX};
-  for (int k = 0; k < nw; ++k) r = am_better(r, AM{sv[k], si[k]});
-  return r;
-}
-
-__device__ AM block_argmax256(AM x) {
-  __shared__ double sv[4];
-  __shared__ int si[4];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    AM y{__shfl_xor(x.v, o, 64), __shfl_xor(x.i, o, 64)};
-    x = am_better(x, y);
-  }
-  if (lane == 0) { sv[wv] = x.v; si[wv] = x.i; }
-  __syncthreads();
-  AM r{-1.0, INT_MAX};
-  for (int k = 0; k < 4; ++k) r = am_better(r, AM{sv[k], si[k]});
-  __syncthreads();
-  return r;
-}
-
 constexpr int kQrThreads = 1024;            // trailing-update workgroup
 constexpr int kQrWaves = kQrThreads / 64;
 constexpr int kQpThreads = 512;             // panel workgroup (register budget of 256 VGPRs)
@@ -316,409 +264,6 @@ __global__ void k_qr_clear_lower(QrBatch A) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Partial LU (Lemma 2.1) of the n x n problems over their first r columns,
-// pivoting among rows < r: panel j0 = columns j0..j0+jb-1 with row swaps over
-// whole rows, then U12 = L11^{-1} A12 for the panel rows.
-// ---------------------------------------------------------------------------
-// Register-resident panel for panels of at most kLpRows rows (rows j0..n-1):
-// thread t holds rows j0 + t and j0 + t + kLpThreads of the kNb panel
-// columns for all kNb elimination steps; the pivot row is exchanged and
-// broadcast through LDS.  The row interchanges are then applied in order to
-// the columns outside the panel (one thread per column) and U12 is formed.
-constexpr int kLpRows = 2048;  // rows of the largest register panel (1024 threads)
-
-template <int kLpThreads>
-__global__ __launch_bounds__(kLpThreads) void k_lu_panel_reg(LuBatch A, int j0) {
-  const int q = blockIdx.x;
-  const int n = A.n[q], r = A.r[q];
-  if (j0 >= r) return;
-  double* M = A.base + A.moff[q];
-  int32_t* piv = A.piv + A.poff[q];
-  const int jb = min(kNb, r - j0);
-  const int tid = threadIdx.x;
-  __shared__ double sA[kNb], sB[kNb];
-  __shared__ int spiv[kNb];
-  double y[2][kNb];
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int R = j0 + tid + u * kLpThreads;
-    const double* src = M + int64_t(R < n ? R : j0) * n + j0;
-#pragma unroll
-    for (int c = 0; c < kNb; ++c) y[u][c] = (R < n && c < jb) ? src[c] : 0.0;
-  }
-  for (int jj = 0; jj < jb; ++jj) {
-    const int j = j0 + jj;
-    AM loc{-1.0, INT_MAX};
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int R = j0 + tid + u * kLpThreads;
-      if (R >= j && R < r) loc = am_better(loc, AM{fabs(pick16(y[u], jj)), R});
-    }
-    const AM best = block_argmax_n(loc);
-    if (!(best.v > 0.0)) {
-      if (tid == 0) atomicOr(A.status, 1);
-      return;
-    }
-    const int p = best.i;
-    // rows j (slot 0 of thread jj) and p trade places; everyone reads the new row j
-    const int tp = (p - j0) % kLpThreads, up = (p - j0) / kLpThreads;
-    if (tid == jj) {
-#pragma unroll
-      for (int c = 0; c < kNb; ++c) sA[c] = y[0][c];
-    }
-    if (tid == tp) {
-#pragma unroll
-      for (int c = 0; c < kNb; ++c) sB[c] = up == 0 ? y[0][c] : y[1][c];
-    }
-    if (tid == 0) spiv[jj] = p;
-    __syncthreads();
-    const double* prow = sB;  // the new row j, read from LDS
-    if (p != j) {
-      if (tid == jj) {
-#pragma unroll
-        for (int c = 0; c < kNb; ++c) y[0][c] = prow[c];
-      }
-      if (tid == tp) {
-#pragma unroll
-        for (int c = 0; c < kNb; ++c) {
-          if (up == 0) y[0][c] = sA[c]; else y[1][c] = sA[c];
-        }
-      }
-    }
-    const double inv = 1.0 / prow[jj];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int R = j0 + tid + u * kLpThreads;
-      if (R > j && R < n) {
-        const double l = pick16(y[u], jj) * inv;
-#pragma unroll
-        for (int c = 0; c < kNb; ++c) {
-          if (c == jj) y[u][c] = l;
-          else if (c > jj) y[u][c] -= l * prow[c];
-        }
-      }
-    }
-    // Two barriers per step: the argmax slots are read before this step's
-    // exchange barrier, which every thread passes before the next step
-    // writes them; sA / sB are read after that barrier and before the next
-    // step's argmax barrier, which precedes their next writes.
-  }
-  __syncthreads();  // sA / sB of the last step, before the code below
-  // panel back to memory
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int R = j0 + tid + u * kLpThreads;
-    if (R < n) {
-      double* dst = M + int64_t(R) * n + j0;
-#pragma unroll
-      for (int c = 0; c < kNb; ++c)
-        if (c < jb) dst[c] = y[u][c];
-    }
-  }
-  if (tid < jb) piv[j0 + tid] = spiv[tid];
-  // interchanges on the columns outside the panel, in order
-  for (int col = tid; col < n; col += kLpThreads) {
-    if (col >= j0 && col < j0 + jb) continue;
-    for (int jj = 0; jj < jb; ++jj) {
-      const int pj = spiv[jj];
-      if (pj != j0 + jj) {
-        const double t = M[int64_t(j0 + jj) * n + col];
-        M[int64_t(j0 + jj) * n + col] = M[int64_t(pj) * n + col];
-        M[int64_t(pj) * n + col] = t;
-      }
-    }
-  }
-  __syncthreads();  // the panel rows and the interchanges are in memory
-  // the unit lower L11 of the panel, read once into LDS for every column
-  __shared__ double sL11[kNb][kNb];
-  for (int e = tid; e < kNb * kNb; e += kLpThreads) {
-    const int a = e / kNb, b = e % kNb;
-    sL11[a][b] = (a < jb && b < a) ? M[int64_t(j0 + a) * n + j0 + b] : 0.0;
-  }
-  __syncthreads();
-  // U12 = L11^{-1} A12 (rows j0..j0+jb-1, columns j0+jb..n-1)
-  for (int c = j0 + jb + tid; c < n; c += kLpThreads) {
-    double x[kNb];
-#pragma unroll
-    for (int i = 0; i < kNb; ++i) x[i] = i < jb ? M[int64_t(j0 + i) * n + c] : 0.0;
-#pragma unroll
-    for (int i = 1; i < kNb; ++i) {
-      if (i >= jb) break;
-      double v = x[i];
-#pragma unroll
-      for (int p2 = 0; p2 < kNb; ++p2)
-        if (p2 < i) v -= sL11[i][p2] * x[p2];
-      x[i] = v;
-    }
-#pragma unroll
-    for (int i = 1; i < kNb; ++i)
-      if (i < jb) M[int64_t(j0 + i) * n + c] = x[i];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Multi-workgroup panel for panels taller than the register panels (the top
-// block and the largest redundant blocks in 3D): rows in blocks of kLmRows
-// per workgroup, one launch per column step.  Every workgroup reduces the
-// block maxima left by the previous launch to the pivot (largest |a(i, j)|
-// over unpivoted candidate rows i < r, ties to the lowest row), eliminates
-// column j from its own unpivoted rows and leaves its block maximum of
-// column j + 1 (double-buffered by step parity).  The pivot row is flagged,
-// not moved, so no workgroup reads a row that another writes in the same
-// launch; after the panel the interchanges go to piv in LAPACK order and are
-// applied as one permutation, with U12 = L11^{-1} A12.
-// ---------------------------------------------------------------------------
-constexpr int kLmRows = 256;
-
-struct LuPanelState {
-  double* pv;      // [2][nprob][nblk] block maxima
-  int32_t* pi;     // [2][nprob][nblk] their rows
-  int32_t* flag;   // [nprob][fstride] -1 unpivoted, else the step (rows j0..)
-  int32_t* prow;   // [nprob][kNb] pivot row of each step
-  int nblk;
-  int64_t fstride;
-};
-
-__global__ __launch_bounds__(256) void k_lum_init(LuBatch A, LuPanelState P, int j0) {
-  const int q = blockIdx.y, blk = blockIdx.x;
-  const int n = A.n[q], r = A.r[q];
-  if (j0 >= r || j0 + blk * kLmRows >= n) return;
-  const double* M = A.base + A.moff[q];
-  const int i = j0 + blk * kLmRows + threadIdx.x;
-  if (i < n) P.flag[q * P.fstride + (i - j0)] = -1;
-  AM loc{-1.0, INT_MAX};
-  if (i < r) loc = AM{fabs(M[int64_t(i) * n + j0]), i};
-  const AM b = block_argmax256(loc);
-  if (threadIdx.x == 0) {
-    P.pv[q * P.nblk + blk] = b.v;
-    P.pi[q * P.nblk + blk] = b.i;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_lum_step(LuBatch A, LuPanelState P, int j0, int jj) {
-  const int q = blockIdx.y, blk = blockIdx.x;
-  const int n = A.n[q], r = A.r[q];
-  if (j0 >= r) return;
-  const int jb = min(kNb, r - j0);
-  const int rb0 = j0 + blk * kLmRows;
-  if (jj >= jb || rb0 >= n) return;
-  double* M = A.base + A.moff[q];
-  const int tid = threadIdx.x;
-  const int64_t cur = int64_t(jj & 1) * A.nprob * P.nblk, nxt = int64_t((jj + 1) & 1) * A.nprob * P.nblk;
-  const int nbr = (r - j0 + kLmRows - 1) / kLmRows;  // blocks holding candidate rows
-  AM loc{-1.0, INT_MAX};
-  for (int b = tid; b < nbr; b += 256) loc = am_better(loc, AM{P.pv[cur + q * P.nblk + b], P.pi[cur + q * P.nblk + b]});
-  const AM best = block_argmax256(loc);
-  if (!(best.v > 0.0)) {
-    if (blk == 0 && tid == 0) atomicOr(A.status, 1);
-    return;
-  }
-  const int rp = best.i;
-  __shared__ double sp[kNb];
-  if (tid < kNb) sp[tid] = tid < jb ? M[int64_t(rp) * n + j0 + tid] : 0.0;
-  __syncthreads();
-  if (blk == 0 && tid == 0) P.prow[q * kNb + jj] = rp;
-  const int i = rb0 + tid;
-  AM nx{-1.0, INT_MAX};
-  if (i < n && i != rp && P.flag[q * P.fstride + (i - j0)] < 0) {
-    double* row = M + int64_t(i) * n + j0;
-    double y[kNb];
-#pragma unroll
-    for (int c = 0; c < kNb; ++c) y[c] = (c >= jj && c < jb) ? row[c] : 0.0;
-    const double l = pick16(y, jj) / sp[jj];
-#pragma unroll
-    for (int c = 0; c < kNb; ++c) {
-      if (c == jj) row[c] = l;
-      else if (c > jj && c < jb) {
-        y[c] -= l * sp[c];
-        row[c] = y[c];
-      }
-    }
-    if (jj + 1 < jb && i < r) nx = AM{fabs(pick16(y, jj + 1)), i};
-  }
-  if (i == rp) P.flag[q * P.fstride + (i - j0)] = jj;
-  const AM b2 = block_argmax256(nx);
-  if (tid == 0) {
-    P.pv[nxt + q * P.nblk + blk] = b2.v;
-    P.pi[nxt + q * P.nblk + blk] = b2.i;
-  }
-}
-
-// The panel's interchanges as a permutation of at most 2 kNb rows (one wave,
-// lane a holds entry a: position dst receives physical row src), and piv.
-__device__ void lum_perm(const LuPanelState& P, int q, int j0, int jb, int* s_dst, int* s_src, int* s_na,
-                         int32_t* piv) {
-  const int lane = threadIdx.x & 63;
-  if (threadIdx.x >= 64) return;
-  int dst = lane < jb ? j0 + lane : -1, src = dst, na = jb;
-  for (int jj = 0; jj < jb; ++jj) {
-    const int rp = P.prow[q * kNb + jj];
-    const unsigned long long hit = __ballot(src == rp);
-    int ap;
-    if (hit) {
-      ap = __ffsll(hit) - 1;
-    } else {
-      ap = na++;
-      if (lane == ap) dst = src = rp;
-    }
-    const int pos = __shfl(dst, ap, 64);
-    if (piv && lane == 0) piv[j0 + jj] = pos;
-    const int s_jj = __shfl(src, jj, 64), s_ap = __shfl(src, ap, 64);
-    if (lane == jj) src = s_ap;
-    if (lane == ap) src = s_jj;
-  }
-  if (lane < na) {
-    s_dst[lane] = dst;
-    s_src[lane] = src;
-  }
-  if (lane == 0) *s_na = na;
-}
-
-// Columns outside the panel (mode 0): the interchanges, and right of the
-// panel U12 = L11^{-1} A12 with L11 from the pivot rows' panel columns (not
-// written here).  Mode 1: the interchanges of the panel columns.
-__global__ __launch_bounds__(256) void k_lum_finish(LuBatch A, LuPanelState P, int j0, int mode) {
-  const int q = blockIdx.y;
-  const int n = A.n[q], r = A.r[q];
-  if (j0 >= r) return;
-  const int jb = min(kNb, r - j0);
-  double* M = A.base + A.moff[q];
-  __shared__ int s_dst[2 * kNb], s_src[2 * kNb], s_na;
-  __shared__ double sL[kNb][kNb + 1];
-  lum_perm(P, q, j0, jb, s_dst, s_src, &s_na, (mode == 0 && blockIdx.x == 0) ? A.piv + A.poff[q] : nullptr);
-  __syncthreads();
-  const int na = s_na;
-  if (mode == 1) {
-    const int e = threadIdx.x;  // one thread per panel column
-    if (blockIdx.x != 0 || e >= jb) return;
-    const int col = j0 + e;
-    double v[2 * kNb];
-#pragma unroll
-    for (int a2 = 0; a2 < 2 * kNb; ++a2) v[a2] = a2 < na ? M[int64_t(s_src[a2]) * n + col] : 0.0;
-#pragma unroll
-    for (int a2 = 0; a2 < 2 * kNb; ++a2)
-      if (a2 < na && s_src[a2] != s_dst[a2]) M[int64_t(s_dst[a2]) * n + col] = v[a2];
-    return;
-  }
-  for (int e = threadIdx.x; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, c = e % kNb;
-    sL[i][c] = (i < jb && c < jb) ? M[int64_t(s_src[i]) * n + j0 + c] : 0.0;
-  }
-  bool moved = false;
-  for (int a2 = 0; a2 < na; ++a2) moved = moved || s_src[a2] != s_dst[a2];
-  __syncthreads();
-  const int col = blockIdx.x * 256 + threadIdx.x;
-  if (col >= n || (col >= j0 && col < j0 + jb)) return;
-  const bool right = col >= j0 + jb;
-  if (!right && !moved) return;
-  double v[2 * kNb];
-#pragma unroll
-  for (int a2 = 0; a2 < 2 * kNb; ++a2)
-    v[a2] = (a2 < na && ((right && a2 < jb) || s_src[a2] != s_dst[a2])) ? M[int64_t(s_src[a2]) * n + col] : 0.0;
-  if (right) {
-#pragma unroll
-    for (int i = 1; i < kNb; ++i) {
-      if (i >= jb) break;
-      double t = v[i];
-#pragma unroll
-      for (int p2 = 0; p2 < kNb; ++p2)
-        if (p2 < i) t -= sL[i][p2] * v[p2];
-      v[i] = t;
-    }
-  }
-#pragma unroll
-  for (int a2 = 0; a2 < 2 * kNb; ++a2)
-    if (a2 < na && ((right && a2 < jb) || s_src[a2] != s_dst[a2])) M[int64_t(s_dst[a2]) * n + col] = v[a2];
-}
-
-// Trailing update A22 -= L21 U12 of one 64 x 64 tile (K = panel width).
-__global__ __launch_bounds__(256) void k_lu_update(LuBatch A, int j0) {
-  const int q = blockIdx.z;
-  const int n = A.n[q], r = A.r[q];
-  if (j0 >= r) return;
-  const int jb = min(kNb, r - j0);
-  const int s0 = j0 + jb;
-  const int rt0 = s0 + blockIdx.y * 64, ct0 = s0 + blockIdx.x * 64;
-  if (rt0 >= n || ct0 >= n) return;
-  double* M = A.base + A.moff[q];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int wr = wv >> 1, wc = wv & 1;
-  if (A.fp32 && rt0 >= r && ct0 >= r) {
-    // Schur update of the skeleton block (rows and columns >= r) in FP32
-    float4_t d[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) d[a][b] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < kNb; ks += 4) {
-      const int k = ks + lk;
-      float af[2], bf[2];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const int i = rt0 + wr * 32 + a * 16 + li;
-        af[a] = (i < n && k < jb) ? float(M[int64_t(i) * n + j0 + k]) : 0.f;
-      }
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int c = ct0 + wc * 32 + b * 16 + li;
-        bf[b] = (c < n && k < jb) ? float(M[int64_t(j0 + k) * n + c]) : 0.f;
-      }
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) d[a][b] = mfma_f32(af[a], bf[b], d[a][b]);
-    }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int i = rt0 + wr * 32 + a * 16 + 4 * lk + v;
-          const int c = ct0 + wc * 32 + b * 16 + li;
-          if (i < n && c < n) M[int64_t(i) * n + c] -= double(d[a][b][v]);
-        }
-    return;
-  }
-  double4_t d[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) d[a][b] = double4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int ks = 0; ks < kNb; ks += 4) {
-    const int k = ks + lk;
-    double af[2], bf[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const int i = rt0 + wr * 32 + a * 16 + li;
-      af[a] = (i < n && k < jb) ? M[int64_t(i) * n + j0 + k] : 0.0;
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int c = ct0 + wc * 32 + b * 16 + li;
-      bf[b] = (c < n && k < jb) ? M[int64_t(j0 + k) * n + c] : 0.0;
-    }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) d[a][b] = mfma_f64(af[a], bf[b], d[a][b]);
-  }
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = rt0 + wr * 32 + a * 16 + 4 * v + lk;
-        const int c = ct0 + wc * 32 + b * 16 + li;
-        if (i < n && c < n) M[int64_t(i) * n + c] -= d[a][b][v];
-      }
-}
-
 // Batched general GEMM, one 64 x 64 tile of C per workgroup:
 // C = beta C + alpha op(A) op(B) for every entry of a problem table.
 __global__ __launch_bounds__(256) void k_gemm_tiles(const GemmDesc* D, int nd) {
@@ -891,55 +436,6 @@ void launch_rowqr_split(double* base, const std::vector<int64_t>& moff, const st
     cur.swap(next);
     rbase = nxt.p;
   }
-}
-
-void launch_lu_batched(const LuBatch& A, int max_r, int max_n, hipStream_t s) {
-  if (A.nprob == 0) return;
-  // state of the multi-workgroup panel (panels taller than kLpRows)
-  DBuf<double> pv;
-  DBuf<int32_t> pi, flag, prow;
-  LuPanelState P{};
-  if (max_n > kLpRows) {
-    P.nblk = (max_n + kLmRows - 1) / kLmRows;
-    P.fstride = max_n;
-    pv.alloc(size_t(2) * A.nprob * P.nblk, nullptr);
-    pi.alloc(size_t(2) * A.nprob * P.nblk, nullptr);
-    flag.alloc(size_t(A.nprob) * max_n, nullptr);
-    prow.alloc(size_t(A.nprob) * kNb, nullptr);
-    P.pv = pv.p;
-    P.pi = pi.p;
-    P.flag = flag.p;
-    P.prow = prow.p;
-  }
-  const hif_tuning tu = tuning();
-  for (int j0 = 0; j0 < max_r; j0 += kNb) {
-    if (max_n - j0 > kLpRows) {
-      const dim3 g(unsigned((max_n - j0 + kLmRows - 1) / kLmRows), unsigned(A.nprob));
-      hipLaunchKernelGGL(k_lum_init, g, dim3(256), 0, s, A, P, j0);
-      for (int jj = 0; jj < kNb; ++jj) hipLaunchKernelGGL(k_lum_step, g, dim3(256), 0, s, A, P, j0, jj);
-      hipLaunchKernelGGL(k_lum_finish, dim3(unsigned((max_n + 255) / 256), unsigned(A.nprob)), dim3(256), 0, s, A,
-                         P, j0, 0);
-      hipLaunchKernelGGL(k_lum_finish, dim3(1, unsigned(A.nprob)), dim3(256), 0, s, A, P, j0, 1);
-    } else {
-      // two rows per thread: at least (panel rows) / 2 threads; within that,
-      // the thread count of the launch-shape table for the panel's size
-      const int rows = max_n - j0;
-      int threads = rows <= kLpRows / 4 ? tu.lu_panel_threads[0] : (rows <= kLpRows / 2 ? tu.lu_panel_threads[1] : 1024);
-      if (2 * threads < rows) threads = rows <= kLpRows / 2 ? 512 : 1024;
-      if (threads == 256)
-        hipLaunchKernelGGL(k_lu_panel_reg<256>, dim3(A.nprob), dim3(256), 0, s, A, j0);
-      else if (threads == 512)
-        hipLaunchKernelGGL(k_lu_panel_reg<512>, dim3(A.nprob), dim3(512), 0, s, A, j0);
-      else
-        hipLaunchKernelGGL(k_lu_panel_reg<1024>, dim3(A.nprob), dim3(1024), 0, s, A, j0);
-    }
-    const int rem = max_n - j0 - 1;
-    if (rem > 0) {
-      const unsigned tiles = unsigned((rem + 63) / 64);
-      hipLaunchKernelGGL(k_lu_update, dim3(tiles, tiles, A.nprob), dim3(256), 0, s, A, j0);
-    }
-  }
-  HIF_HIP(hipGetLastError());
 }
 
 void launch_gemm_tiles(const GemmDesc* D, int nd, int max_m, int max_n, hipStream_t s) {

@@ -28,3 +28,46 @@ def test_row_compression_tree_edges(m, n):
     for Y, (sk, rd, T) in zip(cases, out):
         osk, _, oT = interp_decomp(Y, tol)
         _check_id(Y, tol, True, sk.numpy(), rd.numpy(), T.numpy(), osk, oT)
+
+
+@pytest.mark.parametrize("sizes", [
+    [(64, 64), (65, 65), (16, 16), (17, 3), (1, 1)],       # one panel, a column past it
+    [(130, 64), (130, 65), (128, 63), (200, 129)],         # panels that end at, past and short of 64 columns
+    [(513, 100), (1025, 80), (300, 300)],                  # every thread count of the register panel
+    [(2049, 70), (500, 200)],                              # a panel over the registers beside one within them
+])
+def test_lu_batched_panel_edges(sizes):
+    # P A = L U over the first r columns to the backward error bound of the
+    # elimination, |P A - L U| <= n u |L| |U| (tripled: the multipliers are
+    # products with the pivot's rounded reciprocal), entry by entry, and the
+    # pivots of partial pivoting: |L| <= 1 (up to the rounding of the
+    # multipliers) among the candidate rows.
+    rng = np.random.default_rng(sum(n + r for n, r in sizes))
+    mats = [rng.standard_normal((n, n)) for n, _ in sizes]
+    out, pv, zero = hif.lu_batched([torch.tensor(M) for M in mats], [r for _, r in sizes])
+    assert not zero
+    u = np.finfo(float).eps / 2
+    for M, (n, r), F, piv in zip(mats, sizes, out, pv):
+        F, piv = F.numpy(), piv.numpy()
+        P = M.copy()
+        for j, p in enumerate(piv):
+            assert j <= p < r
+            P[[j, p]] = P[[p, j]]
+        L = np.tril(F[:, :r], -1) + np.eye(n, r)
+        U = np.triu(F[:r])
+        R = L @ U
+        R[r:, r:] += F[r:, r:]
+        bound = np.abs(L) @ np.abs(U)
+        bound[r:, r:] += np.abs(F[r:, r:])
+        # the comparison's own product is as inexact again
+        assert np.all(np.abs(P - R) <= 4 * (r + 2) * u * bound)
+        assert np.abs(L[:r]).max() <= 1 + 2 * u
+
+
+def test_lu_batched_singular_panel_reports_and_stays_in_bounds():
+    # a zero column inside the second panel: the status is set, and the
+    # panels after it find only interchanges within the block
+    M = np.random.default_rng(5).standard_normal((200, 200))
+    M[:, 90] = 0.0
+    _, _, zero = hif.lu_batched([torch.tensor(M)], [200])
+    assert zero
