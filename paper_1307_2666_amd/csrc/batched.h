@@ -40,6 +40,9 @@ __host__ __device__ inline int tsqr_chunks(int mp) { return (mp + kTsqrRows - 1)
 __host__ __device__ inline int tsqr_groups(int nck) { return (nck + kTsqrFan - 1) / kTsqrFan; }
 // Problems of at most kTsqrMaxRows rows.
 void launch_tsqr(const QrBatch& A, int max_rows, int max_cols, hipStream_t s);
+// One panel of every problem, from A.j0v and A.jbv, and its update of all
+// columns right of it (at most max_trail of any problem).
+void launch_tsqr_panel(const QrBatch& A, int max_rows, int max_trail, hipStream_t s);
 // Scratch of one problem with m rows (doubles): V of the chunks (m x nb) | T
 // per chunk | stacked chunk R, replaced by V of the groups | T per group |
 // with several groups, their stacked R, replaced by V of the root, and its T.

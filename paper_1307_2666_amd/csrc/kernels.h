@@ -61,9 +61,13 @@ struct IdArgs {
   int skip_cols = 0;
 };
 void launch_id(const IdArgs& A, int max_cols, hipStream_t s);
-// Blocked pivoted QR on the uncompressed problems (rows up to max_rows), same
-// outputs as launch_id; id_blocked_fits says whether a batch suits it.
+// Blocked pivoted QR (pqr.hip) of problems of any shape, rows up to max_rows,
+// same outputs as launch_id; id_blocked_fits says whether a batch suits it.
 void launch_id_blocked(const IdArgs& A, int max_rows, int max_cols, hipStream_t s);
+// T = R11^{-1} R12 in place over R12 (ranks up to kmax), R_ii in alpha + q stride,
+// and its compact copy where A.Tout asks for one.
+void launch_id_T(const IdArgs& A, double* alpha, int64_t stride, int kmax, int max_cols, hipStream_t s);
+void launch_id_Tcopy(const IdArgs& A, int max_cols, hipStream_t s);
 bool id_blocked_fits(int nprob, int max_rows, int max_cols);
 // Whether launch_id runs a problem of rows x cols (after row compression) in
 // registers, in a batch whose widest problem has max_cols columns.
@@ -84,6 +88,10 @@ struct RowQrArgs {
   double* scratch;       // per problem: rowqr_scratch(m, n) doubles
   const int64_t* soff;
   int nprob = 0;
+  // set by the pivoted QR: problem q factors columns j0v[q] .. j0v[q] + jbv[q] - 1
+  // as its next panel (none if jbv[q] = 0), whatever its shape
+  const int32_t* j0v = nullptr;
+  const int32_t* jbv = nullptr;
 };
 void launch_rowqr(const RowQrArgs& A, hipStream_t s);
 void launch_rowqr_auto(const RowQrArgs& A, int max_rows, int max_cols, hipStream_t s);

@@ -29,13 +29,23 @@ static_assert(kTb == 32, "the lane layout below holds two column groups of 16");
 struct PanelGeom {
   int mp, jb, nck, ng;
 };
-__device__ __forceinline__ PanelGeom panel_geom(int m, int n, int j0) {
-  PanelGeom g;
+// The panel of problem q: the one at the given j0 where that is a panel of its
+// row compression, or the one the pivoted QR has chosen (j0 is set to its
+// first column).  false: none.
+__device__ __forceinline__ bool panel_geom(const QrBatch& A, int q, int& j0, PanelGeom& g) {
+  const int m = A.rows[q], n = A.cols[q];
+  if (A.j0v) {
+    j0 = A.j0v[q];
+    g.jb = A.jbv[q];
+    if (g.jb <= 0) return false;
+  } else {
+    if (m <= n || j0 >= n) return false;
+    g.jb = min(kTb, n - j0);
+  }
   g.mp = m - j0;
-  g.jb = min(kTb, n - j0);
   g.nck = tsqr_chunks(g.mp);
   g.ng = g.nck > 1 ? tsqr_groups(g.nck) : 0;
-  return g;
+  return true;
 }
 __device__ __forceinline__ int part_lo(int i, int total, int parts) {
   return int(unsigned(i) * unsigned(total) / unsigned(parts));  // total <= 32768 rows, i <= parts <= 128
@@ -213,10 +223,9 @@ __device__ __forceinline__ void build_T(FactLds<NW>& L, double* Tout) {
 template <int NW, int LEVEL>
 __global__ __launch_bounds__(64 * NW) void k_tsqr_fact(QrBatch A, int j0, int half) {
   const int q = blockIdx.y, x = blockIdx.x;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const PanelGeom g = panel_geom(m, n, j0);
-  const TsqrLayout L = tsqr_layout(m);
+  PanelGeom g;
+  if (!panel_geom(A, q, j0, g)) return;
+  const TsqrLayout L = tsqr_layout(A.rows[q]);
   double* S0 = A.scratch + A.soff[q] + half * L.total;
   const int ld = A.ld[q];
   double* Mj = A.base + A.moff[q] + int64_t(j0) * ld + j0;
@@ -313,12 +322,15 @@ __global__ __launch_bounds__(64 * NW) void k_tsqr_fact(QrBatch A, int j0, int ha
 template <int NW, int LEVEL>
 __global__ __launch_bounds__(64 * NW, 2) void k_tsqr_apply(QrBatch A, int j0, int half, int cbeg, int cend, int tpw) {
   const int q = blockIdx.z, x = blockIdx.y;
-  const int m = A.rows[q], n = A.cols[q];
-  if (m <= n || j0 >= n) return;
-  const int c0 = cbeg + int(blockIdx.x) * 16 * tpw, ce = min(min(n, cend), c0 + 16 * tpw);
+  PanelGeom g;
+  if (!panel_geom(A, q, j0, g)) return;
+  if (A.j0v) {
+    cbeg = j0 + g.jb;
+    cend = A.cols[q];
+  }
+  const int c0 = cbeg + int(blockIdx.x) * 16 * tpw, ce = min(min(A.cols[q], cend), c0 + 16 * tpw);
   if (c0 >= ce) return;
-  const PanelGeom g = panel_geom(m, n, j0);
-  const TsqrLayout L = tsqr_layout(m);
+  const TsqrLayout L = tsqr_layout(A.rows[q]);
   const double* S0 = A.scratch + A.soff[q] + half * L.total;
   const int ld = A.ld[q];
   double* Mj = A.base + A.moff[q] + int64_t(j0) * ld;
@@ -577,6 +589,21 @@ void launch_tsqr(const QrBatch& A, int max_rows, int max_cols, hipStream_t s) {
     if (ng > 1) launch_apply<8, 2>(A, j0, half, nb0, ne, 1, s);
   }
   if (rest_pending) HIF_HIP(hipStreamWaitEvent(s, aux.ev_rest, 0));
+  HIF_HIP(hipGetLastError());
+}
+
+void launch_tsqr_panel(const QrBatch& A, int max_rows, int max_trail, hipStream_t s) {
+  const int nck = std::max(1, tsqr_chunks(max_rows)), ng = tsqr_groups(nck);
+  const unsigned np = unsigned(A.nprob);
+  hipLaunchKernelGGL((k_tsqr_fact<4, 0>), dim3(unsigned(nck), np), dim3(256), 0, s, A, 0, 0);
+  if (nck > 1) hipLaunchKernelGGL((k_tsqr_fact<8, 1>), dim3(unsigned(ng), np), dim3(512), 0, s, A, 0, 0);
+  if (ng > 1) hipLaunchKernelGGL((k_tsqr_fact<8, 2>), dim3(1, np), dim3(512), 0, s, A, 0, 0);
+  if (max_trail > 0) {
+    // the columns themselves come from each problem's panel; max_trail sizes the grid
+    launch_apply<4, 0>(A, 0, 0, 0, max_trail, nck, s);
+    if (nck > 1) launch_apply<8, 1>(A, 0, 0, 0, max_trail, ng, s);
+    if (ng > 1) launch_apply<8, 2>(A, 0, 0, 0, max_trail, 1, s);
+  }
   HIF_HIP(hipGetLastError());
 }
 

@@ -71,3 +71,40 @@ def test_lu_batched_singular_panel_reports_and_stays_in_bounds():
     M[:, 90] = 0.0
     _, _, zero = hif.lu_batched([torch.tensor(M)], [200])
     assert zero
+
+
+@pytest.mark.parametrize("m,n,decay,tol", [
+    (128, 128, 5.0, 1e-3), (140, 129, 12.0, 1e-9),   # one and two chunks; several Gram matrices
+    (300, 1024, 9.0, 1e-6), (300, 1025, 9.0, 1e-6),  # the last width with the Cholesky rows in registers
+    (200, 2049, 6.0, 1e-4), (200, 4096, 6.0, 1e-4),  # several columns per thread
+    (1, 200, 3.0, 1e-2), (33, 400, 3.0, 1e-8),       # fewer rows than a block; a block of one column after a full one
+])
+def test_blocked_pivoted_qr_edges(m, n, decay, tol):
+    # The pivots come from Gram matrices good to about 1e-10 of the largest
+    # squared norm; random columns of separated scales are further apart, so
+    # the skeleton and T are the oracle's.  Two problems share the batch.
+    rng = np.random.default_rng(m * 7 + n)
+    cases = []
+    for mm, nn in ((m, n), (max(1, m - 1), max(128, n - 3))):
+        cases.append(rng.standard_normal((mm, nn)) * (10.0 ** (-decay * np.arange(nn) / nn))[rng.permutation(nn)])
+    out = hif.id_batched([torch.tensor(Y) for Y in cases], [tol] * len(cases))
+    for Y, (sk, rd, T) in zip(cases, out):
+        osk, _, oT = interp_decomp(Y, tol)
+        _check_id(Y, tol, True, sk.numpy(), rd.numpy(), T.numpy(), osk, oT)
+
+
+def test_blocked_pivoted_qr_zero_tied_and_nonfinite_columns():
+    # Zero columns are never pivots; of equal columns the lowest is chosen
+    # first and the others vanish; a column of NaN is never chosen and does not
+    # stop the others.
+    rng = np.random.default_rng(4)
+    Y = np.repeat(rng.standard_normal((150, 40)) * 10.0 ** (-np.arange(40) / 10.0), 5, axis=1)
+    Y[:, 17] = 0.0
+    (sk, rd, T), = hif.id_batched([torch.tensor(Y)], [1e-9])
+    osk, _, oT = interp_decomp(Y, 1e-9)
+    assert sk.numel() == 40 and set((sk.numpy() // 5).tolist()) == set(range(40))
+    assert np.all(sk.numpy() % 5 <= 1) and 17 not in sk.tolist()
+    assert np.linalg.norm(Y[:, rd.numpy()] - Y[:, sk.numpy()] @ T.numpy()) <= 1e-9 * np.linalg.norm(Y)
+    Y[:, 3] = np.nan
+    (sk, rd, T), = hif.id_batched([torch.tensor(Y)], [1e-9])
+    assert sk.numel() == 40 and 3 not in sk.tolist()
