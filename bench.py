@@ -54,12 +54,12 @@ HBM_PEAK_GBS = 8000.0
 # (see the profile summaries); None until taken for the kernels as they stand.
 # 267 GB read + 73 GB written per factorization (profiles/hbm_traffic_id_sq512.md).
 ID_STEP_TRAFFIC_BYTES = 340.50e9
-# ALU roof of the exact pair-by-pair product (2D, 8 right-hand sides, two
-# targets per thread): its inner loop issues 110 vector instructions per
-# source for two targets, 55 per pair (log, distance, select, 8 FMAs); a
+# ALU roof of the exact pair-by-pair product (2D, 8 right-hand sides): its
+# inner loop issues 157 vector instructions for four pairs, 39 per pair (log,
+# distance, 8 FMAs); a
 # wave64 vector instruction takes 4 cycles of a 16-lane SIMD, so the chip
 # issues 256 CUs x 64 lanes x 2.4 GHz lane-operations per second.
-MATVEC_VALU_PER_PAIR = 55
+MATVEC_VALU_PER_PAIR = 39
 VALU_LANE_OPS_PER_S = 256 * 64 * 2.4e9
 
 

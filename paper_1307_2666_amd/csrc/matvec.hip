@@ -1,31 +1,46 @@
 // Exact on-the-fly y = A x for A = diag(a) + diag(b) K diag(c) (eqn 1.1 under
 // the collocation of Section 3.1): K_ij = G(|x_i - x_j|) w_j off the
-// diagonal, K_ii the cell integral.  O(N^2) pair evaluations; each workgroup
-// owns 256 targets and streams the sources through LDS in tiles, all
-// right-hand sides (up to 8 per pass) sharing one kernel evaluation per pair.
+// diagonal, K_ii the cell integral.  O(N^2) pair evaluations; the waves of a
+// workgroup share its targets and divide the sources, which they stream
+// through LDS in tiles of their own; all right-hand sides (up to 8 per pass)
+// share one kernel evaluation per pair.
+#include <type_traits>
+
 #include "common.h"
 
 namespace hif {
 
 namespace {
 
-constexpr int kTile = 256;
-
-// Natural logarithm of a positive normal x, within about 2 ulp, in some 30
-// instructions (the library's double-precision log carries extra-precise
-// steps that cost several times that, and the pair loop below is bound by
-// it).  x = 2^e m with m in [sqrt(1/2), sqrt(2)); with s = (m - 1) / (m + 1),
-// |s| <= 3 - 2 sqrt(2) < 0.1716, log m = 2 atanh(s) = 2 s sum_k s^(2k) /
-// (2k + 1), whose terms past s^18 sum to below 2^-55 relative (s^2 < 0.0295);
-// log x = e ln2_hi + (e ln2_lo + log m), ln2_hi holding 29 significant bits so
-// that e ln2_hi is exact.
-__device__ __forceinline__ double log_pos(double x) {
+// Natural logarithm of a positive normal x, within about 2 ulp (the library's
+// double-precision log carries extra-precise steps that cost several times as
+// much, and the pair loop below is bound by it).  x = 2^e m with m in
+// [sqrt(1/2), sqrt(2)); with s = (m - 1) / (m + 1), |s| <= 3 - 2 sqrt(2) <
+// 0.1716, log m = 2 atanh(s) = 2 s + 2 s z P(z), z = s^2, P(z) = sum z^k /
+// (2k + 3); the coefficients are those of P's Chebyshev expansion of degree 6
+// on [0, (3 - 2 sqrt 2)^2], off by less than 2^-57 of the logarithm (the power
+// series takes two more).  log x = e ln2_hi + (e ln2_lo + log m), ln2_hi
+// holding 29 significant bits so that e ln2_hi is exact.
+// The constants of the pair loop in registers: as literals each would be moved
+// into place ahead of its fused multiply-add.
+struct LogCoef {
+  double c[7], lo, hi;
+  __device__ LogCoef()
+      : c{0.3333333333333333, 0.19999999999965573, 0.1428571430871919, 0.111111060617156, 0.09091416704888747,
+          0.07666614987761301, 0.07300366937947979},
+        lo(-4.2009150726810846e-11),
+        hi(0.6931471806019545) {
+#pragma unroll
+    for (int k = 0; k < 7; ++k) asm volatile("" : "+v"(c[k]));
+    asm volatile("" : "+v"(lo), "+v"(hi));
+  }
+};
+__device__ __forceinline__ double log_pos(double x, const LogCoef& L) {
   double m = __builtin_amdgcn_frexp_mant(x);  // [0.5, 1)
   int e = __builtin_amdgcn_frexp_exp(x);
-  if (m < 0.70710678118654752440) {
-    m *= 2.0;
-    e -= 1;
-  }
+  const bool lo = m < 0.70710678118654752440;
+  m = __builtin_amdgcn_ldexp(m, lo ? 1 : 0);
+  e -= lo ? 1 : 0;
   const double f = m - 1.0;  // exact
   const double d = m + 1.0;
   double t = __builtin_amdgcn_rcp(d);
@@ -33,145 +48,199 @@ __device__ __forceinline__ double log_pos(double x) {
   double q = f * t;
   q = fma(fma(-q, d, f), t, q);  // s = f / d, corrected once
   const double z = q * q;
-  double p = 1.0 / 19.0;
-  p = fma(p, z, 1.0 / 17.0);
-  p = fma(p, z, 1.0 / 15.0);
-  p = fma(p, z, 1.0 / 13.0);
-  p = fma(p, z, 1.0 / 11.0);
-  p = fma(p, z, 1.0 / 9.0);
-  p = fma(p, z, 1.0 / 7.0);
-  p = fma(p, z, 1.0 / 5.0);
-  p = fma(p, z, 1.0 / 3.0);
+  double p = L.c[6];
+#pragma unroll
+  for (int k = 5; k >= 0; --k) p = fma(p, z, L.c[k]);
   const double s2 = 2.0 * q;
   const double ed = double(e);
-  const double lo = fma(s2 * z, p, ed * -4.2009150726810846e-11);  // + e ln2_lo
-  return fma(ed, 0.6931471806019545, s2 + lo);
+  const double r = fma(s2 * z, p, ed * L.lo);  // + e ln2_lo
+  return fma(ed, L.hi, s2 + r);
 }
 
-// G(r) from the squared distance for the pair loop (2D through log_pos).
+// G(r) without its constant factor from the squared distance: log r^2 (2D) or
+// 1 / r (3D).  1 / r: the hardware's estimate (2^-24 or better) and one
+// third-order step; r = 0 keeps the estimate's infinity.
 template <int D>
-__device__ __forceinline__ double green_pair(double r2) {
-  if constexpr (D == 2) {
-    return -0.5 * kInv2Pi * log_pos(r2);
-  } else {
-    return kInv4Pi * rsqrt(r2);
+struct Green;
+template <>
+struct Green<2> {
+  static constexpr double factor = -0.5 * kInv2Pi;
+  LogCoef L;
+  __device__ __forceinline__ double operator()(double r2) const { return log_pos(r2, L); }
+};
+template <>
+struct Green<3> {
+  static constexpr double factor = kInv4Pi;
+  __device__ __forceinline__ double operator()(double r2) const {
+    const double y = __builtin_amdgcn_rsq(r2);
+    const double e = fma(-r2 * y, y, 1.0);
+    const double v = fma(y * e, fma(e, 0.375, 0.5), y);
+    return r2 > 0.0 ? v : y;
   }
-}
+};
 
-// Each workgroup owns TPT * 256 targets (thread t: targets t + 256 u) and
-// streams the sources through LDS in tiles of 256: the point and the
-// weighted right-hand-side values of a source are read once per tile and
-// serve TPT targets; all right-hand sides (up to 8 per pass) share one kernel
-// evaluation per pair.  The self pair is dropped by a select, not a branch.
-template <int D, int NR, int TPT>
-__global__ __launch_bounds__(kTile) void k_matvec(const double* __restrict__ pts, int64_t n,
-                                                  const double* __restrict__ a, const double* __restrict__ b,
-                                                  const double* __restrict__ c, const double* __restrict__ w,
-                                                  double w_const, const double* __restrict__ selfk,
-                                                  double self_const, const double* __restrict__ x,
-                                                  double* __restrict__ y, int64_t ldx, int nr) {
-  __shared__ double sp[kTile][D];
-  __shared__ double sq[kTile][NR];
-  int64_t i[TPT];
-  double xi[TPT][D];
-  double acc[TPT][NR];
+// Workgroup of NW waves: L = 64 / SPL lanes hold TPT targets each (the same
+// L TPT targets in every wave), lane group s = lane / L of wave w takes the
+// sources s, s + SPL, ... of the tiles of 64 it streams, w, w + NW, ...  The
+// partial sums are added over the groups and then the waves, in order.
+// Bound by the vector ALU: per pair the distance, G (about 25 instructions in
+// 2D, 7 in 3D) and one multiply-add per right-hand side (39 and 20 in all with
+// 8 and 5 of them; 80% of the issue rate at 262144 points in 2D), against the
+// LDS reads of a source's D + NR values, which TPT targets share.  Before, a
+// workgroup's 256 lanes held a target each and passed over all sources, one
+// wave a SIMD at 50000 points: 49999 points in 3D with 5 right-hand sides 7.5
+// -> 2.1 ms, 65536 in 2D with 4 11.7 -> 4.9 ms, 262144 with 8 126 -> 87 ms,
+// 5000 with one 0.85 -> 0.06 ms.
+template <int D, int NR, int TPT, int SPL, int NW>
+__global__ __launch_bounds__(64 * NW) void k_matvec(const double* __restrict__ pts, int64_t n,
+                                                    const double* __restrict__ a, const double* __restrict__ b,
+                                                    const double* __restrict__ c, const double* __restrict__ w,
+                                                    double w_const, const double* __restrict__ selfk,
+                                                    double self_const, const double* __restrict__ x,
+                                                    double* __restrict__ y, int64_t ldx) {
+  constexpr int L = 64 / SPL, WS = (D + NR + 1) & ~1;
+  static_assert(L * TPT <= 64 * WS, "the partial sums reuse the tiles");
+  alignas(16) __shared__ double st[NW][64][WS];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tl = lane % L, sl = lane / L;
+  const int64_t i0 = blockIdx.x * int64_t(L * TPT);
+  const Green<D> green;
+  double xi[TPT][D], acc[TPT][NR];
 #pragma unroll
   for (int u = 0; u < TPT; ++u) {
-    i[u] = (blockIdx.x * int64_t(TPT) + u) * kTile + threadIdx.x;
+    const int64_t i = i0 + u * L + tl;
 #pragma unroll
-    for (int k = 0; k < D; ++k) xi[u][k] = i[u] < n ? pts[i[u] * D + k] : 4.0 + k;
+    for (int k = 0; k < D; ++k) xi[u][k] = i < n ? pts[i * D + k] : 4.0 + k;
 #pragma unroll
     for (int v = 0; v < NR; ++v) acc[u][v] = 0.0;
   }
-  for (int64_t j0 = 0; j0 < n; j0 += kTile) {
-    const int64_t j = j0 + threadIdx.x;
-    __syncthreads();
+  double src[D + NR];  // this lane's source of the next tile
+  auto fetch = [&](int64_t j0) {
+    const int64_t j = j0 + lane;
     if (j < n) {
 #pragma unroll
-      for (int k = 0; k < D; ++k) sp[threadIdx.x][k] = pts[j * D + k];
+      for (int k = 0; k < D; ++k) src[k] = pts[j * D + k];
       const double wc = (w ? w[j] : w_const) * (c ? c[j] : 1.0);
 #pragma unroll
-      for (int v = 0; v < NR; ++v) sq[threadIdx.x][v] = v < nr ? wc * x[v * ldx + j] : 0.0;
+      for (int v = 0; v < NR; ++v) src[D + v] = wc * x[v * ldx + j];
     } else {
 #pragma unroll
-      for (int k = 0; k < D; ++k) sp[threadIdx.x][k] = 2.0 + k;  // far away, weight 0
+      for (int k = 0; k < D; ++k) src[k] = 2.0 + k;  // far away, weight 0
 #pragma unroll
-      for (int v = 0; v < NR; ++v) sq[threadIdx.x][v] = 0.0;
+      for (int v = 0; v < NR; ++v) src[D + v] = 0.0;
     }
-    __syncthreads();
-    const int cnt = int(n - j0 < kTile ? n - j0 : kTile);
-    int self_t[TPT];
+  };
+  fetch(int64_t(wv) * 64);
+  for (int64_t j0 = int64_t(wv) * 64; j0 < n; j0 += 64 * NW) {
+    __builtin_amdgcn_wave_barrier();  // the wave's own tile: its LDS accesses are in order
 #pragma unroll
-    for (int u = 0; u < TPT; ++u) self_t[u] = (i[u] >= j0 && i[u] < j0 + kTile) ? int(i[u] - j0) : -1;
-    for (int t = 0; t < cnt; ++t) {
-      double q[NR];
+    for (int k = 0; k < D + NR; ++k) st[wv][lane][k] = src[k];
+    if (j0 + 64 * NW < n) fetch(j0 + 64 * NW);
+    __builtin_amdgcn_wave_barrier();
+    auto pass = [&](auto self_tile) {
+#pragma unroll 2
+      for (int t = 0; t < 64; t += SPL) {
+        double s[WS];
+        const double* row = st[wv][t + sl];
 #pragma unroll
-      for (int v = 0; v < NR; ++v) q[v] = sq[t][v];
-#pragma unroll
-      for (int u = 0; u < TPT; ++u) {
-        double r2 = 0.0;
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-          const double dd = xi[u][k] - sp[t][k];
-          r2 += dd * dd;
+        for (int k = 0; k < WS; k += 2) {
+          const double2 v = *reinterpret_cast<const double2*>(row + k);
+          s[k] = v.x;
+          s[k + 1] = v.y;
         }
-        const bool self = t == self_t[u];
-        const double g = self ? 0.0 : green_pair<D>(self ? 1.0 : r2);
 #pragma unroll
-        for (int v = 0; v < NR; ++v) acc[u][v] += g * q[v];
+        for (int u = 0; u < TPT; ++u) {
+          double r2 = 0.0;
+#pragma unroll
+          for (int k = 0; k < D; ++k) {
+            const double dd = xi[u][k] - s[k];
+            r2 = k == 0 ? dd * dd : fma(dd, dd, r2);
+          }
+          double g;
+          if constexpr (decltype(self_tile)::value) {  // the self pair is dropped by a select
+            const bool self = j0 + t + sl == i0 + u * L + tl;
+            g = green(self ? 1.0 : r2);
+            g = self ? 0.0 : g;
+          } else {
+            g = green(r2);
+          }
+#pragma unroll
+          for (int v = 0; v < NR; ++v) acc[u][v] = fma(g, s[D + v], acc[u][v]);
+        }
       }
-    }
+    };
+    if (j0 < i0 + L * TPT && j0 + 64 > i0)
+      pass(std::true_type{});
+    else
+      pass(std::false_type{});
   }
+  // partial sums: over the lane groups, then the waves
 #pragma unroll
-  for (int u = 0; u < TPT; ++u) {
-    if (i[u] >= n) continue;
-    const int64_t ii = i[u];
-    const double ai = a ? a[ii] : 0.0, bi = b ? b[ii] : 1.0, ci = c ? c[ii] : 1.0;
-    const double si = selfk ? selfk[ii] : self_const;
+  for (int u = 0; u < TPT; ++u)
 #pragma unroll
     for (int v = 0; v < NR; ++v)
-      if (v < nr) {
-        const double xv = x[v * ldx + ii];
-        y[v * ldx + ii] = ai * xv + bi * (acc[u][v] + si * ci * xv);
-      }
+#pragma unroll
+      for (int o = L; o < 64; o *= 2) acc[u][v] += __shfl_xor(acc[u][v], o, 64);
+  double* part = &st[0][0][0];
+#pragma unroll
+  for (int v = 0; v < NR; ++v) {
+    __syncthreads();  // the tiles, or the sums of the last vector, have been read
+    if (sl == 0) {
+#pragma unroll
+      for (int u = 0; u < TPT; ++u) part[wv * 64 * WS + u * L + tl] = acc[u][v];
+    }
+    __syncthreads();
+    for (int e = tid; e < L * TPT; e += 64 * NW) {
+      const int64_t i = i0 + e;
+      if (i >= n) continue;
+      double s = 0.0;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) s += part[k * 64 * WS + e];
+      const double ai = a ? a[i] : 0.0, bi = b ? b[i] : 1.0, ci = c ? c[i] : 1.0;
+      const double si = selfk ? selfk[i] : self_const;
+      const double xv = x[v * ldx + i];
+      y[v * ldx + i] = ai * xv + bi * (Green<D>::factor * s + si * ci * xv);
+    }
   }
 }
 
-template <int D, int TPT>
-void launch_t(const double* pts, int64_t n, const double* a, const double* b, const double* c, const double* w,
-              double w_const, const double* selfk, double self_const, const double* x, double* y, int64_t nrhs,
-              hipStream_t s) {
-  const unsigned blocks = unsigned((n + TPT * kTile - 1) / (TPT * kTile));
-  for (int64_t v0 = 0; v0 < nrhs; v0 += 8) {
-    const int nr = int(std::min<int64_t>(8, nrhs - v0));
-    const double* xv = x + v0 * n;
-    double* yv = y + v0 * n;
-    if (nr == 1)
-      hipLaunchKernelGGL((k_matvec<D, 1, TPT>), dim3(blocks), dim3(kTile), 0, s, pts, n, a, b, c, w, w_const, selfk,
-                         self_const, xv, yv, n, nr);
-    else if (nr <= 2)
-      hipLaunchKernelGGL((k_matvec<D, 2, TPT>), dim3(blocks), dim3(kTile), 0, s, pts, n, a, b, c, w, w_const, selfk,
-                         self_const, xv, yv, n, nr);
-    else if (nr <= 4)
-      hipLaunchKernelGGL((k_matvec<D, 4, TPT>), dim3(blocks), dim3(kTile), 0, s, pts, n, a, b, c, w, w_const, selfk,
-                         self_const, xv, yv, n, nr);
-    else
-      hipLaunchKernelGGL((k_matvec<D, 8, TPT>), dim3(blocks), dim3(kTile), 0, s, pts, n, a, b, c, w, w_const, selfk,
-                         self_const, xv, yv, n, nr);
-    HIF_HIP(hipGetLastError());
-  }
+template <int D, int NR>
+void launch_nr(const double* pts, int64_t n, const double* a, const double* b, const double* c, const double* w,
+               double w_const, const double* selfk, double self_const, const double* x, double* y, hipStream_t s) {
+  // Targets per workgroup: 64 TPT / SPL.
+  auto run = [&](auto tpt, auto spl, auto nw) {
+    constexpr int TPT = decltype(tpt)::value, SPL = decltype(spl)::value, NW = decltype(nw)::value;
+    const int64_t tw = 64 / SPL * TPT;
+    hipLaunchKernelGGL((k_matvec<D, NR, TPT, SPL, NW>), dim3(unsigned((n + tw - 1) / tw)), dim3(64 * NW), 0, s, pts, n,
+                       a, b, c, w, w_const, selfk, self_const, x, y, n);
+  };
+  using std::integral_constant;
+  constexpr integral_constant<int, (NR <= 4 ? 4 : 2)> many;  // targets a lane: as many as leave 3 waves a SIMD
+  if (n >= (int64_t(1) << 18))
+    run(many, integral_constant<int, 1>{}, integral_constant<int, 4>{});
+  else if (n >= (int64_t(1) << 15))  // four lanes a target: workgroups for every CU
+    run(many, integral_constant<int, 4>{}, integral_constant<int, 4>{});
+  else  // fewer targets and more waves a workgroup
+    run(integral_constant<int, 1>{}, integral_constant<int, 4>{}, integral_constant<int, 8>{});
+  HIF_HIP(hipGetLastError());
 }
 
-// Two targets per thread once there are enough targets to give every CU
-// several workgroups of them.
 template <int D>
 void launch(const double* pts, int64_t n, const double* a, const double* b, const double* c, const double* w,
             double w_const, const double* selfk, double self_const, const double* x, double* y, int64_t nrhs,
             hipStream_t s) {
-  if (n >= (int64_t(1) << 18))
-    launch_t<D, 2>(pts, n, a, b, c, w, w_const, selfk, self_const, x, y, nrhs, s);
-  else
-    launch_t<D, 1>(pts, n, a, b, c, w, w_const, selfk, self_const, x, y, nrhs, s);
+  const int64_t passes = (nrhs + 7) / 8;
+  for (int64_t p = 0; p < passes; ++p) {  // right-hand sides divided evenly
+    const int64_t v0 = nrhs * p / passes, nr = nrhs * (p + 1) / passes - v0;
+    const double* xv = x + v0 * n;
+    double* yv = y + v0 * n;
+#define HIF_CASE(NR) \
+  case NR: launch_nr<D, NR>(pts, n, a, b, c, w, w_const, selfk, self_const, xv, yv, s); break;
+    switch (nr) {
+      HIF_CASE(1) HIF_CASE(2) HIF_CASE(3) HIF_CASE(4) HIF_CASE(5) HIF_CASE(6) HIF_CASE(7) HIF_CASE(8)
+    }
+#undef HIF_CASE
+  }
 }
 
 }  // namespace

@@ -108,3 +108,31 @@ def test_blocked_pivoted_qr_zero_tied_and_nonfinite_columns():
     Y[:, 3] = np.nan
     (sk, rd, T), = hif.id_batched([torch.tensor(Y)], [1e-9])
     assert sk.numel() == 40 and 3 not in sk.tolist()
+
+
+@pytest.mark.parametrize("d", [2, 3])
+@pytest.mark.parametrize("n,nrhs", [(1, 1), (63, 2), (65, 3), (257, 9), (1000, 6), (32767, 4), (32768, 5),
+                                    (262143, 1), (262144, 7)])
+def test_matvec_sizes_and_right_hand_sides(d, n, nrhs):
+    # The product at the sizes where its split of targets and sources changes
+    # and for every number of right-hand sides a pass takes, against sampled
+    # rows: a row's sum of n terms is off by at most n u of the sum of their
+    # magnitudes, each term by 8 u (the kernel within 2 ulp, the distance and
+    # weights); G is small near r = 1, so its own scale is kept above 1e-3.
+    gen = np.random.default_rng(n + 10 * nrhs + d)
+    pts = gen.random((n, d))
+    w, s, a, b, c = (0.5 + gen.random(n) for _ in range(5))
+    x = gen.standard_normal((nrhs, n))
+    t = lambda v: torch.tensor(v, device="cuda:0")  # noqa: E731
+    y = hif.matvec(t(pts), t(x), a=t(a), b=t(b), c=t(c), weights=t(w), selfk=t(s)).cpu().numpy()
+    u = np.finfo(float).eps / 2
+    for i in sorted({0, n - 1, n // 2, *gen.integers(0, n, 6).tolist()}):
+        r = np.sqrt(((pts[i] - pts) ** 2).sum(1))
+        r[i] = 1.0
+        G = -np.log(r) / (2 * np.pi) if d == 2 else 1.0 / (4 * np.pi * r)
+        G[i] = 0.0
+        K = G * w
+        K[i] = s[i]
+        ref = a[i] * x[:, i] + b[i] * ((K * c) * x).sum(1)
+        mag = np.abs(a[i] * x[:, i]) + b[i] * ((np.maximum(np.abs(K), 1e-3 * w) * c) * np.abs(x)).sum(1)
+        assert np.all(np.abs(y[:, i] - ref) <= (2 * n * u + 16 * u) * mag)
