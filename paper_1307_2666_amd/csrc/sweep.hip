@@ -370,8 +370,11 @@ constexpr int kCapL = 16384;   // LDS doubles, largest records and the top block
 // record (launch-shape table), fewer records 1024 threads each.
 constexpr int kManyRecords = 1024;
 // Top blocks of at least this many unknowns are solved by the many-workgroup
-// blocked triangular solves (one workgroup is latency-bound there).
-constexpr int64_t kTopSplitMin = 512;
+// blocked triangular solves: one workgroup walks the block's rows with the
+// loads of one workgroup in flight (a solve with a top of 212: 154 us against
+// 101, of 474: 527 against 286; applies of 212: 115 against 94).  Below two
+// 64-row blocks there is nothing to hand over.
+constexpr int64_t kTopSplitMin = 128;
 
 // The helpers below issue their global loads eight at a time before using
 // them, so that a single workgroup (one per large group) keeps many requests
@@ -964,6 +967,20 @@ __global__ __launch_bounds__(64) void k_make_perm_top(const int32_t* piv, int32_
   make_perm(piv, perm, n);
 }
 
+// The top block's solve record: indices, interchanges, gather permutation.
+__global__ void k_top_record(const int32_t* idx, const int32_t* piv, const int32_t* perm, int r, int32_t* iarena,
+                             GroupRec* rec, int64_t* woff) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) {
+    *rec = GroupRec{r, 0, 0, 0};
+    *woff = 0;
+  }
+  if (i >= r) return;
+  iarena[i] = idx[i];
+  iarena[r + i] = piv[i];
+  iarena[2 * r + i] = perm[i];
+}
+
 __global__ void k_copy(const double* x, double* y, int64_t n) {
   for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
     y[i] = x[i];
@@ -993,7 +1010,8 @@ struct SpArgs {
   int nv;
   const double* dinv;  // diagonal-block inverses (SubLevel::dinv layout)
   int dnb;             // blocks per record in dinv
-  // Ticket counter of the chained triangular solve.
+  // Ticket counter of the chained triangular solve (two of them where a top
+  // block's two solves follow each other).
   uint32_t* sync = nullptr;
   int nbm = 0;  // blocks of the largest record
   long long wait_ticks = 0;  // bound on each wait, in ticks of the 100 MHz constant clock
@@ -1036,8 +1054,126 @@ __device__ __forceinline__ void sp_ready_chain(const SpArgs& A, const SpRec& R, 
   for (int e = threadIdx.x; e < A.nv * n; e += blockDim.x) X[(e / n) * R.r + i0 + e % n] = kXPending;
 }
 
+// Where a vector of a record's redundant unknowns is read or written: its X
+// or B block of the work buffer, or the right-hand sides themselves through
+// the record's indices (u_r, or P u_r with the row interchanges).
+enum SpVec { kInX = 0, kInB = 1, kInU = 2, kInPu = 3 };
+
+__device__ __forceinline__ double* sp_at(const SpArgs& A, const SpRec& R, int where, int v, int i) {
+  if (where >= kInU) return A.u + v * A.N + R.rd[where == kInPu ? R.perm[i] : i];
+  return (where == kInX ? R.X : R.B) + int64_t(v) * R.r + i;
+}
+
 constexpr int kSpChunk = 512;  // skeleton entries staged in LDS per pass
-constexpr int kUc = 16;         // loads in flight per lane in the column-form products
+
+// The product of a 64 x 16 tile of a matrix with 16 entries of each right-hand
+// side, one wave.  One right-hand side: lane = row, the entries of x broadcast
+// through scalar registers (read from LDS, they would cost a broadcast read
+// per entry and wave, and the one LDS of a CU bounds its four SIMDs).  Up to
+// 8: matrix instructions, 16 of 64 cycles, whose 16 columns hold the
+// right-hand sides (columns 8 .. 15 are ignored).  Broadcasts cost 128
+// products, 256 lane reads and their wait states, three times as long.
+//   m[q]:  entry (row(q), col(q)) of the tile
+//   x[s]:  entry col_x(s) of right-hand side rhs()
+using d4 = double __attribute__((ext_vector_type(4)));
+template <int NV>
+struct SpTile {
+  static_assert(NV == 1 || NV == kMaxV, "one right-hand side, or a pass of up to kMaxV");
+  static constexpr int kNx = NV == 1 ? 1 : 4;
+  static constexpr int kLd = 66;  // row of sums or entries in LDS, padded against bank conflicts
+  double s = 0.0;
+  d4 a[NV == 1 ? 1 : 4] = {};
+
+  static __device__ __forceinline__ int row(int q) {
+    return NV == 1 ? int(threadIdx.x & 63) : 16 * (q >> 2) + int(threadIdx.x & 15);
+  }
+  static __device__ __forceinline__ int col(int q) { return NV == 1 ? q : 4 * (q & 3) + int(threadIdx.x & 63) / 16; }
+  static __device__ __forceinline__ int rhs() { return NV == 1 ? 0 : int(threadIdx.x & 15); }
+  static __device__ __forceinline__ int col_x(int s) {
+    return NV == 1 ? int(threadIdx.x & 15) : 4 * s + int(threadIdx.x & 63) / 16;
+  }
+  __device__ __forceinline__ void mul(const double (&m)[16], const double (&x)[kNx]) {
+    if constexpr (NV == 1) {
+      const uint64_t b = uint64_t(__double_as_longlong(x[0]));
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b)), q));
+        const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b >> 32)), q));
+        s += m[q] * __longlong_as_double((long long)((uint64_t(hi) << 32) | lo));
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(m[4 * t + k], x[k], a[t], 0, 0, 0);
+    }
+  }
+  // the 64 sums of each right-hand side
+  __device__ __forceinline__ void put(double (*dst)[kLd]) const {
+    const int lane = threadIdx.x & 63;
+    if constexpr (NV == 1) {
+      dst[0][lane] = s;
+    } else if ((lane & 15) < NV) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dst[lane & 15][16 * t + 4 * e + lane / 16] = a[t][e];
+    }
+  }
+};
+
+// acc += sum_{j < n} M(j, ib + l) x(v, j) for the 64 columns ib + l of the
+// workgroup, clamped to column nc - 1 (M row-major, leading dimension ld): the
+// waves take 16 rows j each in turn, 16 coalesced loads in flight per wave and
+// no barrier; x(v, j) is read where x stands.  colmap (if given) is the column
+// read in place of ib + l.  TRI >= 0 keeps one triangle of a matrix whose row
+// 0 is jb: 2 the rows jb + j > ib + l, 3 the rows jb + j <= ib + l.
+template <int NV, int TRI = -1, typename X>
+__device__ __forceinline__ void sp_cols_acc(const double* M, int64_t ld, int ib, int nc, int n, int nv,
+                                            SpTile<NV>& acc, X x, const int32_t* colmap = nullptr, int jb = 0) {
+  using T = SpTile<NV>;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  constexpr int kCols = NV == 1 ? 1 : 4;  // columns of a lane
+  int c[kCols];
+#pragma unroll
+  for (int t = 0; t < kCols; ++t) {
+    c[t] = min(ib + T::row(4 * t), nc - 1);
+    if (colmap) c[t] = colmap[c[t]];
+  }
+  for (int j0 = wv * 16; j0 < n; j0 += nw * 16) {
+    double m[16], xv[T::kNx];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) m[q] = M[int64_t(min(j0 + T::col(q), n - 1)) * ld + c[NV == 1 ? 0 : q >> 2]];
+#pragma unroll
+    for (int k = 0; k < T::kNx; ++k) {
+      const int j = j0 + T::col_x(k);
+      xv[k] = j < n && T::rhs() < nv ? x(T::rhs(), j) : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int j = j0 + T::col(q), i = ib + T::row(q);
+      if (j >= n || (TRI == 2 && jb + j <= i) || (TRI == 3 && jb + j > i)) m[q] = 0.0;
+    }
+    acc.mul(m, xv);
+  }
+}
+
+// The waves' sums of a workgroup's 64 columns, added in wave order: out(v, l)
+// is called with the total of column l of right-hand side v.
+constexpr int kSpColWaves = 16;
+template <int NV, typename O>
+__device__ __forceinline__ void sp_cols_out(const SpTile<NV>& acc, int nv, O out) {
+  __shared__ double sred[kSpColWaves][NV][SpTile<NV>::kLd];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  acc.put(sred[wv]);
+  __syncthreads();
+  for (int v = wv; v < nv; v += kSpColWaves) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kSpColWaves; ++w) t += sred[w][v][lane];
+    out(v, lane, t);
+  }
+}
 
 // The sums over the wave of acc[q][v] (4 rows q of the wave, kMaxV
 // right-hand sides) in one reduce-scatter: returns the total of row q =
@@ -1067,6 +1203,23 @@ __device__ __forceinline__ void sp_stage(const double* base, int64_t ld, const i
     for (int v = 0; v < kMaxV; ++v)
       if (v < nv) dst[v][e] = t[v];
   }
+}
+
+// The same of entries c0 .. c0 + n - 1 of a record's vector.
+__device__ __forceinline__ void sp_stage_vec(const SpArgs& A, const SpRec& R, int where, int c0, int n,
+                                             double (*dst)[kSpChunk]) {
+  if (where == kInX || where == kInB)
+    sp_stage((where == kInX ? R.X : R.B) + c0, R.r, nullptr, n, A.nv, dst);
+  else
+    for (int e = threadIdx.x; e < n; e += blockDim.x) {
+      const int64_t g = R.rd[where == kInPu ? R.perm[c0 + e] : c0 + e];
+      double t[kMaxV];
+#pragma unroll
+      for (int v = 0; v < kMaxV; ++v) t[v] = v < A.nv ? A.u[v * A.N + g] : 0.0;
+#pragma unroll
+      for (int v = 0; v < kMaxV; ++v)
+        if (v < A.nv) dst[v][e] = t[v];
+    }
 }
 
 // acc[q][v] += sum_{c < nc} mr[q][c] s[v][c] for a wave's 4 rows q (mr[q] null
@@ -1104,63 +1257,45 @@ __device__ __forceinline__ void sp_rows4_acc(const double* const (&mr)[4], int n
   }
 }
 
+// Readies the chained solves of a pass that has no product before them (the
+// top block): X and B pending, both ticket counters zero.
+__global__ __launch_bounds__(256) void k_sp_ready(SpArgs A) {
+  const SpRec R = sp_rec(A, blockIdx.y);
+  const int i0 = blockIdx.x * 64;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) A.sync[threadIdx.x] = 0u;
+  const int n = min(64, R.r - i0);
+  for (int e = threadIdx.x; e < A.nv * n; e += blockDim.x) {
+    const int64_t o = int64_t(e / n) * R.r + i0 + e % n;
+    reinterpret_cast<uint64_t*>(R.X)[o] = kXPending;
+    reinterpret_cast<uint64_t*>(R.B)[o] = kXPending;
+  }
+}
+
 // First step of an up pass (and of the transposed solve's down pass), column
 // form: B(v, i) = u_r(v, c) - (M^T u_s)(v, c) with c = perm[i] (PERM: the
 // row interchanges of the solve, B = P(u_r - T^T u_s)) or c = i, and
 // M = T (k x r), or L_sr with LSR.  With ADD instead u_r(v, i) += (M^T u_s)(v, i)
 // in place (the last step of the apply sweeps' down pass).  64 rows i per
-// workgroup, lane per row, the sum over the skeleton split between the 4
-// waves and added through LDS.
-template <bool LSR, bool PERM, bool ADD = false>
-__global__ __launch_bounds__(256) void k_sp_first_cols(SpArgs A) {
+// workgroup, lane per row, the sum over the skeleton split between its 16
+// waves.
+template <bool LSR, bool PERM, bool ADD, int NV>
+__global__ __launch_bounds__(kSpColWaves * 64) void k_sp_first_cols(SpArgs A) {
   const SpRec R = sp_rec(A, blockIdx.y);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + lane;  // 64 rows per workgroup
-  if (!ADD) sp_ready_chain(A, R, blockIdx.x * 64, 64);
-  if (blockIdx.x * 64 >= R.r) return;
-  const int nv = A.nv;
-  const double* M = LSR ? R.Lsr : R.T;
-  __shared__ double sus[kMaxV][kSpChunk];
-  __shared__ double sred[4][kMaxV][64];
-  const int c = i < R.r ? (PERM ? R.perm[i] : i) : 0;
-  double acc[kMaxV];
-#pragma unroll
-  for (int v = 0; v < kMaxV; ++v) acc[v] = 0.0;
-  for (int j0 = 0; j0 < R.k; j0 += kSpChunk) {
-    const int nj = min(kSpChunk, R.k - j0);
-    __syncthreads();
-    sp_stage(A.u, A.N, R.sk + j0, nj, nv, sus);
-    __syncthreads();
-    // wave wv takes the quarter [jb, je) of the chunk
-    const int jb = (nj * wv) / 4, je = (nj * (wv + 1)) / 4;
-    if (i < R.r) {
-      const double* tc = M + int64_t(j0) * R.r + c;
-      for (int j = jb; j < je; j += kUc) {
-        double t[kUc];
-#pragma unroll
-        for (int u = 0; u < kUc; ++u) t[u] = j + u < je ? tc[int64_t(j + u) * R.r] : 0.0;
-#pragma unroll
-        for (int u = 0; u < kUc; ++u)
-          if (j + u < je)
-#pragma unroll
-            for (int v = 0; v < kMaxV; ++v)
-              if (v < nv) acc[v] += t[u] * sus[v][j + u];
-      }
-    }
-  }
-#pragma unroll
-  for (int v = 0; v < kMaxV; ++v) sred[wv][v][lane] = acc[v];
-  __syncthreads();
-  if (wv == 0 && i < R.r)
-#pragma unroll
-    for (int v = 0; v < kMaxV; ++v)
-      if (v < nv) {
-        const double t = (sred[0][v][lane] + sred[1][v][lane]) + (sred[2][v][lane] + sred[3][v][lane]);
-        if (ADD)
-          A.u[v * A.N + R.rd[c]] += t;
-        else
-          R.B[v * R.r + i] = A.u[v * A.N + R.rd[c]] - t;
-      }
+  const int lane = threadIdx.x & 63, ib = blockIdx.x * 64;
+  if (!ADD) sp_ready_chain(A, R, ib, 64);
+  if (ib >= R.r) return;
+  const int i = min(ib + lane, R.r - 1), c = PERM ? R.perm[i] : i;
+  SpTile<NV> acc;
+  sp_cols_acc<NV>(LSR ? R.Lsr : R.T, R.r, ib, R.r, R.k, A.nv, acc,
+                  [&](int v, int j) { return A.u[v * A.N + R.sk[j]]; }, PERM ? R.perm : nullptr);
+  sp_cols_out<NV>(acc, A.nv, [&](int v, int l, double t) {
+    if (ib + l >= R.r) return;
+    double* ur = A.u + v * A.N + R.rd[c];
+    if (ADD)
+      *ur += t;
+    else
+      R.B[int64_t(v) * R.r + ib + l] = *ur - t;
+  });
 }
 
 // Down, first step of the solve: B(v, i) = (u_r - U_rs u_s)(v, i), one wave
@@ -1240,64 +1375,18 @@ __global__ __launch_bounds__(256) void k_sp_skel_update(SpArgs A, int which, dou
 
 // u_s += sgn U_rs^T x (U_rs r x k), x = X or with GATHER the record's u_r
 // read through its indices: lane per skeleton entry j, 64 per workgroup, the
-// sum over the rows of U_rs split between the 4 waves and added through LDS;
-// x staged in LDS by chunks.
-template <bool GATHER>
-__global__ __launch_bounds__(256) void k_sp_skel_update_T(SpArgs A, double sgn) {
+// sum over the rows of U_rs split between its 16 waves.
+template <bool GATHER, int NV>
+__global__ __launch_bounds__(kSpColWaves * 64) void k_sp_skel_update_T(SpArgs A, double sgn) {
   const SpRec R = sp_rec(A, blockIdx.y);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lane;
-  if (blockIdx.x * 64 >= R.k) return;
-  const int nv = A.nv;
-  __shared__ double sx[kMaxV][kSpChunk];
-  __shared__ double sred[4][kMaxV][64];
-  double acc[kMaxV];
-#pragma unroll
-  for (int v = 0; v < kMaxV; ++v) acc[v] = 0.0;
-  for (int i0 = 0; i0 < R.r; i0 += kSpChunk) {
-    const int ni = min(kSpChunk, R.r - i0);
-    __syncthreads();
-    if (GATHER)
-      sp_stage(A.u, A.N, R.rd + i0, ni, nv, sx);
-    else
-      sp_stage(R.X + i0, R.r, nullptr, ni, nv, sx);
-    __syncthreads();
-    const int ib = (ni * wv) / 4, ie = (ni * (wv + 1)) / 4;
-    if (j < R.k) {
-      const double* mc = R.Urs + int64_t(i0) * R.k + j;
-      for (int i = ib; i < ie; i += kUc) {
-        double m[kUc];
-#pragma unroll
-        for (int u = 0; u < kUc; ++u) m[u] = i + u < ie ? mc[int64_t(i + u) * R.k] : 0.0;
-#pragma unroll
-        for (int u = 0; u < kUc; ++u)
-          if (i + u < ie)
-#pragma unroll
-            for (int v = 0; v < kMaxV; ++v)
-              if (v < nv) acc[v] += m[u] * sx[v][i + u];
-      }
-    }
-  }
-#pragma unroll
-  for (int v = 0; v < kMaxV; ++v) sred[wv][v][lane] = acc[v];
-  __syncthreads();
-  if (wv == 0 && j < R.k)
-#pragma unroll
-    for (int v = 0; v < kMaxV; ++v)
-      if (v < nv)
-        A.u[v * A.N + R.sk[j]] += sgn * ((sred[0][v][lane] + sred[1][v][lane]) + (sred[2][v][lane] + sred[3][v][lane]));
-}
-
-// u_r = x, or with PERM u_r = P^T x (u_r[perm[i]] = x[i]); x = X (src 0) or
-// B (src 1).
-template <bool PERM>
-__global__ __launch_bounds__(256) void k_sp_scatter(SpArgs A, int src) {
-  const SpRec R = sp_rec(A, blockIdx.y);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= R.r) return;
-  const double* x = src ? R.B : R.X;
-  const int d = R.rd[PERM ? R.perm[i] : i];
-  for (int v = 0; v < A.nv; ++v) A.u[v * A.N + d] = x[v * R.r + i];
+  const int jb = blockIdx.x * 64;
+  if (jb >= R.k) return;
+  SpTile<NV> acc;
+  sp_cols_acc<NV>(R.Urs, R.k, jb, R.k, R.r, A.nv, acc,
+                  [&](int v, int i) { return *sp_at(A, R, GATHER ? kInU : kInX, v, i); });
+  sp_cols_out<NV>(acc, A.nv, [&](int v, int l, double t) {
+    if (jb + l < R.k) A.u[v * A.N + R.sk[jb + l]] += sgn * t;
+  });
 }
 
 // B = u_r, or with PERM B = P u_r (B[i] = u_r[perm[i]]).
@@ -1311,20 +1400,18 @@ __global__ __launch_bounds__(256) void k_sp_gather(SpArgs A) {
 }
 
 // The triangular products of the apply sweeps (and the rectangular ones
-// beside them), for few large records: x = B, out = X (io 0) or x = X,
-// out = B (io 1).  Row form: out(v, i) = (M x)(v, i) [+ (U_rs u_s)(v, i)]
+// beside them), for few large records, from vector src to vector dst of the
+// record (not the same one).  Row form: out(v, i) = (M x)(v, i) [+ (U_rs u_s)(v, i)]
 // with M the upper U of the record's LU (TRI 0, columns j >= i) or its unit
 // lower L (TRI 1, x_i plus the columns j < i); one wave per row i, 16 rows
 // per workgroup, x and u_s staged in LDS by chunks.
 template <int TRI, bool RECT>
-__global__ __launch_bounds__(256) void k_sp_rowmv(SpArgs A, int io) {
+__global__ __launch_bounds__(256) void k_sp_rowmv(SpArgs A, int src, int dst) {
   const SpRec R = sp_rec(A, blockIdx.y);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int i0 = blockIdx.x * 16;
   if (i0 >= R.r) return;
   const int nv = A.nv, r = R.r;
-  const double* x = io ? R.X : R.B;
-  double* out = io ? R.B : R.X;
   __shared__ double sx[kMaxV][kSpChunk];
   double acc[4][kMaxV];
 #pragma unroll
@@ -1336,7 +1423,7 @@ __global__ __launch_bounds__(256) void k_sp_rowmv(SpArgs A, int io) {
   for (int c0 = cb; c0 < ce; c0 += kSpChunk) {
     const int nc = min(kSpChunk, ce - c0);
     __syncthreads();
-    sp_stage(x + c0, r, nullptr, nc, nv, sx);
+    sp_stage_vec(A, R, src, c0, nc, sx);
     __syncthreads();
     const double* mr[4];
     int iq[4];
@@ -1364,116 +1451,82 @@ __global__ __launch_bounds__(256) void k_sp_rowmv(SpArgs A, int io) {
   {
     const double t = sp_rows_sum(acc);
     const int i = i0 + wv * 4 + (lane >> 4), v = (lane >> 1) & 7;
-    if ((lane & 1) == 0 && i < r && v < nv) out[v * r + i] = t + (TRI == 1 ? x[v * r + i] : 0.0);
+    if ((lane & 1) == 0 && i < r && v < nv)
+      *sp_at(A, R, dst, v, i) = t + (TRI == 1 ? *sp_at(A, R, src, v, i) : 0.0);
   }
 }
 
 // Column form: out(v, i) = (M^T x)(v, i) [+ (L_sr^T u_s)(v, i)] with M^T the
 // unit upper L^T (TRI 2: x_i plus the rows j > i of L) or the lower U^T
 // (TRI 3: the rows j <= i of U); lane per i, 64 per workgroup, the sum over
-// j split between the 4 waves and added through LDS.
-template <int TRI, bool RECT>
-__global__ __launch_bounds__(256) void k_sp_colmv(SpArgs A, int io) {
+// j split between its 16 waves.
+template <int TRI, bool RECT, int NV>
+__global__ __launch_bounds__(kSpColWaves * 64) void k_sp_colmv(SpArgs A, int src, int dst) {
   const SpRec R = sp_rec(A, blockIdx.y);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int ib = blockIdx.x * 64, i = ib + lane;
-  if (ib >= R.r) return;
-  const int nv = A.nv, r = R.r;
-  const double* x = io ? R.X : R.B;
-  double* out = io ? R.B : R.X;
-  __shared__ double sx[kMaxV][kSpChunk];
-  __shared__ double sred[4][kMaxV][64];
-  double acc[kMaxV];
-#pragma unroll
-  for (int v = 0; v < kMaxV; ++v) acc[v] = 0.0;
+  const int ib = blockIdx.x * 64, r = R.r;
+  if (ib >= r) return;
+  SpTile<NV> acc;
   // the rows the workgroup's columns reach
   const int jb = TRI == 2 ? ib : 0, je = TRI == 2 ? r : min(r, ib + 64);
-  for (int j0 = jb; j0 < je; j0 += kSpChunk) {
-    const int nj = min(kSpChunk, je - j0);
-    __syncthreads();
-    sp_stage(x + j0, r, nullptr, nj, nv, sx);
-    __syncthreads();
-    const int qb = (nj * wv) / 4, qe = (nj * (wv + 1)) / 4;
-    if (i < r) {
-      const double* mc = R.LU + int64_t(j0) * r + i;
-      for (int j = qb; j < qe; j += kUc) {
-        double m[kUc];
-#pragma unroll
-        for (int u = 0; u < kUc; ++u) {
-          const int jr = j0 + j + u;
-          m[u] = (j + u < qe && (TRI == 2 ? jr > i : jr <= i)) ? mc[int64_t(j + u) * r] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < kUc; ++u)
-          if (j + u < qe)
-#pragma unroll
-            for (int v = 0; v < kMaxV; ++v)
-              if (v < nv) acc[v] += m[u] * sx[v][j + u];
-      }
-    }
-  }
+  sp_cols_acc<NV, TRI>(R.LU + int64_t(jb) * r, r, ib, r, je - jb, A.nv, acc,
+                       [&](int v, int j) { return *sp_at(A, R, src, v, jb + j); }, nullptr, jb);
   if (RECT)
-    for (int j0 = 0; j0 < R.k; j0 += kSpChunk) {
-      const int nj = min(kSpChunk, R.k - j0);
-      __syncthreads();
-      sp_stage(A.u, A.N, R.sk + j0, nj, nv, sx);
-      __syncthreads();
-      const int qb = (nj * wv) / 4, qe = (nj * (wv + 1)) / 4;
-      if (i < r) {
-        const double* mc = R.Lsr + int64_t(j0) * r + i;
-        for (int j = qb; j < qe; j += kUc) {
-          double m[kUc];
-#pragma unroll
-          for (int u = 0; u < kUc; ++u) m[u] = j + u < qe ? mc[int64_t(j + u) * r] : 0.0;
-#pragma unroll
-          for (int u = 0; u < kUc; ++u)
-            if (j + u < qe)
-#pragma unroll
-              for (int v = 0; v < kMaxV; ++v)
-                if (v < nv) acc[v] += m[u] * sx[v][j + u];
-        }
-      }
-    }
-#pragma unroll
-  for (int v = 0; v < kMaxV; ++v) sred[wv][v][lane] = acc[v];
-  __syncthreads();
-  if (wv == 0 && i < r)
-#pragma unroll
-    for (int v = 0; v < kMaxV; ++v)
-      if (v < nv)
-        out[v * r + i] = ((sred[0][v][lane] + sred[1][v][lane]) + (sred[2][v][lane] + sred[3][v][lane])) +
-                         (TRI == 2 ? x[v * r + i] : 0.0);
+    sp_cols_acc<NV>(R.Lsr, r, ib, r, R.k, A.nv, acc, [&](int v, int j) { return A.u[v * A.N + R.sk[j]]; });
+  sp_cols_out<NV>(acc, A.nv, [&](int v, int l, double t) {
+    if (ib + l < r) *sp_at(A, R, dst, v, ib + l) = t + (TRI == 2 ? *sp_at(A, R, src, v, ib + l) : 0.0);
+  });
 }
 
 // Inverses of the diagonal blocks of the records' L (unit lower) and U
 // (upper) for the chained solves below: workgroup (b, i) inverts block b of
-// record i; lane c builds column c of each inverse by substitution (L: down
-// the rows, U: up the rows), so no lane reads another's column.  Rows and
-// columns past a partial last block are the identity.
-__global__ __launch_bounds__(64) void k_sp_dinv(SpArgs A, double* dinv) {
+// record i, wave 0 the block of L and wave 1 that of U, read with rows and
+// columns reversed, which makes it lower triangular too.  Lane c builds
+// column c by substitution, 16 rows at a time in registers: a row of 16
+// entries of the matrix is read from LDS as eight broadcasts for 16 products.
+// Rows and columns past a partial last block are the identity.
+__global__ __launch_bounds__(128) void k_sp_dinv(SpArgs A, double* dinv) {
   const SpRec R = sp_rec(A, blockIdx.y);
   const int b = blockIdx.x, j0 = b * kNbT;
   if (j0 >= R.r) return;
-  const int nb = min(kNbT, R.r - j0), r = R.r, c = threadIdx.x;
-  __shared__ double sM[kNbT][kNbT + 1];
-  __shared__ double sX[kNbT][kNbT + 1];
-  for (int a = 0; a < kNbT; ++a)
-    sM[a][c] = (a < nb && c < nb) ? R.LU[int64_t(j0 + a) * r + j0 + c] : (a == c ? 1.0 : 0.0);
+  const int nb = min(kNbT, R.r - j0), r = R.r, c = threadIdx.x & 63, w = threadIdx.x >> 6;
+  __shared__ __align__(16) double sM[2][kNbT][kNbT + 2];  // [j][i]: column j of the lower triangle
+  __shared__ double sX[2][kNbT][kNbT + 1];
+  for (int a = w; a < kNbT; a += 2) {
+    const double m = (a < nb && c < nb) ? R.LU[int64_t(j0 + a) * r + j0 + c] : (a == c ? 1.0 : 0.0);
+    const bool low = a > c;
+    if (low)
+      sM[0][c][a] = m;
+    else
+      sM[1][kNbT - 1 - c][kNbT - 1 - a] = m;
+    if (a == c) sM[0][c][c] = 1.0;
+  }
+  __syncthreads();
+  for (int i0 = 0; i0 < kNbT; i0 += 16) {
+    double v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = i0 + i == c ? 1.0 : 0.0;
+#pragma unroll 2
+    for (int j = 0; j < i0; ++j) {
+      const double xj = sX[w][j][c];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] -= sM[w][j][i0 + i] * xj;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      double x = v[i];
+      if (w) x = x / sM[1][i0 + i][i0 + i];
+      if (i0 + i < c) x = 0.0;
+      sX[w][i0 + i][c] = x;
+#pragma unroll
+      for (int q = i + 1; q < 16; ++q) v[q] -= sM[w][i0 + i][i0 + q] * x;
+    }
+  }
   __syncthreads();
   double* out = dinv + (int64_t(blockIdx.y) * A.dnb + b) * 2 * kNbT * kNbT;
-  for (int a = 0; a < kNbT; ++a) {  // L X = I, unit diagonal
-    double acc = 0.0;
-    for (int j = c; j < a; ++j) acc += sM[a][j] * sX[j][c];
-    sX[a][c] = a == c ? 1.0 : (a > c ? -acc : 0.0);
+  for (int a = w; a < kNbT; a += 2) {
+    out[a * kNbT + c] = sX[0][a][c];
+    out[kNbT * kNbT + a * kNbT + c] = sX[1][kNbT - 1 - a][kNbT - 1 - c];
   }
-  for (int a = 0; a < kNbT; ++a) out[a * kNbT + c] = sX[a][c];
-  for (int a = kNbT - 1; a >= 0; --a) {  // U X = I
-    double acc = 0.0;
-    for (int j = a + 1; j <= c; ++j) acc += sM[a][j] * sX[j][c];
-    const double d = sM[a][a];
-    sX[a][c] = a > c ? 0.0 : (a == c ? 1.0 / d : -acc / d);
-  }
-  for (int a = 0; a < kNbT; ++a) out[kNbT * kNbT + a * kNbT + c] = sX[a][c];
 }
 
 // ---------------------------------------------------------------------------
@@ -1493,38 +1546,45 @@ __global__ __launch_bounds__(64) void k_sp_dinv(SpArgs A, double* dinv) {
 // every wait ends however many workgroups are resident at once.  Each wait
 // is also bounded in time; past the bound (not expected) the workgroup
 // writes NaN in its block, so that the failure shows in the result instead
-// of stalling the device.  Each next block of M is loaded into registers
-// before its wait.
+// of stalling the device.
+//   A chain is bound by the time from one block of X to the next, so little
+// stands on that path.  Wave 4 polls and nothing else: loads return in order,
+// so a wave that also loaded tiles would wait for those on every poll (all
+// waves did both before: 2.2 us per block of one right-hand side, 4.5 us of
+// eight).  Waves 0 .. 3 each hold 16 columns of a tile of M in registers, the
+// next two tiles in flight, and their sums meet once, after the last block.
 //   MODE 0: L X = B    (unit lower L of the record's LU; blocks first to last)
 //   MODE 1: U X = B    (upper U; last to first)
 //   MODE 2: U^T X = B  (first to last; U read by columns)
 //   MODE 3: L^T X = B  (last to first; L read by columns)
-// Grid (A.nbm, records), 256 threads; the ticket is zero and X pending at
-// launch.
+// B is the record's vector src, X its block `dst` of the work buffer (X or B,
+// not the one B is read from), and with put (kInU or kInPu) the entries are
+// also written there.  Grid (A.nbm, records), 320 threads; the ticket is zero
+// and dst pending at launch.
 // ---------------------------------------------------------------------------
 constexpr long long kWaitTicks = 20000000;  // 0.2 s of the 100 MHz constant clock (default bound)
 
-// Wave 0 of a reader: block b0 .. b0 + nbb - 1 of X, every right-hand side,
+// The polling wave: block b0 .. b0 + nbb - 1 of X, every right-hand side,
 // into sx (lane = row of the block), polled until no entry is pending.
 // Returns false past the time bound (wait ticks of the constant clock).
-__device__ __forceinline__ bool sp_read_block(const double* X, int r, int b0, int nbb, int nv,
-                                              double (*sx)[kNbT], long long wait) {
+template <int NV>
+__device__ __forceinline__ bool sp_read_block(const double* X, int r, int b0, int nbb, int nv, double (*sx)[66],
+                                              long long wait) {
   const int lane = threadIdx.x & 63;
-  const uint64_t* X64 = reinterpret_cast<const uint64_t*>(X);
-  uint64_t got[kMaxV];
-#pragma unroll
-  for (int v = 0; v < kMaxV; ++v) got[v] = kXPending;
+  // every lane reads an entry that exists, and every load of a poll is issued
+  // before any is looked at: one load at a time made a poll of 8 right-hand
+  // sides take 8 memory round trips
+  const uint64_t* X64 = reinterpret_cast<const uint64_t*>(X) + b0 + min(lane, nbb - 1);
+  uint64_t got[NV];
   const long long t0 = wall_clock64();
   bool ok = true;
   for (;;) {
-    int ready = 1;
 #pragma unroll
-    for (int v = 0; v < kMaxV; ++v)
-      if (v < nv && lane < nbb && got[v] == kXPending)
-        got[v] = __hip_atomic_load(X64 + int64_t(v) * r + b0 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int v = 0; v < NV; ++v)
+      got[v] = __hip_atomic_load(X64 + int64_t(min(v, nv - 1)) * r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool ready = true;
 #pragma unroll
-    for (int v = 0; v < kMaxV; ++v)
-      if (v < nv && lane < nbb && got[v] == kXPending) ready = 0;
+    for (int v = 0; v < NV; ++v) ready &= got[v] != kXPending;
     if (__all(ready)) break;
     if (wall_clock64() - t0 > wait) {
       ok = false;
@@ -1533,21 +1593,22 @@ __device__ __forceinline__ bool sp_read_block(const double* X, int r, int b0, in
     __builtin_amdgcn_s_sleep(1);
   }
 #pragma unroll
-  for (int v = 0; v < kMaxV; ++v) sx[v][lane] = (v < nv && lane < nbb) ? __longlong_as_double((long long)got[v]) : 0.0;
+  for (int v = 0; v < NV; ++v) sx[v][lane] = v < nv && lane < nbb ? __longlong_as_double((long long)got[v]) : 0.0;
   return ok;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_sp_chain(SpArgs A) {
+template <int MODE, int NV>
+__global__ __launch_bounds__(320) void k_sp_chain(SpArgs A, int src, int dst, int put) {
   constexpr bool kFwd = MODE == 0 || MODE == 2;
   constexpr bool kTrans = MODE >= 2;
   constexpr bool kUseU = MODE == 1 || MODE == 2;
   __shared__ unsigned s_ticket;
   __shared__ int s_ok;
-  __shared__ double sM[kNbT][kNbT + 1];
-  __shared__ double sD[kNbT][kNbT + 1];  // the diagonal block's inverse, staged before any wait
-  __shared__ double sx[kMaxV][kNbT];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  using T = SpTile<NV>;
+  __shared__ double sT[4][kTrans ? 1 : kNbT][17];  // a wave's 16 columns of a tile on their way to SpTile's layout
+  __shared__ double sx[2][NV][T::kLd];
+  __shared__ double sacc[2][4][NV][T::kLd];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (tid == 0) {
     s_ticket = atomicAdd(A.sync, 1u);
     s_ok = 1;
@@ -1555,92 +1616,122 @@ __global__ __launch_bounds__(256) void k_sp_chain(SpArgs A) {
   __syncthreads();
   const unsigned t = s_ticket;
   const int rec = int(t / unsigned(A.nbm)), jj = int(t % unsigned(A.nbm));
+  if (unsigned(rec) >= gridDim.y) return;  // sweeps of one handle that overlap on two streams draw from one counter
   const SpRec R = sp_rec(A, rec);
   const int r = R.r, nbk = (r + kNbT - 1) / kNbT;
   if (jj >= nbk) return;
   const int j = kFwd ? jj : nbk - 1 - jj;
   const int j0 = j * kNbT, nb = min(kNbT, r - j0), nv = A.nv;
   const int ndep = kFwd ? j : nbk - 1 - j;
-  // Element q of a thread is e = tid + 256 q of a 64 x 64 tile at (a, c):
-  // (e / 64, e % 64) for a row-major read, (e % 64, e / 64) for a column
-  // read, so consecutive threads read consecutive addresses either way.
-  double pre[16], dpre[16];
-  auto load_block = [&](int b) {
-    const int b0 = b * kNbT, nbb = min(kNbT, r - b0);
+  double* X = dst == kInX ? R.X : R.B;
+  // the polling wave; the barrier of step d hands over block d (sx[d & 1] is
+  // written again only after the next barrier, when all have read it)
+  if (wv == 4) {
+    for (int d = 0; d < ndep; ++d) {
+      const int b0 = (kFwd ? d : nbk - 1 - d) * kNbT;
+      if (!sp_read_block<NV>(X, r, b0, min(kNbT, r - b0), nv, sx[d & 1], A.wait_ticks) && lane == 0) s_ok = 0;
+      __syncthreads();
+    }
+    __syncthreads();
+    __syncthreads();
+    return;
+  }
+  // The wave's columns are 16 wv .. 16 wv + 15 of a tile.  A tile of M^T is
+  // read in the layout of the product (consecutive lanes, consecutive
+  // addresses); a tile of M is read by rows, 16 consecutive entries of 4 rows
+  // at a time, and turned through LDS by the wave that owns its columns.
+  const int cw = 16 * wv, c4 = cw + (lane & 15), r4 = lane >> 4;
+  auto load_tile = [&](int d, double (&p)[16]) {
+    const int b0 = (kFwd ? d : nbk - 1 - d) * kNbT, nbb = min(kNbT, r - b0);
+    if constexpr (kTrans) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int e = tid + 256 * q, hi = e >> 6, lo = e & 63;
-      const int a = kTrans ? lo : hi, c = kTrans ? hi : lo;
-      pre[q] = (a < nb && c < nbb)
-                   ? (kTrans ? R.LU[int64_t(b0 + c) * r + j0 + a] : R.LU[int64_t(j0 + a) * r + b0 + c])
-                   : 0.0;
+      for (int q = 0; q < 16; ++q)
+        p[q] = R.LU[int64_t(b0 + min(cw + T::col(q), nbb - 1)) * r + j0 + min(T::row(q), nb - 1)];
+    } else {
+      const double* m = R.LU + int64_t(j0) * r + b0 + min(c4, nbb - 1);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) p[q] = m[int64_t(min(4 * q + r4, nb - 1)) * r];
     }
   };
-  auto store_tile = [&](double (*dst)[kNbT + 1], const double* v) {
+  auto turn = [&](const double (&p)[16], double (&m)[16]) {
+    if constexpr (kTrans) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int e = tid + 256 * q, hi = e >> 6, lo = e & 63;
-      dst[kTrans ? lo : hi][kTrans ? hi : lo] = v[q];
+      for (int q = 0; q < 16; ++q) m[q] = p[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) sT[wv][4 * q + r4][lane & 15] = p[q];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int q = 0; q < 16; ++q) m[q] = sT[wv][T::row(q)][T::col(q)];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   };
   {
-    // the stored inverse of the diagonal block, row-major; transposed for U^T, L^T
+    // the wave's columns of the stored inverse of the diagonal block
+    // (row-major; transposed for U^T, L^T)
     const double* Dg = A.dinv + (int64_t(rec) * A.dnb + j) * 2 * kNbT * kNbT + (kUseU ? kNbT * kNbT : 0);
+    double p[16], dm[16], p0[16], p1[16], b[T::kNx], x[T::kNx];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) dpre[q] = Dg[tid + 256 * q];
-  }
-  // into LDS now: it depends on no other block, and the barriers below order
-  // these stores before the product that reads them
-  store_tile(sD, dpre);
-  double acc[kMaxV / 4];
+    for (int q = 0; q < 16; ++q)
+      p[q] = kTrans ? Dg[(cw + T::col(q)) * kNbT + T::row(q)] : Dg[(4 * q + r4) * kNbT + c4];
+    if (ndep > 0) load_tile(0, p0);
+    if (ndep > 1) load_tile(1, p1);
+    const int vx = T::rhs(), vl = NV == 1 ? 0 : vx & (NV - 1);
 #pragma unroll
-  for (int q = 0; q < kMaxV / 4; ++q) {
-    const int v = wv + 4 * q;
-    acc[q] = (v < nv && lane < nb) ? R.B[v * r + j0 + lane] : 0.0;
-  }
-  if (ndep > 0) load_block(kFwd ? 0 : nbk - 1);
-  for (int d = 0; d < ndep; ++d) {
-    const int b = kFwd ? d : nbk - 1 - d;
-    // wave 0 waits for X_b and stages it in LDS; the other waves store the
-    // prefetched tile meanwhile
-    if (wv == 0) {
-      const int b0 = b * kNbT;
-      if (!sp_read_block(R.X, r, b0, min(kNbT, r - b0), nv, sx, A.wait_ticks) && lane == 0) s_ok = 0;
+    for (int k = 0; k < T::kNx; ++k) {
+      const int c = cw + T::col_x(k);
+      b[k] = c < nb && vx < nv ? *sp_at(A, R, src, vx, j0 + c) : 0.0;
     }
-    store_tile(sM, pre);
-    __syncthreads();
-    if (d + 1 < ndep) load_block(kFwd ? d + 1 : nbk - 2 - d);
+    turn(p, dm);
+    T acc, y;
+    auto step = [&](int d, double (&pd)[16]) {
+      double m[16];
+      turn(pd, m);
+      if (d + 2 < ndep) load_tile(d + 2, pd);
+      __syncthreads();
 #pragma unroll
-    for (int q = 0; q < kMaxV / 4; ++q) {
-      const int v = wv + 4 * q;
-      if (v < nv) {
-        double sum = 0.0;
-#pragma unroll 16
-        for (int c = 0; c < kNbT; ++c) sum += sM[lane][c] * sx[v][c];
-        acc[q] -= sum;
-      }
+      for (int k = 0; k < T::kNx; ++k) x[k] = sx[d & 1][vl][cw + T::col_x(k)];
+      acc.mul(m, x);
+    };
+    for (int d = 0; d < ndep; d += 2) {
+      step(d, p0);
+      if (d + 1 < ndep) step(d + 1, p1);
     }
+    // B - M X of the wave's 16 rows, then its part of X = D^{-1} (B - M X)
+    acc.put(sacc[0][wv]);
     __syncthreads();
-  }
 #pragma unroll
-  for (int q = 0; q < kMaxV / 4; ++q) sx[wv + 4 * q][lane] = acc[q];
+    for (int k = 0; k < T::kNx; ++k) {
+      const int c = cw + T::col_x(k);
+      if (c < nb)
+        b[k] -= (sacc[0][0][vl][c] + sacc[0][1][vl][c]) + (sacc[0][2][vl][c] + sacc[0][3][vl][c]);
+    }
+    y.mul(dm, b);
+    y.put(sacc[1][wv]);
+  }
   __syncthreads();
+  // each thread its row (lane) of its right-hand sides, entry by entry
+  // visible to the readers, and only then u
   const bool ok = s_ok != 0;
-  // X_j = D_j^{-1} B_j: each thread its row (lane) of its right-hand sides,
-  // written straight from registers, entry by entry visible to the readers
-  uint64_t* X64 = reinterpret_cast<uint64_t*>(R.X);
+  uint64_t* X64 = reinterpret_cast<uint64_t*>(X);
+  double x[(NV + 3) / 4];
 #pragma unroll
-  for (int q = 0; q < kMaxV / 4; ++q) {
-    const int v = wv + 4 * q;
-    if (v < nv) {
-      double y = 0.0;
-#pragma unroll 16
-      for (int c = 0; c < kNbT; ++c) y += sD[lane][c] * sx[v][c];
-      if (lane < nb)
-        __hip_atomic_store(X64 + int64_t(v) * r + j0 + lane, (uint64_t)__double_as_longlong(ok ? y : __builtin_nan("")),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+  for (int e = 0; e < (NV + 3) / 4; ++e) {
+    const int v = wv + 4 * e;
+    if (v >= nv || lane >= nb) continue;
+    x[e] = ok ? (sacc[1][0][v][lane] + sacc[1][1][v][lane]) + (sacc[1][2][v][lane] + sacc[1][3][v][lane])
+              : __builtin_nan("");
+    __hip_atomic_store(X64 + int64_t(v) * r + j0 + lane, (uint64_t)__double_as_longlong(x[e]), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (put)
+#pragma unroll
+    for (int e = 0; e < (NV + 3) / 4; ++e) {
+      const int v = wv + 4 * e;
+      if (v < nv && lane < nb) *sp_at(A, R, put, v, j0 + lane) = x[e];
+    }
 }
 
 }  // namespace
@@ -1696,18 +1787,52 @@ static bool top_split_solve(const hif_factor_s* H) {
   return H->ntop >= kTopSplitMin && 2 * H->ntop <= H->n;
 }
 
-// The blocked triangular solve X = M^{-1} B of every record of a pass, one
-// launch (k_sp_chain); mode as there.
-static void chain(const SpArgs& P, int mode, unsigned nr, hipStream_t s) {
-  const dim3 g(unsigned(P.nbm), nr);
-  if (mode == 0)
-    hipLaunchKernelGGL(k_sp_chain<0>, g, dim3(256), 0, s, P);
-  else if (mode == 1)
-    hipLaunchKernelGGL(k_sp_chain<1>, g, dim3(256), 0, s, P);
-  else if (mode == 2)
-    hipLaunchKernelGGL(k_sp_chain<2>, g, dim3(256), 0, s, P);
+// Right-hand sides per pass that the kernels are built for, f(integral
+// constant): one, or up to kMaxV.
+template <typename F>
+static void for_nv(int nv, F f) {
+  if (nv == 1)
+    f(std::integral_constant<int, 1>{});
   else
-    hipLaunchKernelGGL(k_sp_chain<3>, g, dim3(256), 0, s, P);
+    f(std::integral_constant<int, kMaxV>{});
+}
+
+// The blocked triangular solve X = M^{-1} B of every record of a pass, one
+// launch (k_sp_chain); mode, src, dst and put as there.
+static void chain(const SpArgs& P, int mode, unsigned nr, hipStream_t s, int src, int dst, int put) {
+  const dim3 g(unsigned(P.nbm), nr);
+  for_nv(P.nv, [&](auto nvc) {
+    constexpr int NV = decltype(nvc)::value;
+    if (mode == 0)
+      hipLaunchKernelGGL((k_sp_chain<0, NV>), g, dim3(320), 0, s, P, src, dst, put);
+    else if (mode == 1)
+      hipLaunchKernelGGL((k_sp_chain<1, NV>), g, dim3(320), 0, s, P, src, dst, put);
+    else if (mode == 2)
+      hipLaunchKernelGGL((k_sp_chain<2, NV>), g, dim3(320), 0, s, P, src, dst, put);
+    else
+      hipLaunchKernelGGL((k_sp_chain<3, NV>), g, dim3(320), 0, s, P, src, dst, put);
+  });
+}
+
+template <bool LSR, bool PERM, bool ADD = false>
+static void first_cols(const SpArgs& P, dim3 g, hipStream_t s) {
+  for_nv(P.nv, [&](auto nvc) {
+    hipLaunchKernelGGL((k_sp_first_cols<LSR, PERM, ADD, decltype(nvc)::value>), g, dim3(kSpColWaves * 64), 0, s, P);
+  });
+}
+
+template <bool GATHER>
+static void skel_update_T(const SpArgs& P, dim3 g, hipStream_t s, double sgn) {
+  for_nv(P.nv, [&](auto nvc) {
+    hipLaunchKernelGGL((k_sp_skel_update_T<GATHER, decltype(nvc)::value>), g, dim3(kSpColWaves * 64), 0, s, P, sgn);
+  });
+}
+
+template <int TRI, bool RECT>
+static void colmv(const SpArgs& P, dim3 g, hipStream_t s, int src, int dst) {
+  for_nv(P.nv, [&](auto nvc) {
+    hipLaunchKernelGGL((k_sp_colmv<TRI, RECT, decltype(nvc)::value>), g, dim3(kSpColWaves * 64), 0, s, P, src, dst);
+  });
 }
 
 // The sweeps proper.  work: min(nrhs, 8) * N doubles of scratch, reused by
@@ -1754,47 +1879,39 @@ static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64
         const dim3 gs(unsigned((sub.max_k + 15) / 16), nr), gt(unsigned((sub.max_k + 63) / 64), nr);
         const bool sk = sub.max_k > 0;
         if (op == 0 && !down) {
-          hipLaunchKernelGGL((k_sp_first_cols<false, true>), gu, dim3(256), 0, s, P);
-          chain(P, 0, nr, s);
+          first_cols<false, true>(P, gu, s);
+          chain(P, 0, nr, s, kInB, kInX, kInU);
           if (sk) hipLaunchKernelGGL(k_sp_skel_update<false>, gs, dim3(256), 0, s, P, 0, -1.0);
-          hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
         } else if (op == 0) {
           hipLaunchKernelGGL(k_sp_down_first, gw, dim3(256), 0, s, P);
-          chain(P, 1, nr, s);
+          chain(P, 1, nr, s, kInB, kInX, kInU);
           if (sk) hipLaunchKernelGGL(k_sp_skel_update<false>, gs, dim3(256), 0, s, P, 1, -1.0);
-          hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
         } else if (op == 1 && !down) {
-          hipLaunchKernelGGL((k_sp_first_cols<false, false>), gu, dim3(256), 0, s, P);
-          chain(P, 2, nr, s);
-          if (sk) hipLaunchKernelGGL(k_sp_skel_update_T<false>, gt, dim3(256), 0, s, P, -1.0);
-          hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
+          first_cols<false, false>(P, gu, s);
+          chain(P, 2, nr, s, kInB, kInX, kInU);
+          if (sk) skel_update_T<false>(P, gt, s, -1.0);
         } else if (op == 1) {
-          hipLaunchKernelGGL((k_sp_first_cols<true, false>), gu, dim3(256), 0, s, P);
-          chain(P, 3, nr, s);
-          hipLaunchKernelGGL(k_sp_scatter<true>, gr, dim3(256), 0, s, P, 0);
+          first_cols<true, false>(P, gu, s);
+          chain(P, 3, nr, s, kInB, kInX, kInPu);
           if (sk) hipLaunchKernelGGL(k_sp_skel_update<true>, gs, dim3(256), 0, s, P, 1, -1.0);
         } else if (op == 2 && !down) {
           hipLaunchKernelGGL(k_sp_gather<false>, gr, dim3(256), 0, s, P);
           if (sk) hipLaunchKernelGGL(k_sp_skel_update<true>, gs, dim3(256), 0, s, P, 1, 1.0);
-          hipLaunchKernelGGL((k_sp_rowmv<0, true>), gw, dim3(256), 0, s, P, 0);
-          hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
+          hipLaunchKernelGGL((k_sp_rowmv<0, true>), gw, dim3(256), 0, s, P, kInB, kInU);
         } else if (op == 2) {
           hipLaunchKernelGGL(k_sp_gather<false>, gr, dim3(256), 0, s, P);
           if (sk) hipLaunchKernelGGL(k_sp_skel_update<true>, gs, dim3(256), 0, s, P, 0, 1.0);
-          hipLaunchKernelGGL((k_sp_rowmv<1, false>), gw, dim3(256), 0, s, P, 0);
-          hipLaunchKernelGGL(k_sp_scatter<true>, gr, dim3(256), 0, s, P, 0);
-          if (sk) hipLaunchKernelGGL((k_sp_first_cols<false, false, true>), gu, dim3(256), 0, s, P);
+          hipLaunchKernelGGL((k_sp_rowmv<1, false>), gw, dim3(256), 0, s, P, kInB, kInPu);
+          if (sk) first_cols<false, false, true>(P, gu, s);
         } else if (!down) {
           hipLaunchKernelGGL(k_sp_gather<true>, gr, dim3(256), 0, s, P);
           if (sk) hipLaunchKernelGGL(k_sp_skel_update<true>, gs, dim3(256), 0, s, P, 1, 1.0);
-          hipLaunchKernelGGL((k_sp_colmv<2, true>), gu, dim3(256), 0, s, P, 0);
-          hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
+          colmv<2, true>(P, gu, s, kInB, kInU);
         } else {
           hipLaunchKernelGGL(k_sp_gather<false>, gr, dim3(256), 0, s, P);
-          if (sk) hipLaunchKernelGGL(k_sp_skel_update_T<true>, gt, dim3(256), 0, s, P, 1.0);
-          hipLaunchKernelGGL((k_sp_colmv<3, false>), gu, dim3(256), 0, s, P, 0);
-          hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
-          if (sk) hipLaunchKernelGGL((k_sp_first_cols<false, false, true>), gu, dim3(256), 0, s, P);
+          if (sk) skel_update_T<true>(P, gt, s, 1.0);
+          colmv<3, false>(P, gu, s, kInB, kInU);
+          if (sk) first_cols<false, false, true>(P, gu, s);
         }
         return;
       }
@@ -1837,31 +1954,23 @@ static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64
       P.sync = H->sync.p;
       P.wait_ticks = wait_ticks;
       P.nbm = nbk;
-      const dim3 gr(unsigned((r + 255) / 256), 1), gu(unsigned((r + 63) / 64), 1), gw(unsigned((r + 15) / 16), 1);
+      const dim3 gu(unsigned(nbk), 1), gw(unsigned((r + 15) / 16), 1);
+      SpArgs P2 = P;
+      P2.sync = P.sync + 1;
       if (op == 0) {
-        hipLaunchKernelGGL((k_sp_first_cols<false, true>), gu, dim3(256), 0, s, P);
-        chain(P, 0, 1, s);
-        hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
-        hipLaunchKernelGGL(k_sp_down_first, gw, dim3(256), 0, s, P);
-        chain(P, 1, 1, s);
-        hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
+        hipLaunchKernelGGL(k_sp_ready, gu, dim3(256), 0, s, P);
+        chain(P, 0, 1, s, kInPu, kInX, 0);
+        chain(P2, 1, 1, s, kInX, kInB, kInU);
       } else if (op == 1) {
-        hipLaunchKernelGGL((k_sp_first_cols<false, false>), gu, dim3(256), 0, s, P);
-        chain(P, 2, 1, s);
-        hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 0);
-        hipLaunchKernelGGL((k_sp_first_cols<true, false>), gu, dim3(256), 0, s, P);
-        chain(P, 3, 1, s);
-        hipLaunchKernelGGL(k_sp_scatter<true>, gr, dim3(256), 0, s, P, 0);
+        hipLaunchKernelGGL(k_sp_ready, gu, dim3(256), 0, s, P);
+        chain(P, 2, 1, s, kInU, kInX, 0);
+        chain(P2, 3, 1, s, kInX, kInB, kInPu);
       } else if (op == 2) {
-        hipLaunchKernelGGL(k_sp_gather<false>, gr, dim3(256), 0, s, P);
-        hipLaunchKernelGGL((k_sp_rowmv<0, false>), gw, dim3(256), 0, s, P, 0);
-        hipLaunchKernelGGL((k_sp_rowmv<1, false>), gw, dim3(256), 0, s, P, 1);
-        hipLaunchKernelGGL(k_sp_scatter<true>, gr, dim3(256), 0, s, P, 1);
+        hipLaunchKernelGGL((k_sp_rowmv<0, false>), gw, dim3(256), 0, s, P, kInU, kInX);
+        hipLaunchKernelGGL((k_sp_rowmv<1, false>), gw, dim3(256), 0, s, P, kInX, kInPu);
       } else {
-        hipLaunchKernelGGL(k_sp_gather<true>, gr, dim3(256), 0, s, P);
-        hipLaunchKernelGGL((k_sp_colmv<2, false>), gu, dim3(256), 0, s, P, 0);
-        hipLaunchKernelGGL((k_sp_colmv<3, false>), gu, dim3(256), 0, s, P, 1);
-        hipLaunchKernelGGL(k_sp_scatter<false>, gr, dim3(256), 0, s, P, 1);
+        colmv<2, false>(P, gu, s, kInPu, kInX);
+        colmv<3, false>(P, gu, s, kInX, kInU);
       }
     } else if (H->ntop > 0) {
       if (2 * H->ntop <= kCapL)
@@ -1889,36 +1998,30 @@ static void build_dinv(hif_factor_s* H, hipStream_t s) {
     sub.dinv.alloc(size_t(sub.nrec) * sub.dinv_nb * 2 * kNbT * kNbT, &H->mem);
     SpArgs P{sub.rec.p, sub.iarena.p, sub.darena.p, sub.woff.p, nullptr, nullptr, nullptr, H->n, 1,
              nullptr, sub.dinv_nb};
-    hipLaunchKernelGGL(k_sp_dinv, dim3(unsigned(sub.dinv_nb), unsigned(sub.nrec)), dim3(64), 0, s, P, sub.dinv.p);
+    hipLaunchKernelGGL(k_sp_dinv, dim3(unsigned(sub.dinv_nb), unsigned(sub.nrec)), dim3(128), 0, s, P, sub.dinv.p);
   }
   HIF_HIP(hipGetLastError());
 }
 
 void prepare_sweeps(hif_factor_s* H, hipStream_t s) {
   build_dinv(H, s);
-  // the ticket counter of the chained triangular solves
+  // the ticket counters of the chained triangular solves
   bool chained = top_split_solve(H);
   for (const SubLevel& sub : H->subs) chained = chained || sub.dinv.p != nullptr;
-  if (chained && !H->sync.p) H->sync.alloc(1, &H->mem);
+  if (chained && !H->sync.p) H->sync.alloc(2, &H->mem);
   if (!top_split_solve(H) || H->top_rec.p) return;
   const int r = int(H->ntop);
   H->top_iarena.alloc(size_t(3) * r, &H->mem);
-  HIF_HIP(hipMemcpyAsync(H->top_iarena.p, H->top_idx.p, sizeof(int32_t) * r, hipMemcpyDeviceToDevice, s));
-  HIF_HIP(hipMemcpyAsync(H->top_iarena.p + r, H->top_piv.p, sizeof(int32_t) * r, hipMemcpyDeviceToDevice, s));
-  HIF_HIP(hipMemcpyAsync(H->top_iarena.p + 2 * r, H->top_perm.p, sizeof(int32_t) * r, hipMemcpyDeviceToDevice, s));
-  const GroupRec rec{r, 0, 0, 0};
-  const int64_t wo = 0;
   H->top_rec.alloc(1, &H->mem);
   H->top_woff.alloc(1, &H->mem);
-  HIF_HIP(hipMemcpyAsync(H->top_rec.p, &rec, sizeof(GroupRec), hipMemcpyHostToDevice, s));
-  HIF_HIP(hipMemcpyAsync(H->top_woff.p, &wo, sizeof(int64_t), hipMemcpyHostToDevice, s));
+  hipLaunchKernelGGL(k_top_record, dim3(unsigned((r + 255) / 256)), dim3(256), 0, s, H->top_idx.p, H->top_piv.p,
+                     H->top_perm.p, r, H->top_iarena.p, H->top_rec.p, H->top_woff.p);
   const int nbk = (r + kNbT - 1) / kNbT;
   H->top_dinv.alloc(size_t(nbk) * 2 * kNbT * kNbT, &H->mem);
   SpArgs P{H->top_rec.p, H->top_iarena.p, H->top_lu.p, H->top_woff.p, nullptr, nullptr, nullptr, H->n, 1,
            nullptr, nbk};
-  hipLaunchKernelGGL(k_sp_dinv, dim3(unsigned(nbk), 1), dim3(64), 0, s, P, H->top_dinv.p);
+  hipLaunchKernelGGL(k_sp_dinv, dim3(unsigned(nbk), 1), dim3(128), 0, s, P, H->top_dinv.p);
   HIF_HIP(hipGetLastError());
-  HIF_HIP(hipStreamSynchronize(s));  // the host values above are copied before they go out of scope
 }
 
 void sweep_impl(hif_factor_s* H, int op, const double* x, double* y, int64_t nrhs, hipStream_t s) {

@@ -136,3 +136,37 @@ def test_matvec_sizes_and_right_hand_sides(d, n, nrhs):
         ref = a[i] * x[:, i] + b[i] * ((K * c) * x).sum(1)
         mag = np.abs(a[i] * x[:, i]) + b[i] * ((np.maximum(np.abs(K), 1e-3 * w) * c) * np.abs(x)).sum(1)
         assert np.all(np.abs(y[:, i] - ref) <= (2 * n * u + 16 * u) * mag)
+
+
+@pytest.mark.parametrize("n,d,leaf,eps", [(16, 2, 64, 1e-9), (28, 2, 64, 1e-9), (40, 2, 16, 1e-9), (64, 2, 64, 1e-10),
+                                          (12, 3, 64, 1e-6), (20, 3, 64, 1e-6)])
+def test_sweeps_top_sizes_and_right_hand_sides(n, d, leaf, eps):
+    # The four sweeps of a non-symmetric operator over top blocks from below
+    # one 64-row block of the chained solve to many, and over records of few
+    # large groups.  F^-1 F x = x and <F^T x, y> = <x, F y> to rounding times
+    # the size of the operator's inverse (about 1 here: a well conditioned
+    # second-kind operator), and right-hand sides taken together, in passes of
+    # 1, 4 and 8, give each one's own result.
+    rng = np.random.default_rng(n * d)
+    g = (np.arange(n) + 0.5) / n
+    pts = np.stack(np.meshgrid(*[g] * d, indexing="ij"), -1).reshape(-1, d)
+    N = n ** d
+    t = lambda v: torch.tensor(v, device="cuda:0")  # noqa: E731
+    F = hif.factor(t(pts), eps, leaf, a=t(1.0 + rng.random(N)), b=t(0.5 + rng.random(N)), c=t(0.5 + rng.random(N)),
+                   h=1.0 / n)
+    x, y = t(rng.standard_normal((9, N))), t(rng.standard_normal((9, N)))
+    rel = lambda a, b: (torch.linalg.norm(a - b, dim=1) / torch.linalg.norm(b, dim=1)).max().item()  # noqa: E731
+    assert rel(F.solve(F.apply(x)), x) <= 1e-10
+    assert rel(F.solve_T(F.apply_T(x)), x) <= 1e-10
+    for op, tr in ((F.apply, F.apply_T), (F.solve, F.solve_T)):
+        Oy = op(y)
+        dot = ((tr(x) * y).sum(1) - (x * Oy).sum(1)).abs() / (torch.linalg.norm(x, dim=1) * torch.linalg.norm(Oy, dim=1))
+        assert dot.max().item() <= 1e-12
+        for f in (op, tr):
+            full = f(x)
+            for k in (1, 2, 3, 4, 5):
+                assert rel(f(x[:k].clone()), full[:k]) <= 1e-13
+            z = x.clone()
+            f(z, out=z)  # in place
+            assert torch.equal(z, full)
+    F.free()
