@@ -6,20 +6,16 @@
 #include <climits>
 
 #include "common.h"
+#include "wave.h"
 
 namespace hif {
 
-template <int CTRL>
-__device__ __forceinline__ int dpp(int x) {
-  return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false);
-}
 template <int CTRL>
 __device__ __forceinline__ double dpp_max(double x) {
   const unsigned long long u = __double_as_longlong(x);
   const int lo = dpp<CTRL>(int(unsigned(u))), hi = dpp<CTRL>(int(unsigned(u >> 32)));
   return fmax(x, __longlong_as_double((static_cast<long long>(hi) << 32) | unsigned(lo)));
 }
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;  // within rows of 16 lanes
 // Largest value of each aligned group of G = 4, 8 or 16 lanes, on all of them (no NaN).
 template <int G>
 __device__ __forceinline__ double group_max(double x) {

@@ -253,107 +253,6 @@ __global__ void k_down(SwArgs A) {
   }
 }
 
-// Block solve / multiply with an LU factorization P B = L U (row interchanges
-// j <-> piv[j] applied in order j = 0..n-1), on the entries u[v*N + idx[i]].
-__device__ void lu_op(const double* LU, const int32_t* piv, int n, const int32_t* idx, double* u, double* work,
-                      int64_t N, int nrhs, int op) {
-  const int tid = threadIdx.x, B = blockDim.x;
-  auto X = [&](int i, int v) -> double& { return u[v * N + idx[i]]; };
-  auto W = [&](int i, int v) -> double& { return work[v * N + idx[i]]; };
-  if (op == 0) {  // x = B^{-1} x = U^{-1} L^{-1} P x
-    for (int v = tid; v < nrhs; v += B)
-      for (int j = 0; j < n; ++j)
-        if (piv[j] != j) { double t = X(j, v); X(j, v) = X(piv[j], v); X(piv[j], v) = t; }
-    __syncthreads();
-    for (int j = 0; j < n - 1; ++j) {
-      const int w = n - 1 - j;
-      for (int e = tid; e < w * nrhs; e += B) {
-        const int i = j + 1 + e % w, v = e / w;
-        X(i, v) -= LU[int64_t(i) * n + j] * X(j, v);
-      }
-      __syncthreads();
-    }
-    for (int j = n - 1; j >= 0; --j) {
-      const double inv = 1.0 / LU[int64_t(j) * n + j];
-      for (int e = tid; e < j * nrhs; e += B) {
-        const int i = e % j, v = e / j;
-        X(i, v) -= LU[int64_t(i) * n + j] * (X(j, v) * inv);
-      }
-      __syncthreads();
-    }
-    for (int e = tid; e < n * nrhs; e += B) {
-      const int i = e % n, v = e / n;
-      X(i, v) /= LU[int64_t(i) * n + i];
-    }
-  } else if (op == 1) {  // x = B^{-T} x = P^T L^{-T} U^{-T} x
-    for (int j = 0; j < n; ++j) {
-      const double inv = 1.0 / LU[int64_t(j) * n + j];
-      const int w = n - 1 - j;
-      for (int e = tid; e < w * nrhs; e += B) {
-        const int i = j + 1 + e % w, v = e / w;
-        X(i, v) -= LU[int64_t(j) * n + i] * (X(j, v) * inv);
-      }
-      __syncthreads();
-    }
-    for (int e = tid; e < n * nrhs; e += B) {
-      const int i = e % n, v = e / n;
-      X(i, v) /= LU[int64_t(i) * n + i];
-    }
-    __syncthreads();
-    for (int j = n - 1; j > 0; --j) {
-      for (int e = tid; e < j * nrhs; e += B) {
-        const int i = e % j, v = e / j;
-        X(i, v) -= LU[int64_t(j) * n + i] * X(j, v);
-      }
-      __syncthreads();
-    }
-    for (int v = tid; v < nrhs; v += B)
-      for (int j = n - 1; j >= 0; --j)
-        if (piv[j] != j) { double t = X(j, v); X(j, v) = X(piv[j], v); X(piv[j], v) = t; }
-  } else if (op == 2) {  // x = B x = P^T L U x
-    for (int e = tid; e < n * nrhs; e += B) {
-      const int i = e % n, v = e / n;
-      double s = 0.0;
-      for (int j = i; j < n; ++j) s += LU[int64_t(i) * n + j] * X(j, v);
-      W(i, v) = s;
-    }
-    __syncthreads();
-    for (int e = tid; e < n * nrhs; e += B) {
-      const int i = e % n, v = e / n;
-      double s = W(i, v);
-      for (int j = 0; j < i; ++j) s += LU[int64_t(i) * n + j] * W(j, v);
-      X(i, v) = s;
-    }
-    __syncthreads();
-    for (int v = tid; v < nrhs; v += B)
-      for (int j = n - 1; j >= 0; --j)
-        if (piv[j] != j) { double t = X(j, v); X(j, v) = X(piv[j], v); X(piv[j], v) = t; }
-  } else {  // x = B^T x = U^T L^T P x
-    for (int v = tid; v < nrhs; v += B)
-      for (int j = 0; j < n; ++j)
-        if (piv[j] != j) { double t = X(j, v); X(j, v) = X(piv[j], v); X(piv[j], v) = t; }
-    __syncthreads();
-    for (int e = tid; e < n * nrhs; e += B) {
-      const int i = e % n, v = e / n;
-      double s = X(i, v);
-      for (int j = i + 1; j < n; ++j) s += LU[int64_t(j) * n + i] * X(j, v);
-      W(i, v) = s;
-    }
-    __syncthreads();
-    for (int e = tid; e < n * nrhs; e += B) {
-      const int i = e % n, v = e / n;
-      double s = 0.0;
-      for (int j = 0; j <= i; ++j) s += LU[int64_t(j) * n + i] * W(j, v);
-      X(i, v) = s;
-    }
-  }
-}
-
-__global__ void k_top(const double* LU, const int32_t* piv, int n, const int32_t* idx, double* u, double* work,
-                      int64_t N, int nrhs, int op) {
-  lu_op(LU, piv, n, idx, u, work, N, nrhs, op);
-}
-
 // ---------------------------------------------------------------------------
 // LDS-staged solve / solve_T.  The entries u_r, u_s of a group (or the top
 // block's entries) are gathered into LDS once; the products and the blocked
@@ -371,131 +270,104 @@ constexpr int kCapL = 16384;   // LDS doubles, largest records and the top block
 constexpr int kManyRecords = 1024;
 // Top blocks of at least this many unknowns are solved by the many-workgroup
 // blocked triangular solves: one workgroup walks the block's rows with the
-// loads of one workgroup in flight (a solve with a top of 212: 154 us against
-// 101, of 474: 527 against 286; applies of 212: 115 against 94).  Below two
-// 64-row blocks there is nothing to hand over.
+// loads of one workgroup in flight (a solve with a top of 152: 93 us against
+// 61, of 474: 527 against 286, of 2872: 5360 against 161; applies of 152: 72
+// against 51).  Below two 64-row blocks there is nothing to hand over.
 constexpr int64_t kTopSplitMin = 128;
 
-// The helpers below issue their global loads eight at a time before using
-// them, so that a single workgroup (one per large group) keeps many requests
-// in flight.  Indices past a block are guarded on both factors.
-constexpr int kU = 8;
+// Loads in flight per lane in the products below.  A workgroup waits for
+// memory at most a few times in a product then: a wait (with the address
+// translation of a record's pages, each touched once) costs 1 - 2 us here.
+constexpr int kU = 16;
 
-// y[v*ys + i] += sgn * sum_j M[i*ld + j] x[v*xs + j]   (one wave per row)
+// y[v*ys + i] += sgn * sum_j M[i*ld + j] x[v*xs + j]   (one wave per row).  A
+// wave takes R rows and 64 C columns of each at a time, R C loads before any is
+// used (16 rows of up to 64 columns at a time were slower than 4: the code is
+// run a few times per workgroup, and four times as much of it has to be
+// fetched); TRI >= 0 keeps one triangle: 0 the columns j >= i, 1 the columns
+// j < i.
+template <int R, int C, int TRI>
+__device__ __forceinline__ void l_gemv_n_rc(const double* __restrict__ M, int nrow, int ncol, int ld, const double* x,
+                                            int xs, double* y, int ys, int nv, double sgn) {
+  constexpr bool kOnce = R > 2;  // the columns fit: a row is finished before the next
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  for (int i0 = wv; i0 < nrow; i0 += R * nw) {
+    double acc[kOnce ? 1 : R][kMaxV];
+    if constexpr (!kOnce)
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+#pragma unroll
+        for (int v = 0; v < kMaxV; ++v) acc[q][v] = 0.0;
+    auto put = [&](double (&a)[kMaxV], int i) {
+      const double t = wave_rs8(a);
+      const int v = lane >> 3;
+      if ((lane & 7) == 0 && v < nv && i < nrow) y[v * ys + i] += sgn * t;
+    };
+    for (int j0 = 0; j0 < ncol; j0 += 64 * C) {
+      double m[R][C];
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+#pragma unroll
+        for (int h = 0; h < C; ++h) {
+          const int i = min(i0 + q * nw, nrow - 1), j = j0 + 64 * h + lane;
+          const double t = M[int64_t(i) * ld + min(j, ncol - 1)];
+          m[q][h] = j < ncol && (TRI != 0 || j >= i) && (TRI != 1 || j < i) ? t : 0.0;
+        }
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        if (i0 + q * nw >= nrow) break;
+        double(&a)[kMaxV] = acc[kOnce ? 0 : q];
+        if constexpr (kOnce)
+#pragma unroll
+          for (int v = 0; v < kMaxV; ++v) a[v] = 0.0;
+#pragma unroll
+        for (int h = 0; h < C; ++h) {
+          const int j = j0 + 64 * h + lane;
+          if (j < ncol)
+#pragma unroll
+            for (int v = 0; v < kMaxV; ++v)
+              if (v < nv) a[v] += m[q][h] * x[v * xs + j];
+        }
+        if constexpr (kOnce) put(a, i0 + q * nw);
+      }
+    }
+    if constexpr (!kOnce)
+#pragma unroll
+      for (int q = 0; q < R; ++q) put(acc[q], i0 + q * nw);
+  }
+}
+
+template <int TRI = -1>
 __device__ __forceinline__ void l_gemv_n(const double* __restrict__ M, int nrow, int ncol, int ld, const double* x, int xs, double* y,
                          int ys, int nv, double sgn) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if (ncol <= 64) {
-    // rows of at most one element per lane: x in registers, four rows of the
-    // wave at a time with their loads issued together
-    double xv[kMaxV];
-#pragma unroll
-    for (int v = 0; v < kMaxV; ++v) xv[v] = (v < nv && lane < ncol) ? x[v * xs + lane] : 0.0;
-    for (int i0 = wv; i0 < nrow; i0 += 4 * nw) {
-      double m[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + q * nw;
-        m[q] = (i < nrow && lane < ncol) ? M[int64_t(i) * ld + lane] : 0.0;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + q * nw;
-        if (i < nrow) {
-          double acc[kMaxV];
-#pragma unroll
-          for (int v = 0; v < kMaxV; ++v) acc[v] = m[q] * xv[v];
-          const double t = wave_rs8(acc);
-          const int v = lane >> 3;
-          if ((lane & 7) == 0 && v < nv) y[v * ys + i] += sgn * t;
-        }
-      }
-    }
-    return;
-  }
-  if (ncol <= 128) {
-    // rows of at most two entries per lane: four rows of the wave at a time,
-    // their eight loads issued together, x read from LDS (no more registers
-    // than one row at a time); each sum in the order of the general path
-    for (int i0 = wv; i0 < nrow; i0 += 4 * nw) {
-      double m[4][2];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + q * nw;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int j = 64 * h + lane;
-          m[q][h] = (i < nrow && j < ncol) ? M[int64_t(i) * ld + j] : 0.0;
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + q * nw;
-        if (i < nrow) {
-          double acc[kMaxV];
-#pragma unroll
-          for (int v = 0; v < kMaxV; ++v) acc[v] = 0.0;
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int j = 64 * h + lane;
-            if (j < ncol) {
-#pragma unroll
-              for (int v = 0; v < kMaxV; ++v)
-                if (v < nv) acc[v] += m[q][h] * x[v * xs + j];
-            }
-          }
-          const double t = wave_rs8(acc);
-          const int v = lane >> 3;
-          if ((lane & 7) == 0 && v < nv) y[v * ys + i] += sgn * t;
-        }
-      }
-    }
-    return;
-  }
-  for (int i = wv; i < nrow; i += nw) {
-    const double* mr = M + int64_t(i) * ld;
-    double acc[kMaxV];
-#pragma unroll
-    for (int v = 0; v < kMaxV; ++v) acc[v] = 0.0;
-    for (int j0 = 0; j0 < ncol; j0 += 64 * kU) {
-      double mv[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int j = j0 + u * 64 + lane;
-        mv[u] = j < ncol ? mr[j] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int j = j0 + u * 64 + lane;
-        if (j < ncol) {
-#pragma unroll
-          for (int v = 0; v < kMaxV; ++v)
-            if (v < nv) acc[v] += mv[u] * x[v * xs + j];
-        }
-      }
-    }
-    // the 8 right-hand sides' sums at once: lane l holds that of l >> 3
-    const double t = wave_rs8(acc);
-    const int v = lane >> 3;
-    if ((lane & 7) == 0 && v < nv) y[v * ys + i] += sgn * t;
-  }
+  if (ncol <= 0) return;
+  if (ncol <= 64)
+    l_gemv_n_rc<4, 1, TRI>(M, nrow, ncol, ld, x, xs, y, ys, nv, sgn);
+  else if (ncol <= 128)
+    l_gemv_n_rc<4, 2, TRI>(M, nrow, ncol, ld, x, xs, y, ys, nv, sgn);
+  else if (ncol <= 256)
+    l_gemv_n_rc<4, 4, TRI>(M, nrow, ncol, ld, x, xs, y, ys, nv, sgn);
+  else
+    l_gemv_n_rc<2, 8, TRI>(M, nrow, ncol, ld, x, xs, y, ys, nv, sgn);
 }
 
 // y[v*ys + j] += sgn * sum_i M[i*ld + j] x[v*xs + i]   (one thread per column).
 // With few columns the waves split the rows: wave w takes column group
-// w % ncg (64 columns) and row slice w / ncg (at most 4 slices), and the
-// slices add their partial sums in slice order (deterministic).  Every
-// thread of the workgroup calls it; it ends synchronized.
+// w % ncg (64 columns) and row slice w / ncg (at least 8 rows each), and the
+// slices add their partial sums in slice order (deterministic).  TRI >= 0 keeps
+// one triangle: 2 the rows i > j, 3 the rows i <= j.  Every thread of the
+// workgroup calls it; it ends synchronized.
+template <int TRI = -1>
 __device__ __forceinline__ void l_gemv_t(const double* __restrict__ M, int nrow, int ncol, int ld, const double* x, int xs, double* y,
                          int ys, int nv, double sgn) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   if (ncol <= 0 || nrow <= 0) {
     __syncthreads();
     return;
   }
   const int ncg = (ncol + 63) / 64;
-  const int nrs = ncg <= nw ? min(4, nw / ncg) : 1;
   const bool split = ncg <= nw;
+  const int nrs = split ? min((nrow + 7) / 8, nw / ncg) : 1;
   const int cg = split ? wv % ncg : 0, rs = split ? wv / ncg : 0;
   const bool active = !split || wv < ncg * nrs;
   const int ib = split ? (nrow * rs) / nrs : 0, ie = split ? (nrow * (rs + 1)) / nrs : nrow;
@@ -506,13 +378,14 @@ __device__ __forceinline__ void l_gemv_t(const double* __restrict__ M, int nrow,
     for (int i0 = ib; i0 < ie; i0 += kU) {
       double mv[kU];
 #pragma unroll
-      for (int u = 0; u < kU; ++u) mv[u] = i0 + u < ie ? M[int64_t(i0 + u) * ld + j] : 0.0;
+      for (int u = 0; u < kU; ++u) mv[u] = M[int64_t(min(i0 + u, ie - 1)) * ld + j];
 #pragma unroll
       for (int u = 0; u < kU; ++u)
         if (i0 + u < ie) {
+          const double m = (TRI != 2 || i0 + u > j) && (TRI != 3 || i0 + u <= j) ? mv[u] : 0.0;
 #pragma unroll
           for (int v = 0; v < kMaxV; ++v)
-            if (v < nv) acc[v] += mv[u] * x[v * xs + i0 + u];
+            if (v < nv) acc[v] += m * x[v * xs + i0 + u];
         }
     }
     if (!split)
@@ -533,35 +406,113 @@ __device__ __forceinline__ void l_gemv_t(const double* __restrict__ M, int nrow,
   __syncthreads();
 }
 
-// x = L^{-1} x, L the unit lower triangle of the row-major n x n LU.
-__device__ __forceinline__ void l_solve_L(const double* __restrict__ LU, int n, double* x, int xs, int nv) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
-  for (int j0 = 0; j0 < n; j0 += kNbT) {
-    const int nb = min(kNbT, n - j0);
-    const double* Lr = LU + int64_t(j0 + min(lane, nb - 1)) * n + j0;
-    // a wave takes right-hand sides v and v + nw together: one load of each
-    // entry of L for both
+// The value of lane l, a scalar.
+__device__ __forceinline__ double lane_value(double x, int l) {
+  const uint64_t b = uint64_t(__double_as_longlong(x));
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b)), l));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b >> 32)), l));
+  return __longlong_as_double((long long)((uint64_t(hi) << 32) | lo));
+}
+
+// One triangle of a diagonal block of at most kNbT rows, packed in LDS: entry
+// (a, c) of a lower triangle at a (a + 1) / 2 + c, of an upper one the same
+// with rows and columns reversed.  Triangular numbers are a permutation modulo
+// a power of two, so a column is read without bank conflicts.
+__host__ __device__ constexpr int tri_len(int nb) { return nb * (nb + 1) / 2; }
+
+constexpr int kSu = 8;  // columns of the triangle read together
+
+template <bool UPPER>
+__device__ __forceinline__ int tri_at(int nb, int a, int c) {
+  return UPPER ? tri_len(nb - 1 - a) + nb - 1 - c : tri_len(a) + c;
+}
+
+template <bool UPPER>
+__device__ __forceinline__ void tri_stage(const double* __restrict__ LU, int n, int j0, double* tri) {
+  const int nb = min(kNbT, n - j0);
+  const double* M = LU + int64_t(j0) * n + j0;
+  const int c = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  for (int a0 = w; a0 < nb; a0 += kU * nw) {
+    double m[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) m[u] = M[int64_t(min(a0 + u * nw, nb - 1)) * n + min(c, nb - 1)];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int a = a0 + u * nw;
+      if (a < nb && c < nb && (UPPER ? c >= a : c <= a)) tri[tri_at<UPPER>(nb, a, c)] = m[u];
+    }
+  }
+}
+
+// x = M^{-1} x, M a triangle of the row-major n x n LU: MODE 0 its unit lower
+// L, 1 its upper U, 2 U^T, 3 L^T.  By blocks of 64 rows: a wave per right-hand
+// side (or two) substitutes within the block, lane = row, each solved entry
+// broadcast through a scalar register; then the rows not yet solved take the
+// block's product.  The substitution is a chain of dependent steps, so its
+// triangle is read from LDS (read from memory by rows, eight entries per lane
+// at a time, and broadcast through LDS, a 64-row block took about 12 us).  The
+// first triangle is in tri when this is called (tri_first, ordered by a
+// barrier); the next is staged while the rows are updated.
+template <int MODE>
+__device__ __forceinline__ void tri_first(const double* __restrict__ LU, int n, double* tri) {
+  if (n > 0) tri_stage<MODE == 1 || MODE == 2>(LU, n, MODE == 0 || MODE == 2 ? 0 : ((n - 1) / kNbT) * kNbT, tri);
+}
+
+template <int MODE>
+__device__ __forceinline__ void l_solve(const double* __restrict__ LU, int n, double* x, int xs, int nv, double* tri) {
+  constexpr bool kFwd = MODE == 0 || MODE == 2, kUp = MODE == 1 || MODE == 2;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int nblk = (n + kNbT - 1) / kNbT;
+  for (int jb = 0; jb < nblk; ++jb) {
+    const int j0 = (kFwd ? jb : nblk - 1 - jb) * kNbT, nb = min(kNbT, n - j0), row = min(lane, nb - 1);
+    // a wave takes right-hand sides v and v + nw together: one read of each
+    // entry of the triangle for both
     for (int v = wv; v < nv; v += 2 * nw) {
       auto pass = [&](auto two_c) {
         constexpr bool TWO = decltype(two_c)::value;
-        double xi = lane < nb ? x[v * xs + j0 + lane] : 0.0;
-        double xj = TWO && lane < nb ? x[(v + nw) * xs + j0 + lane] : 0.0;
-        for (int c0 = 0; c0 < nb - 1; c0 += kU) {
-          double lr[kU];
+        double xi = x[v * xs + j0 + row], xj = TWO ? x[(v + nw) * xs + j0 + row] : 0.0;
+        // a quotient is a product with the reciprocal and one correction
+        double d = 1.0, di = 1.0;
+        if constexpr (kUp) {
+          d = tri[tri_at<true>(nb, row, row)];
+          di = 1.0 / d;
+        }
+        auto quot = [&](double b) {
+          const double q = b * di;
+          return __builtin_fma(__builtin_fma(-q, d, b), di, q);
+        };
+        for (int c0 = 0; c0 < nb; c0 += kSu) {
+          double m[kSu];
 #pragma unroll
-          for (int u = 0; u < kU; ++u) lr[u] = c0 + u < nb ? Lr[c0 + u] : 0.0;
+          for (int u = 0; u < kSu; ++u) {
+            const int c = kFwd ? min(c0 + u, nb - 1) : max(nb - 1 - c0 - u, 0);
+            // the entry of column c (of row c of U or L in the transposed
+            // solves) that lane's row takes; any entry where it takes none
+            if constexpr (MODE == 0) m[u] = tri[tri_at<false>(nb, max(row, c), c)];
+            if constexpr (MODE == 1) m[u] = tri[tri_at<true>(nb, min(row, c), c)];
+            if constexpr (MODE == 2) m[u] = tri[tri_at<true>(nb, c, max(row, c))];
+            if constexpr (MODE == 3) m[u] = tri[tri_at<false>(nb, c, min(row, c))];
+          }
 #pragma unroll
-          for (int u = 0; u < kU; ++u) {
-            const int c = c0 + u;
-            if (c < nb - 1) {
-              const double xc = __shfl(xi, c, 64);
-              if (lane > c && lane < nb) xi -= lr[u] * xc;
+          for (int u = 0; u < kSu; ++u)
+            if (c0 + u < nb) {
+              const int c = kFwd ? c0 + u : nb - 1 - c0 - u;
+              if constexpr (kUp) {
+                const double qi = quot(xi);
+                xi = lane == c ? qi : xi;
+                if constexpr (TWO) {
+                  const double qj = quot(xj);
+                  xj = lane == c ? qj : xj;
+                }
+              }
+              const bool take = kFwd ? lane > c : lane < c;
+              const double ti = xi - m[u] * lane_value(xi, c);
+              xi = take ? ti : xi;
               if constexpr (TWO) {
-                const double xd = __shfl(xj, c, 64);
-                if (lane > c && lane < nb) xj -= lr[u] * xd;
+                const double tj = xj - m[u] * lane_value(xj, c);
+                xj = take ? tj : xj;
               }
             }
-          }
         }
         if (lane < nb) {
           x[v * xs + j0 + lane] = xi;
@@ -574,157 +525,19 @@ __device__ __forceinline__ void l_solve_L(const double* __restrict__ LU, int n, 
         pass(std::false_type{});
     }
     __syncthreads();
-    // the rows below: x_i -= L(i, block) x_block, four rows of a wave at a time
-    if (j0 + nb < n) l_gemv_n(LU + int64_t(j0 + nb) * n + j0, n - j0 - nb, nb, n, x + j0, xs, x + j0 + nb, xs, nv, -1.0);
-    __syncthreads();
-  }
-}
-
-// x = U^{-1} x, U the upper triangle of the LU.
-__device__ __forceinline__ void l_solve_U(const double* __restrict__ LU, int n, double* x, int xs, int nv) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
-  if (n <= 0) return;
-  for (int j0 = ((n - 1) / kNbT) * kNbT; j0 >= 0; j0 -= kNbT) {
-    const int nb = min(kNbT, n - j0);
-    const double* Ur = LU + int64_t(j0 + min(lane, nb - 1)) * n + j0;
-    for (int v = wv; v < nv; v += 2 * nw) {  // two right-hand sides per pass, as in l_solve_L
-      auto pass = [&](auto two_c) {
-        constexpr bool TWO = decltype(two_c)::value;
-        double xi = lane < nb ? x[v * xs + j0 + lane] : 0.0;
-        double xj = TWO && lane < nb ? x[(v + nw) * xs + j0 + lane] : 0.0;
-        for (int cb = ((nb - 1) / kU) * kU; cb >= 0; cb -= kU) {
-          double ur[kU];
-#pragma unroll
-          for (int u = 0; u < kU; ++u) ur[u] = cb + u < nb ? Ur[cb + u] : 1.0;
-#pragma unroll
-          for (int u = kU - 1; u >= 0; --u) {
-            const int c = cb + u;
-            if (c < nb) {
-              if (lane == c) xi = xi / ur[u];
-              const double xc = __shfl(xi, c, 64);
-              if (lane < c) xi -= ur[u] * xc;
-              if constexpr (TWO) {
-                if (lane == c) xj = xj / ur[u];
-                const double xd = __shfl(xj, c, 64);
-                if (lane < c) xj -= ur[u] * xd;
-              }
-            }
-          }
-        }
-        if (lane < nb) {
-          x[v * xs + j0 + lane] = xi;
-          if constexpr (TWO) x[(v + nw) * xs + j0 + lane] = xj;
-        }
-      };
-      if (v + nw < nv)
-        pass(std::true_type{});
-      else
-        pass(std::false_type{});
+    if (jb + 1 < nblk) {
+      tri_stage<kUp>(LU, n, kFwd ? j0 + kNbT : j0 - kNbT, tri);
+      const int rest = n - j0 - nb;
+      if constexpr (MODE == 0)  // the rows below: x_i -= L(i, block) x_block
+        l_gemv_n(LU + int64_t(j0 + nb) * n + j0, rest, nb, n, x + j0, xs, x + j0 + nb, xs, nv, -1.0);
+      if constexpr (MODE == 1)  // the rows above: x_i -= U(i, block) x_block
+        l_gemv_n(LU + j0, j0, nb, n, x + j0, xs, x, xs, nv, -1.0);
+      if constexpr (MODE == 2)  // the entries below: x_i -= sum_c U(j0 + c, i) x_{j0 + c}
+        l_gemv_t(LU + int64_t(j0) * n + j0 + nb, nb, rest, n, x + j0, xs, x + j0 + nb, xs, nv, -1.0);
+      if constexpr (MODE == 3)  // the entries above: x_i -= sum_c L(j0 + c, i) x_{j0 + c}
+        l_gemv_t(LU + int64_t(j0) * n, nb, j0, n, x + j0, xs, x, xs, nv, -1.0);
+      __syncthreads();
     }
-    __syncthreads();
-    // the rows above: x_i -= U(i, block) x_block
-    if (j0 > 0) l_gemv_n(LU + j0, j0, nb, n, x + j0, xs, x, xs, nv, -1.0);
-    __syncthreads();
-  }
-}
-
-// x = U^{-T} x (U^T lower with diagonal U_jj), forward over column blocks.
-__device__ __forceinline__ void l_solve_UT(const double* __restrict__ LU, int n, double* x, int xs, int nv) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
-  for (int j0 = 0; j0 < n; j0 += kNbT) {
-    const int nb = min(kNbT, n - j0);
-    const int cl = j0 + min(lane, nb - 1);
-    for (int v = wv; v < nv; v += 2 * nw) {  // two right-hand sides per pass, as in l_solve_L
-      auto pass = [&](auto two_c) {
-        constexpr bool TWO = decltype(two_c)::value;
-        double xi = lane < nb ? x[v * xs + j0 + lane] : 0.0;
-        double xj = TWO && lane < nb ? x[(v + nw) * xs + j0 + lane] : 0.0;
-        for (int c0 = 0; c0 < nb; c0 += kU) {
-          double uc[kU], ud[kU];
-#pragma unroll
-          for (int u = 0; u < kU; ++u) {
-            const int c = c0 + u < nb ? c0 + u : nb - 1;
-            uc[u] = LU[int64_t(j0 + c) * n + cl];
-            ud[u] = LU[int64_t(j0 + c) * n + j0 + c];
-          }
-#pragma unroll
-          for (int u = 0; u < kU; ++u) {
-            const int c = c0 + u;
-            if (c < nb) {
-              if (lane == c) xi = xi / ud[u];
-              const double xc = __shfl(xi, c, 64);
-              if (lane > c && lane < nb) xi -= uc[u] * xc;
-              if constexpr (TWO) {
-                if (lane == c) xj = xj / ud[u];
-                const double xd = __shfl(xj, c, 64);
-                if (lane > c && lane < nb) xj -= uc[u] * xd;
-              }
-            }
-          }
-        }
-        if (lane < nb) {
-          x[v * xs + j0 + lane] = xi;
-          if constexpr (TWO) x[(v + nw) * xs + j0 + lane] = xj;
-        }
-      };
-      if (v + nw < nv)
-        pass(std::true_type{});
-      else
-        pass(std::false_type{});
-    }
-    __syncthreads();
-    // the entries below: x_i -= sum_c U(j0 + c, i) x_{j0 + c} (rows of the block, read by columns)
-    if (j0 + nb < n) l_gemv_t(LU + int64_t(j0) * n + j0 + nb, nb, n - j0 - nb, n, x + j0, xs, x + j0 + nb, xs, nv, -1.0);
-    __syncthreads();
-  }
-}
-
-// x = L^{-T} x (L^T unit upper), backward over column blocks.
-__device__ __forceinline__ void l_solve_LT(const double* __restrict__ LU, int n, double* x, int xs, int nv) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
-  if (n <= 0) return;
-  for (int j0 = ((n - 1) / kNbT) * kNbT; j0 >= 0; j0 -= kNbT) {
-    const int nb = min(kNbT, n - j0);
-    const int cl = j0 + min(lane, nb - 1);
-    for (int v = wv; v < nv; v += 2 * nw) {  // two right-hand sides per pass, as in l_solve_L
-      auto pass = [&](auto two_c) {
-        constexpr bool TWO = decltype(two_c)::value;
-        double xi = lane < nb ? x[v * xs + j0 + lane] : 0.0;
-        double xj = TWO && lane < nb ? x[(v + nw) * xs + j0 + lane] : 0.0;
-        for (int cb = ((nb - 1) / kU) * kU; cb >= 0; cb -= kU) {
-          double lc[kU];
-#pragma unroll
-          for (int u = 0; u < kU; ++u) {
-            const int c = cb + u < nb ? cb + u : nb - 1;
-            lc[u] = LU[int64_t(j0 + c) * n + cl];
-          }
-#pragma unroll
-          for (int u = kU - 1; u >= 0; --u) {
-            const int c = cb + u;
-            if (c < nb && c > 0) {
-              const double xc = __shfl(xi, c, 64);
-              if (lane < c) xi -= lc[u] * xc;
-              if constexpr (TWO) {
-                const double xd = __shfl(xj, c, 64);
-                if (lane < c) xj -= lc[u] * xd;
-              }
-            }
-          }
-        }
-        if (lane < nb) {
-          x[v * xs + j0 + lane] = xi;
-          if constexpr (TWO) x[(v + nw) * xs + j0 + lane] = xj;
-        }
-      };
-      if (v + nw < nv)
-        pass(std::true_type{});
-      else
-        pass(std::false_type{});
-    }
-    __syncthreads();
-    // the entries above: x_i -= sum_c L(j0 + c, i) x_{j0 + c}
-    if (j0 > 0) l_gemv_t(LU + int64_t(j0) * n, nb, j0, n, x + j0, xs, x, xs, nv, -1.0);
-    __syncthreads();
   }
 }
 
@@ -733,58 +546,16 @@ __device__ __forceinline__ void l_solve_LT(const double* __restrict__ LU, int n,
 // columns j < i), both one wave per row; mode 2 the unit upper L^T (x_i plus
 // rows j > i of L), 3 U^T (rows j <= i of U), both one thread per column.
 __device__ __forceinline__ void l_trmv(const double* __restrict__ LU, int n, double* x, double* tp, int nv, int mode) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
-  if (mode <= 1) {
-    for (int i = wv; i < n; i += nw) {
-      const double* mr = LU + int64_t(i) * n;
-      const int jb = mode == 0 ? i : 0, je = mode == 0 ? n : i;
-      double acc[kMaxV];
-#pragma unroll
-      for (int v = 0; v < kMaxV; ++v) acc[v] = 0.0;
-      for (int j0 = jb; j0 < je; j0 += 64 * kU) {
-        double mv[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          const int j = j0 + u * 64 + lane;
-          mv[u] = j < je ? mr[j] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          const int j = j0 + u * 64 + lane;
-          if (j < je) {
-#pragma unroll
-            for (int v = 0; v < kMaxV; ++v)
-              if (v < nv) acc[v] += mv[u] * x[v * n + j];
-          }
-        }
-      }
-      const double t = wave_rs8(acc);
-      const int v = lane >> 3;
-      if ((lane & 7) == 0 && v < nv) tp[v * n + i] = t + (mode == 1 ? x[v * n + i] : 0.0);
-    }
-  } else {
-    for (int i = tid; i < n; i += blockDim.x) {
-      const int jb = mode == 2 ? i + 1 : 0, je = mode == 2 ? n : i + 1;
-      double acc[kMaxV];
-#pragma unroll
-      for (int v = 0; v < kMaxV; ++v) acc[v] = 0.0;
-      for (int j0 = jb; j0 < je; j0 += kU) {
-        double mv[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) mv[u] = j0 + u < je ? LU[int64_t(j0 + u) * n + i] : 0.0;
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-          if (j0 + u < je) {
-#pragma unroll
-            for (int v = 0; v < kMaxV; ++v)
-              if (v < nv) acc[v] += mv[u] * x[v * n + j0 + u];
-          }
-      }
-#pragma unroll
-      for (int v = 0; v < kMaxV; ++v)
-        if (v < nv) tp[v * n + i] = acc[v] + (mode == 2 ? x[v * n + i] : 0.0);
-    }
-  }
+  for (int e = threadIdx.x; e < nv * n; e += blockDim.x) tp[e] = mode == 1 || mode == 2 ? x[e] : 0.0;
+  __syncthreads();
+  if (mode == 0)
+    l_gemv_n<0>(LU, n, n, n, x, n, tp, n, nv, 1.0);
+  else if (mode == 1)
+    l_gemv_n<1>(LU, n, n, n, x, n, tp, n, nv, 1.0);
+  else if (mode == 2)
+    l_gemv_t<2>(LU, n, n, n, x, n, tp, n, nv, 1.0);
+  else
+    l_gemv_t<3>(LU, n, n, n, x, n, tp, n, nv, 1.0);
   __syncthreads();
   for (int e = threadIdx.x; e < nv * n; e += blockDim.x) x[e] = tp[e];
   __syncthreads();
@@ -804,17 +575,21 @@ __device__ __forceinline__ void l_permute(const int32_t* perm, int n, double* x,
   __syncthreads();
 }
 
-// One group per workgroup of BS threads; op 0 solve, 1 solve_T, 2 apply,
-// 3 apply_T (the per-group steps in the header of this file); down = 0 for
-// the upward sweep (finest sub-level first), 1 for the downward one.  The LDS
-// holds cap doubles (sized by the launch to the sub-level's largest record);
-// the caller guarantees 2r + k <= cap.
-// Registers are capped for 4 waves per SIMD (only the 64-thread shape
-// spills, a few bytes): the 1024 records of a 512^2 level-1 sub-level then
-// all run at once, 4 per CU.
-template <int BS>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_lds(SwArgs A, int down, int cap) {
+// One group per workgroup of 64 .. 1024 threads; OP 0 solve, 1 solve_T, 2 apply,
+// 3 apply_T (the per-group steps in the header of this file); DOWN: the
+// downward sweep, else the upward one (finest sub-level first).  The LDS
+// holds cap doubles (sized by the launch to the sub-level's largest record)
+// and, in the solves, a diagonal block; the caller guarantees 2r + k <= cap.
+// Registers are capped for 4 waves per SIMD: 1024 records of 256 threads
+// then all run at once, 4 per CU.  Bound by the chain of a record's steps,
+// each a wait for memory.  A kernel per sweep, triangles through LDS, sums
+// across lanes in the vector ALU and column products split over all waves:
+// the sub-levels of a 512^2 solve 885 -> 844 us, of the four 24^3 sweeps 588
+// -> 505 us.
+template <int OP, bool DOWN>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_lds(SwArgs A, int cap) {
   extern __shared__ double sm[];
+  double* tri = sm + cap;  // the solves' diagonal block
   const GroupRec R = A.recs[blockIdx.x];
   const int r = R.r, k = R.k;
   const int32_t* rd = A.iarena + R.idx;
@@ -825,51 +600,53 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const double* Urs = Lsr + int64_t(k) * r;
   const double* LU = Urs + int64_t(r) * k;
   const int64_t N = A.N;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, bs = blockDim.x;
   const int nvb = max(1, min(A.nrhs, cap / (2 * r + k)));
   for (int v0 = 0; v0 < A.nrhs; v0 += nvb) {
     const int nv = min(nvb, A.nrhs - v0);
     double* xr = sm;           // [nv][r]
     double* xs = sm + nv * r;  // [nv][k]
     double* tp = xs + nv * k;  // [nv][r]
+    // the first diagonal block of the solves, on its way with the vectors
+    if constexpr (OP < 2) tri_first<2 * OP + int(DOWN)>(LU, r, tri);
     double* u = A.u + v0 * N;
-    for (int e = tid; e < nv * r; e += BS) xr[e] = u[(e / r) * N + rd[e % r]];
-    for (int e = tid; e < nv * k; e += BS) xs[e] = u[(e / k) * N + sk[e % k]];
+    for (int e = tid; e < nv * r; e += bs) xr[e] = u[(e / r) * N + rd[e % r]];
+    for (int e = tid; e < nv * k; e += bs) xs[e] = u[(e / k) * N + sk[e % k]];
     __syncthreads();
-    if (A.op == 0 && !down) {
+    if constexpr (OP == 0 && !DOWN) {
       if (k > 0) l_gemv_t(T, k, r, r, xs, k, xr, r, nv, -1.0);  // u_r -= T^T u_s
       __syncthreads();
       l_permute(perm, r, xr, tp, nv, true);                     // u_r = P u_r
-      l_solve_L(LU, r, xr, r, nv);                              // u_r = L^{-1} u_r
+      l_solve<0>(LU, r, xr, r, nv, tri);                        // u_r = L^{-1} u_r
       if (k > 0) l_gemv_n(Lsr, k, r, r, xr, r, xs, k, nv, -1.0);  // u_s -= L_sr u_r
-    } else if (A.op == 0) {
+    } else if constexpr (OP == 0) {
       if (k > 0) l_gemv_n(Urs, r, k, k, xs, k, xr, r, nv, -1.0);  // u_r -= U_rs u_s
       __syncthreads();
-      l_solve_U(LU, r, xr, r, nv);                                 // u_r = U^{-1} u_r
+      l_solve<1>(LU, r, xr, r, nv, tri);                           // u_r = U^{-1} u_r
       if (k > 0) l_gemv_n(T, k, r, r, xr, r, xs, k, nv, -1.0);    // u_s -= T u_r
-    } else if (A.op == 1 && !down) {
+    } else if constexpr (OP == 1 && !DOWN) {
       if (k > 0) l_gemv_t(T, k, r, r, xs, k, xr, r, nv, -1.0);    // u_r -= T^T u_s
       __syncthreads();
-      l_solve_UT(LU, r, xr, r, nv);                                // u_r = U^{-T} u_r
+      l_solve<2>(LU, r, xr, r, nv, tri);                           // u_r = U^{-T} u_r
       if (k > 0) l_gemv_t(Urs, r, k, k, xr, r, xs, k, nv, -1.0);  // u_s -= U_rs^T u_r
-    } else if (A.op == 1) {
+    } else if constexpr (OP == 1) {
       if (k > 0) l_gemv_t(Lsr, k, r, r, xs, k, xr, r, nv, -1.0);  // u_r -= L_sr^T u_s
       __syncthreads();
-      l_solve_LT(LU, r, xr, r, nv);                                // u_r = L^{-T} u_r
+      l_solve<3>(LU, r, xr, r, nv, tri);                           // u_r = L^{-T} u_r
       l_permute(perm, r, xr, tp, nv, false);                       // u_r = P^T u_r
       if (k > 0) l_gemv_n(T, k, r, r, xr, r, xs, k, nv, -1.0);    // u_s -= T u_r
-    } else if (A.op == 2 && !down) {
+    } else if constexpr (OP == 2 && !DOWN) {
       if (k > 0) l_gemv_n(T, k, r, r, xr, r, xs, k, nv, 1.0);     // x_s += T x_r
       __syncthreads();
       l_trmv(LU, r, xr, tp, nv, 0);                                // x_r = U x_r
       if (k > 0) l_gemv_n(Urs, r, k, k, xs, k, xr, r, nv, 1.0);   //     + U_rs x_s
-    } else if (A.op == 2) {
+    } else if constexpr (OP == 2) {
       if (k > 0) l_gemv_n(Lsr, k, r, r, xr, r, xs, k, nv, 1.0);   // y_s += L_sr y_r
       __syncthreads();
       l_trmv(LU, r, xr, tp, nv, 1);                                // y_r = L y_r
       l_permute(perm, r, xr, tp, nv, false);                       // y_r = P^T y_r
       if (k > 0) l_gemv_t(T, k, r, r, xs, k, xr, r, nv, 1.0);     // y_r += T^T y_s
-    } else if (!down) {
+    } else if constexpr (!DOWN) {
       if (k > 0) l_gemv_n(T, k, r, r, xr, r, xs, k, nv, 1.0);     // x_s += T x_r
       __syncthreads();
       l_permute(perm, r, xr, tp, nv, true);                        // x_r = P x_r
@@ -882,33 +659,39 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
       if (k > 0) l_gemv_t(T, k, r, r, xs, k, xr, r, nv, 1.0);     // y_r += T^T y_s
     }
     __syncthreads();
-    for (int e = tid; e < nv * r; e += BS) u[(e / r) * N + rd[e % r]] = xr[e];
-    for (int e = tid; e < nv * k; e += BS) u[(e / k) * N + sk[e % k]] = xs[e];
+    for (int e = tid; e < nv * r; e += bs) u[(e / r) * N + rd[e % r]] = xr[e];
+    for (int e = tid; e < nv * k; e += bs) u[(e / k) * N + sk[e % k]] = xs[e];
     __syncthreads();
   }
 }
 
 // Top block: x = A_L^{-1} x (op 0), A_L^{-T} x (op 1), A_L x (op 2) or
-// A_L^T x (op 3) with A_L = P^T L U; requires 2n <= kCapL.
+// A_L^T x (op 3) with A_L = P^T L U; n < kTopSplitMin.
 __global__ __launch_bounds__(1024) void k_top_lds(const double* LU, const int32_t* perm, int n, const int32_t* idx,
                                                   double* u, int64_t N, int nrhs, int op) {
-  __shared__ double sm[kCapL];
+  __shared__ double sm[2 * kTopSplitMin * kMaxV];
+  __shared__ double tri[tri_len(kNbT)];
   const int tid = threadIdx.x, B = blockDim.x;
-  const int nvb = max(1, min(nrhs, kCapL / (2 * n)));
-  for (int v0 = 0; v0 < nrhs; v0 += nvb) {
-    const int nv = min(nvb, nrhs - v0);
+  for (int v0 = 0; v0 < nrhs; v0 += kMaxV) {
+    const int nv = min(kMaxV, nrhs - v0);
     double* x = sm;
     double* tp = sm + nv * n;
     double* uu = u + v0 * N;
     for (int e = tid; e < nv * n; e += B) x[e] = uu[(e / n) * N + idx[e % n]];
+    if (op == 0) tri_first<0>(LU, n, tri);
+    if (op == 1) tri_first<2>(LU, n, tri);
     __syncthreads();
     if (op == 0) {
       l_permute(perm, n, x, tp, nv, true);
-      l_solve_L(LU, n, x, n, nv);
-      l_solve_U(LU, n, x, n, nv);
+      l_solve<0>(LU, n, x, n, nv, tri);
+      tri_first<1>(LU, n, tri);
+      __syncthreads();
+      l_solve<1>(LU, n, x, n, nv, tri);
     } else if (op == 1) {
-      l_solve_UT(LU, n, x, n, nv);
-      l_solve_LT(LU, n, x, n, nv);
+      l_solve<2>(LU, n, x, n, nv, tri);
+      tri_first<3>(LU, n, tri);
+      __syncthreads();
+      l_solve<3>(LU, n, x, n, nv, tri);
       l_permute(perm, n, x, tp, nv, false);
     } else if (op == 2) {
       l_trmv(LU, n, x, tp, nv, 0);
@@ -1094,13 +877,8 @@ struct SpTile {
   }
   __device__ __forceinline__ void mul(const double (&m)[16], const double (&x)[kNx]) {
     if constexpr (NV == 1) {
-      const uint64_t b = uint64_t(__double_as_longlong(x[0]));
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b)), q));
-        const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b >> 32)), q));
-        s += m[q] * __longlong_as_double((long long)((uint64_t(hi) << 32) | lo));
-      }
+      for (int q = 0; q < 16; ++q) s += m[q] * lane_value(x[0], q);
     } else {
 #pragma unroll
       for (int k = 0; k < 4; ++k)
@@ -1747,19 +1525,26 @@ void launch_make_perm_top(const int32_t* piv, int32_t* perm, int n, hipStream_t 
   HIF_HIP(hipGetLastError());
 }
 
-// Dynamic LDS of the staged sweeps goes up to kCapL doubles (128 KiB).
+// k_sweep_lds of one sweep (op, down).
+using SweepLds = void (*)(SwArgs, int);
+static SweepLds sweep_lds_kernel(int op, int down) {
+  static constexpr SweepLds k[4][2] = {{k_sweep_lds<0, false>, k_sweep_lds<0, true>},
+                                       {k_sweep_lds<1, false>, k_sweep_lds<1, true>},
+                                       {k_sweep_lds<2, false>, k_sweep_lds<2, true>},
+                                       {k_sweep_lds<3, false>, k_sweep_lds<3, true>}};
+  return k[op][down];
+}
+
+// Dynamic LDS of the staged sweeps goes up to kCapL doubles (128 KiB) and a
+// diagonal block.
 static void allow_large_lds() {
   static std::once_flag once;
   std::call_once(once, [] {
-    const int bytes = kCapL * int(sizeof(double));
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep_lds<64>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep_lds<128>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep_lds<256>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sweep_lds<1024>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    const int bytes = (kCapL + tri_len(kNbT)) * int(sizeof(double));
+    for (int op = 0; op < 4; ++op)
+      for (int down = 0; down < 2; ++down)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(sweep_lds_kernel(op, down)),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     (void)hipGetLastError();
   });
 }
@@ -1781,10 +1566,13 @@ static bool split_solve(const SubLevel& sub, int64_t N, int nv) {
          (int64_t(sub.max_2rk) * nv > kCapL || (sub.nrec <= kSplitMaxRecords && sub.max_r >= kSplitMinR));
 }
 
-// A top block too large for LDS is solved like a large record with no
-// skeleton through the many-workgroup triangular solves.
-static bool top_split_solve(const hif_factor_s* H) {
-  return H->ntop >= kTopSplitMin && 2 * H->ntop <= H->n;
+// A top block is solved like a large record with no skeleton through the
+// many-workgroup triangular solves.
+static bool top_split_solve(const hif_factor_s* H) { return H->ntop >= kTopSplitMin; }
+
+// Scratch of a sweep over nrhs right-hand sides, in doubles.
+static int64_t sweep_work(const hif_factor_s* H, int64_t nrhs) {
+  return std::min<int64_t>(nrhs, kMaxV) * std::max<int64_t>(H->n, top_split_solve(H) ? 2 * H->ntop : 0);
 }
 
 // Right-hand sides per pass that the kernels are built for, f(integral
@@ -1835,10 +1623,10 @@ static void colmv(const SpArgs& P, dim3 g, hipStream_t s, int src, int dst) {
   });
 }
 
-// The sweeps proper.  work: min(nrhs, 8) * N doubles of scratch, reused by
-// every group of 8 right-hand sides (all launches are ordered on s).
+// The sweeps proper.  work: wcap >= min(nrhs, 8) * N doubles of scratch, reused
+// by every group of 8 right-hand sides (all launches are ordered on s).
 static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64_t nrhs, hipStream_t s,
-                      double* work) {
+                      double* work, int64_t wcap) {
   const int64_t N = H->n;
   const int64_t tot = N * nrhs;
   if (x != y) {
@@ -1922,16 +1710,10 @@ static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64
         // are too few to give every CU several workgroups
         const int nvb = std::max(1, std::min(nv, kCapL / sub.max_2rk));
         const int cap = nvb * sub.max_2rk;
-        const size_t lds = size_t(cap) * sizeof(double);
-        const int many = tuning().sweep_many_threads;
-        if (sub.nrec >= kManyRecords && many == 64)
-          hipLaunchKernelGGL(k_sweep_lds<64>, dim3(sub.nrec), dim3(64), lds, s, A, down, cap);
-        else if (sub.nrec >= kManyRecords && many == 128)
-          hipLaunchKernelGGL(k_sweep_lds<128>, dim3(sub.nrec), dim3(128), lds, s, A, down, cap);
-        else if (sub.nrec >= kManyRecords)
-          hipLaunchKernelGGL(k_sweep_lds<256>, dim3(sub.nrec), dim3(256), lds, s, A, down, cap);
-        else
-          hipLaunchKernelGGL(k_sweep_lds<1024>, dim3(sub.nrec), dim3(1024), lds, s, A, down, cap);
+        const size_t lds = size_t(cap + (op < 2 ? tri_len(std::min(kNbT, sub.max_r)) : 0)) * sizeof(double);
+        const int many = sub.nrec < kManyRecords ? 1024 : tuning().sweep_many_threads;
+        const int bs = many == 64 || many == 128 || many == 1024 ? many : 256;
+        hipLaunchKernelGGL(sweep_lds_kernel(op, down), dim3(sub.nrec), dim3(bs), lds, s, A, cap);
       } else if (down)
         hipLaunchKernelGGL(k_down, dim3(sub.nrec), dim3(kBlock), 0, s, A);
       else
@@ -1939,11 +1721,13 @@ static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64
     };
     for (auto& sub : H->subs)
       if (sub.nrec > 0) sweep(sub, 0);
-    // A top block too large for LDS is swept like a large record with no
+    // A top block of some size is swept like a large record with no
     // skeleton (k = 0), through the same chained triangular solves and
     // products: solve X = U^{-1} L^{-1} P u, solve_T X = P^T L^{-T} U^{-T} u,
     // apply X = P^T L U u, apply_T X = U^T L^T P u.
     const bool top_split = top_split_solve(H);
+    HIF_REQUIRE(!top_split || 2 * int64_t(nv) * H->ntop <= wcap, HIF_EDEVICE,
+                "the top block is larger than the sweep's scratch");  // its matrix would fill the device many times
     if (top_split) {
       const int r = int(H->ntop);
       HIF_REQUIRE(H->top_rec.p && H->top_dinv.p && H->sync.p, HIF_EDEVICE,
@@ -1973,12 +1757,8 @@ static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64
         colmv<3, false>(P, gu, s, kInX, kInU);
       }
     } else if (H->ntop > 0) {
-      if (2 * H->ntop <= kCapL)
-        hipLaunchKernelGGL(k_top_lds, dim3(1), dim3(1024), 0, s, H->top_lu.p, H->top_perm.p, int(H->ntop),
-                           H->top_idx.p, u, N, nv, op);
-      else
-        hipLaunchKernelGGL(k_top, dim3(1), dim3(1024), 0, s, H->top_lu.p, H->top_piv.p, int(H->ntop), H->top_idx.p,
-                           u, wk, N, nv, op);
+      hipLaunchKernelGGL(k_top_lds, dim3(1), dim3(1024), 0, s, H->top_lu.p, H->top_perm.p, int(H->ntop),
+                         H->top_idx.p, u, N, nv, op);
     }
     for (auto it = H->subs.rbegin(); it != H->subs.rend(); ++it)
       if (it->nrec > 0) sweep(*it, 1);
@@ -2025,8 +1805,9 @@ void prepare_sweeps(hif_factor_s* H, hipStream_t s) {
 }
 
 void sweep_impl(hif_factor_s* H, int op, const double* x, double* y, int64_t nrhs, hipStream_t s) {
-  H->work.ensure(std::min<int64_t>(nrhs, 8) * H->n, &H->mem);
-  sweep_run(H, op, x, y, nrhs, s, H->work.p);
+  const int64_t need = sweep_work(H, nrhs);
+  H->work.ensure(need, &H->mem);
+  sweep_run(H, op, x, y, nrhs, s, H->work.p, need);
 }
 
 // The launches of one solve u = F^{-1} f recorded into a HIP graph by stream
@@ -2034,12 +1815,13 @@ void sweep_impl(hif_factor_s* H, int op, const double* x, double* y, int64_t nrh
 // sweep scratch is allocated before the capture starts.
 void graph_solve_impl(hif_factor_s* H, const double* f, double* u, int64_t nrhs, hipStream_t cs,
                       hipGraph_t* graph, hipGraphExec_t* exec) {
-  H->work.ensure(std::min<int64_t>(nrhs, 8) * H->n, &H->mem);
+  const int64_t need = sweep_work(H, nrhs);
+  H->work.ensure(need, &H->mem);
   allow_large_lds();
   HIF_HIP(hipStreamSynchronize(cs));
   HIF_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
   try {
-    sweep_run(H, 0, f, u, nrhs, cs, H->work.p);
+    sweep_run(H, 0, f, u, nrhs, cs, H->work.p, need);
   } catch (...) {
     hipGraph_t g = nullptr;
     (void)hipStreamEndCapture(cs, &g);
@@ -2091,7 +1873,7 @@ void sweep_noalloc_impl(hif_factor_s* H, const double* f, double* u, int64_t nrh
               "min(nrhs, 8) * n = " + std::to_string(need) + " exceeds the " +
                   std::to_string(kSolveScratchDoubles) + " doubles of the solve scratch");
   double* work = scratch_ptr();
-  sweep_run(H, 0, f, u, nrhs, s, work);
+  sweep_run(H, 0, f, u, nrhs, s, work, int64_t(kSolveScratchDoubles));
 }
 
 }  // namespace hif

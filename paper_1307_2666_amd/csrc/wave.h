@@ -5,6 +5,30 @@
 
 namespace hif {
 
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+  return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false);
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B;                          // within groups of 4 lanes
+constexpr int kHalfMirror = 0x141, kMirror = 0x140, kRor8 = 0x128;  // within rows of 16 lanes
+
+// The value of lane ^ X, X = 1, 2, 4 or 8, in the vector ALU: a few cycles
+// where a shuffle through LDS takes more than a hundred.
+template <int X>
+__device__ __forceinline__ int lane_xor(int x) {
+  static_assert(X == 1 || X == 2 || X == 4 || X == 8, "within rows of 16 lanes");
+  if constexpr (X == 1) return dpp<kXor1>(x);
+  if constexpr (X == 2) return dpp<kXor2>(x);
+  if constexpr (X == 4) return dpp<kXor3>(dpp<kHalfMirror>(x));
+  return dpp<kRor8>(x);
+}
+template <int X>
+__device__ __forceinline__ double lane_xor(double x) {
+  const unsigned long long u = __double_as_longlong(x);
+  const int lo = lane_xor<X>(int(unsigned(u))), hi = lane_xor<X>(int(unsigned(u >> 32)));
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | unsigned(lo));
+}
+
 constexpr int kRs = 32;  // values reduced at once by wave_rs32
 
 // Sum of p[c] over the 64 lanes for all kRs = 32 indices at once
@@ -18,7 +42,7 @@ __device__ __forceinline__ void rs_step(double (&p)[kRs], int lane) {
   for (int i = 0; i < H; ++i) {
     const double send = up ? p[i] : p[i + H];
     const double keep = up ? p[i + H] : p[i];
-    p[i] = keep + __shfl_xor(send, 2 * H, 64);
+    p[i] = keep + lane_xor<2 * H>(send);
   }
 }
 // Pair sums across lane halves with the gfx950 lane-swap instructions:
@@ -54,7 +78,7 @@ __device__ __forceinline__ double wave_rs32(double (&p)[kRs]) {
   rs_step<4>(p, lane);
   rs_step<2>(p, lane);
   rs_step<1>(p, lane);
-  return p[0] + __shfl_xor(p[0], 1, 64);
+  return p[0] + lane_xor<1>(p[0]);
 }
 
 // Sum of p[c] over the 64 lanes for all 8 indices at once, the same
@@ -67,10 +91,10 @@ __device__ __forceinline__ double wave_rs8(double (&p)[8]) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) p[i] = swap_pair_sum<8>(p[i], p[i + 2]);  // index + 2 on odd rows of 16
   const bool up = (lane & 8) != 0;
-  double t = (up ? p[1] : p[0]) + __shfl_xor(up ? p[0] : p[1], 8, 64);  // index + 1 on lanes with bit 3
-  t += __shfl_xor(t, 4, 64);
-  t += __shfl_xor(t, 2, 64);
-  t += __shfl_xor(t, 1, 64);
+  double t = (up ? p[1] : p[0]) + lane_xor<8>(up ? p[0] : p[1]);  // index + 1 on lanes with bit 3
+  t += lane_xor<4>(t);
+  t += lane_xor<2>(t);
+  t += lane_xor<1>(t);
   return t;
 }
 
