@@ -93,6 +93,7 @@ __global__ __launch_bounds__(kAsmThreads) void k_asm_fill(AsmArgs A) {
   if (r0 >= m + n) return;
   const int r1 = min(r0 + kAsmRows, m + n), nr = r1 - r0;
   double* Y = A.Y + A.yoff[g];
+  const int ldy = y_ld(n);
   double* Acc = A.Acc + A.aoff[g];
   double* Scc = A.Scc + A.aoff[g];
   const int32_t* cols = A.cord + c0;
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(kAsmThreads) void k_asm_fill(AsmArgs A) {
         else
           v = bj * gk * wj;                    // b_j G(|x_p - x_j|) w_j
         v = entry_prec(v, f32);
-        Y[int64_t(r) * n + col] = v;
+        Y[int64_t(r) * ldy + col] = v;
         k2 += v * v;
       }
     }
@@ -193,6 +194,7 @@ __global__ __launch_bounds__(256) void k_asm_finish(AsmArgs A) {
   const int P = A.nproxy;
   const int m = A.sym ? nf + P : 2 * nf + 2 * P;
   double* Y = A.Y + A.yoff[g];
+  const int ldy = y_ld(n);
   double* Acc = A.Acc + A.aoff[g];
   double* Scc = A.Scc + A.aoff[g];
   const int32_t* nfi = A.nf_idx + f0;
@@ -221,10 +223,10 @@ __global__ __launch_bounds__(256) void k_asm_finish(AsmArgs A) {
         if (nfi[mid] < i) lo = mid + 1; else hi = mid;
       }
       if (lo < nf && nfi[lo] == i) {
-        Y[int64_t(lo) * n + col] += sv.y;
+        Y[int64_t(lo) * ldy + col] += sv.y;
         s2 += sv.y * sv.y;
         if (!A.sym) {
-          Y[int64_t(nf + lo) * n + col] += sv.x;
+          Y[int64_t(nf + lo) * ldy + col] += sv.x;
           s2 += sv.x * sv.x;
         }
       }
@@ -1082,11 +1084,11 @@ __device__ void elim_lists(const ElimArgs& A, int g, const ElimView& v) {
 __device__ void elim_gather(const ElimView& v, int part, int nparts) {
   const int B = blockDim.x;
   const int64_t e0 = int64_t(part) * B + threadIdx.x, es = int64_t(nparts) * B;
-  const int r = v.r, k = v.k, n = v.n;
+  const int r = v.r, k = v.k, n = v.n, ldy = y_ld(n);
   for (int64_t e = e0; e < int64_t(k) * r; e += es) {
     const int a = int(e / r), bb = int(e % r);
     const int lo = v.rlo[bb];
-    v.T[e] = (a >= lo && a < v.rhi[bb]) ? v.Y[int64_t(a - lo) * n + v.rdl[bb]] : 0.0;
+    v.T[e] = (a >= lo && a < v.rhi[bb]) ? v.Y[int64_t(a - lo) * ldy + v.rdl[bb]] : 0.0;
   }
   for (int64_t e = e0; e < int64_t(n) * n; e += es) {
     const int i = int(e / n), j = int(e % n);

@@ -567,7 +567,7 @@ __global__ void k_class_tol(int nc, const int32_t* cls_group, const int32_t* cls
     tol[q] = rho * eps;
     const int nf = int(nf_start[g + 1] - nf_start[g]);
     moff[q] = yoff[g] + col0;
-    ld[q] = n;
+    ld[q] = y_ld(n);
     rows[q] = sym ? nf + nproxy : 2 * nf + 2 * nproxy;
     poff[q] = c0 + col0;
   }
@@ -1063,7 +1063,7 @@ void Factorizer::sublevel(int lvl, int kind) {
     const int64_t m = sym ? nf + P : 2 * nf + 2 * P;
     h_yoff[g] = ytot;
     h_aoff[g] = atot;
-    ytot += m * n;
+    ytot += m * y_ld(int(n));
     atot += n * n;
     maxn = std::max<int>(maxn, int(n));
     maxmn = std::max<int>(maxmn, int(m + n));
@@ -1154,8 +1154,24 @@ void Factorizer::sublevel(int lvl, int kind) {
     keep(H->tr_dofs, cord.p, nact);
     keep(H->tr_nfstart, nf_start.p, G + 1);
     keep(H->tr_nf, nf_idx.p, nnf);
-    keep(H->tr_yoff, yoff.p, G);
-    keep(H->tr_Y, Y.p, ytot);
+    // Y without the padding of its rows
+    std::vector<int64_t> h_tr(G);
+    int64_t ttot = 0;
+    auto rows_of = [&](int g) { return sym ? h_nf[g + 1] - h_nf[g] + P : 2 * (h_nf[g + 1] - h_nf[g]) + 2 * P; };
+    for (int g = 0; g < G; ++g) {
+      h_tr[g] = ttot;
+      ttot += rows_of(g) * (h_gstart[g + 1] - h_gstart[g]);
+    }
+    H->tr_yoff.alloc(G, mt);
+    to_dev(H->tr_yoff.p, h_tr, s);
+    H->tr_Y.alloc(ttot, mt);
+    for (int g = 0; g < G; ++g) {
+      const int64_t n = h_gstart[g + 1] - h_gstart[g], m = rows_of(g);
+      if (m * n > 0)
+        HIF_HIP(hipMemcpy2DAsync(H->tr_Y.p + h_tr[g], sizeof(double) * n, Y.p + h_yoff[g],
+                                 sizeof(double) * y_ld(int(n)), sizeof(double) * n, m, hipMemcpyDeviceToDevice, s));
+    }
+    HIF_HIP(hipStreamSynchronize(s));  // h_tr is released on return
     keep(H->tr_aoff, aoff.p, G);
     keep(H->tr_Acc, Acc.p, atot);
     H->traced = true;

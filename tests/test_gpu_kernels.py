@@ -5,6 +5,8 @@ import torch
 
 import paper_1307_2666_amd as hif
 from oracle.idqr import interp_decomp
+from oracle.kernels import Operator
+from workloads import grid_points
 
 from test_gpu_parity import _check_id
 
@@ -169,4 +171,27 @@ def test_sweeps_top_sizes_and_right_hand_sides(n, d, leaf, eps):
             z = x.clone()
             f(z, out=z)  # in place
             assert torch.equal(z, full)
+    F.free()
+
+
+@pytest.mark.parametrize("n", [22, 26, 32])  # cells of 121, 169 and 256 columns: rows as they are, padded, and past 1 KiB
+def test_padded_blocks_as_assembled(n):
+    # A group's block Y with rows padded in memory: the copy handed out has
+    # none, its near-field rows hold the kernel to 12 u of |K| + h^2 / 2 pi
+    # (each side within 6 u), and what is built on it still inverts.
+    pts = grid_points(n, 2)
+    op = Operator.uniform(pts, 1.0 / n)
+    F = hif.factor(torch.tensor(pts, device="cuda:0"), 1e-9, n * n // 4, a=torch.tensor(op.a, device="cuda:0"),
+                   h=1.0 / n, trace_sublevel=0)
+    tr = F.trace()
+    gs, ns = tr["group_start"], tr["near_start"]
+    assert np.all(np.diff(gs) == n * n // 4)
+    u, h2pi = 2.0 ** -53, (1.0 / n) ** 2 / (2 * np.pi)
+    for g in range(gs.size - 1):
+        dofs, near = tr["group_dofs"][gs[g]:gs[g + 1]], tr["near_dofs"][ns[g]:ns[g + 1]]
+        Y = tr["Y"][tr["y_off"][g]:tr["y_off"][g] + near.size * dofs.size].reshape(near.size, dofs.size)
+        K = op.kernel_block(near, dofs)
+        assert np.all(np.abs(Y - K) <= 12 * u * (np.abs(K) + h2pi)), g
+    x = torch.tensor(np.random.default_rng(n).standard_normal((2, n * n)), device="cuda:0")
+    assert (torch.linalg.norm(F.solve(F.apply(x)) - x) / torch.linalg.norm(x)).item() <= 1e-10
     F.free()
