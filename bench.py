@@ -52,8 +52,8 @@ HBM_PEAK_GBS = 8000.0
 # workload (row compression and pivoted QR), from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE runs scaled by what the counters read for a 256 MiB copy kernel
 # (see the profile summaries); None until taken for the kernels as they stand.
-# 267 GB read + 73 GB written per factorization (profiles/hbm_traffic_id_sq512.md).
-ID_STEP_TRAFFIC_BYTES = 340.50e9
+# 111 GB read + 77 GB written per factorization (profiles/hbm_traffic_id_sq512.md).
+ID_STEP_TRAFFIC_BYTES = 188.32e9
 # ALU roof of the exact pair-by-pair product (2D, 8 right-hand sides): its
 # inner loop issues 157 vector instructions for four pairs, 39 per pair (log,
 # distance, 8 FMAs); a
@@ -228,7 +228,7 @@ def id_roofline(st, ph, traffic=None):
     fl, ms = id_flops_ms(st, ph)
     achieved = fl / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
     return {"kernel": "interpolative decompositions: row compression (k_tsqr_*) + column-pivoted QR "
-                      "(k_bq_*, k_id_reg, k_id, k_idm_T_block), all launches of a step",
+                      "(k_pq_*, k_id_reg, k_id, k_idm_T_block), all launches of a step",
             "bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_FP64_TFLOPS, "traffic": traffic, "flops_per_step": fl, "ms_per_step": ms}
 

@@ -99,8 +99,8 @@ typedef struct {
  *                n x n R factor; 0 = pivoted QR directly on Y; -1 = auto
  *                (0 only when Y is nearly square: sum of m n over the
  *                sub-level's problems at most 1.25 times the sum of n^2).
- *                Either way the pivoted QR delays the updates of 32
- *                reflectors; both give the same ID up to rounding.
+ *                Either way the pivoted QR takes blocks of up to 32 pivots;
+ *                both give the same ID up to rounding.
  *  trace_sublevel: -1 (default) = nothing; s >= 0 = keep copies of
  *                sub-level s's groups, near fields and assembled blocks for
  *                hif_trace_get (step-by-step checks; costs memory and time).
@@ -155,15 +155,17 @@ typedef struct {
   double sub_id_flops[HIF_MAX_SUBLEVELS];  /* algorithmic flops of the IDs */
   double sub_elim_flops[HIF_MAX_SUBLEVELS];/* algorithmic flops of the eliminations */
   double sub_t_ms[HIF_MAX_SUBLEVELS][8];   /* per sub-level split of t_phase_ms */
-  double sub_id_bytes[HIF_MAX_SUBLEVELS];  /* pivoted-QR traffic, summed over classes, m' rows
-                                              (m' = min(m, n) after row compression, m on Y):
-                                              blocked kernel: every step i < k reads the trailing
-                                              block, 8 (m' - i)(n - i), and every full block of 32
-                                              reflectors ending at step e < k reads and writes the
-                                              rows below it, 16 (m' - e)(n - e); block held in
-                                              registers: 8 (m' + k) n; one-workgroup streaming
-                                              kernel: every step reads and writes the trailing
-                                              block, 16 (m' - i)(n - i) */
+  double sub_id_bytes[HIF_MAX_SUBLEVELS];  /* traffic of the pivoted QR by columns, summed over classes,
+                                              m' rows (m' = min(m, n) after row compression, m
+                                              on Y): where the blocked path runs, that of a
+                                              blocked Householder QR, every step i < k reading the
+                                              trailing block, 8 (m' - i)(n - i), and every full
+                                              block of 32 reflectors ending at step e < k reading
+                                              and writing the rows below it, 16 (m' - e)(n - e)
+                                              (the path itself reads the trailing block twice per
+                                              32 steps); block held in registers: 8 (m' + k) n;
+                                              one-workgroup streaming kernel: every step reads and
+                                              writes the trailing block, 16 (m' - i)(n - i) */
   double sub_rowqr_flops[HIF_MAX_SUBLEVELS]; /* row compression: 2 m n^2 - 2 n^3 / 3 per class with m > n */
 } hif_stats_t;
 
