@@ -546,6 +546,54 @@ static void launch_apply(const QrBatch& A, int j0, int half, int cbeg, int cend,
                      dim3(64 * NW), 0, s, A, j0, half, cbeg, cend, tpw);
 }
 
+// Waves of a tree node, 64 rows each, for nodes of at most this many rows.
+// Waves with no row would take part in every barrier, sum and product: a stack
+// of 3 chunk factors by 8 waves took 42 us a panel, where a whole chunk of 256
+// rows by 4 took 30.
+template <typename F>
+static void node_waves(int rows, int most, F f) {
+  if (rows <= 128)
+    f(std::integral_constant<int, 2>{});
+  else if (rows <= 256 || most == 4)
+    f(std::integral_constant<int, 4>{});
+  else
+    f(std::integral_constant<int, 8>{});
+}
+
+// The rows of the nodes of each tree level, of a batch whose tallest panel has
+// mp rows: with more than one group of chunks in the tallest, a shorter one may
+// still have a full group.
+struct TreeRows {
+  int nck, ng, rows[3];
+  explicit TreeRows(int mp) : nck(std::max(1, tsqr_chunks(mp))), ng(tsqr_groups(nck)) {
+    rows[0] = std::min(mp, kTsqrRows);
+    rows[1] = std::min(nck, kTsqrFan) * kTb;
+    rows[2] = ng * kTb;
+  }
+  int nodes(int level) const { return level == 0 ? nck : level == 1 ? ng : 1; }
+  bool has(int level) const { return level == 0 || (level == 1 ? nck > 1 : ng > 1); }
+};
+
+template <int LEVEL>
+static void launch_fact(const QrBatch& A, const TreeRows& t, int j0, int half, hipStream_t s) {
+  if (!t.has(LEVEL)) return;
+  node_waves(t.rows[LEVEL], LEVEL == 0 ? 4 : 8, [&](auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    if constexpr (LEVEL > 0 || NW <= 4)
+      hipLaunchKernelGGL((k_tsqr_fact<NW, LEVEL>), dim3(unsigned(t.nodes(LEVEL)), unsigned(A.nprob)), dim3(64 * NW), 0,
+                         s, A, j0, half);
+  });
+}
+
+template <int LEVEL>
+static void launch_apply(const QrBatch& A, const TreeRows& t, int j0, int half, int cbeg, int cend, hipStream_t s) {
+  if (!t.has(LEVEL)) return;
+  node_waves(t.rows[LEVEL], LEVEL == 0 ? 4 : 8, [&](auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    if constexpr (LEVEL > 0 || NW <= 4) launch_apply<NW, LEVEL>(A, j0, half, cbeg, cend, t.nodes(LEVEL), s);
+  });
+}
+
 void launch_tsqr(const QrBatch& A, int max_rows, int max_cols, hipStream_t s) {
   // Look-ahead: panel p is factored on s; its update of the next panel's
   // 32 columns also runs on s, and that of the remaining columns on a
@@ -562,47 +610,45 @@ void launch_tsqr(const QrBatch& A, int max_rows, int max_cols, hipStream_t s) {
   bool rest_pending = false;
   for (int j0 = 0, p = 0; j0 < max_cols; j0 += kTb, ++p) {
     const int half = p & 1;
-    const int nck = std::max(1, tsqr_chunks(max_rows - j0)), ng = tsqr_groups(nck);
-    const unsigned np = unsigned(A.nprob);
+    const TreeRows t(max_rows - j0);
     const int nb0 = j0 + kTb, nb1 = j0 + 2 * kTb;  // next panel: columns [nb0, nb1)
     const bool rest = nb1 < max_cols;
-    hipLaunchKernelGGL((k_tsqr_fact<4, 0>), dim3(unsigned(nck), np), dim3(256), 0, s, A, j0, half);
+    launch_fact<0>(A, t, j0, half, s);
     if (rest) HIF_HIP(hipEventRecord(aux.ev_chunk, s));
-    if (nck > 1) hipLaunchKernelGGL((k_tsqr_fact<8, 1>), dim3(unsigned(ng), np), dim3(512), 0, s, A, j0, half);
-    if (ng > 1) hipLaunchKernelGGL((k_tsqr_fact<8, 2>), dim3(1, np), dim3(512), 0, s, A, j0, half);
+    launch_fact<1>(A, t, j0, half, s);
+    launch_fact<2>(A, t, j0, half, s);
     if (nb0 >= max_cols) break;
     if (rest) HIF_HIP(hipEventRecord(aux.ev_fact, s));
     if (rest_pending) HIF_HIP(hipStreamWaitEvent(s, aux.ev_rest, 0));  // remaining-columns update of p - 1
     rest_pending = false;
     if (rest) {
       HIF_HIP(hipStreamWaitEvent(s2, aux.ev_chunk, 0));
-      launch_apply<4, 0>(A, j0, half, nb1, max_cols, nck, s2);
+      launch_apply<0>(A, t, j0, half, nb1, max_cols, s2);
       HIF_HIP(hipStreamWaitEvent(s2, aux.ev_fact, 0));
-      if (nck > 1) launch_apply<8, 1>(A, j0, half, nb1, max_cols, ng, s2);
-      if (ng > 1) launch_apply<8, 2>(A, j0, half, nb1, max_cols, 1, s2);
+      launch_apply<1>(A, t, j0, half, nb1, max_cols, s2);
+      launch_apply<2>(A, t, j0, half, nb1, max_cols, s2);
       HIF_HIP(hipEventRecord(aux.ev_rest, s2));
       rest_pending = true;
     }
     const int ne = std::min(nb1, max_cols);
-    launch_apply<4, 0>(A, j0, half, nb0, ne, nck, s);
-    if (nck > 1) launch_apply<8, 1>(A, j0, half, nb0, ne, ng, s);
-    if (ng > 1) launch_apply<8, 2>(A, j0, half, nb0, ne, 1, s);
+    launch_apply<0>(A, t, j0, half, nb0, ne, s);
+    launch_apply<1>(A, t, j0, half, nb0, ne, s);
+    launch_apply<2>(A, t, j0, half, nb0, ne, s);
   }
   if (rest_pending) HIF_HIP(hipStreamWaitEvent(s, aux.ev_rest, 0));
   HIF_HIP(hipGetLastError());
 }
 
 void launch_tsqr_panel(const QrBatch& A, int max_rows, int max_trail, hipStream_t s) {
-  const int nck = std::max(1, tsqr_chunks(max_rows)), ng = tsqr_groups(nck);
-  const unsigned np = unsigned(A.nprob);
-  hipLaunchKernelGGL((k_tsqr_fact<4, 0>), dim3(unsigned(nck), np), dim3(256), 0, s, A, 0, 0);
-  if (nck > 1) hipLaunchKernelGGL((k_tsqr_fact<8, 1>), dim3(unsigned(ng), np), dim3(512), 0, s, A, 0, 0);
-  if (ng > 1) hipLaunchKernelGGL((k_tsqr_fact<8, 2>), dim3(1, np), dim3(512), 0, s, A, 0, 0);
+  const TreeRows t(max_rows);
+  launch_fact<0>(A, t, 0, 0, s);
+  launch_fact<1>(A, t, 0, 0, s);
+  launch_fact<2>(A, t, 0, 0, s);
   if (max_trail > 0) {
     // the columns themselves come from each problem's panel; max_trail sizes the grid
-    launch_apply<4, 0>(A, 0, 0, 0, max_trail, nck, s);
-    if (nck > 1) launch_apply<8, 1>(A, 0, 0, 0, max_trail, ng, s);
-    if (ng > 1) launch_apply<8, 2>(A, 0, 0, 0, max_trail, 1, s);
+    launch_apply<0>(A, t, 0, 0, 0, max_trail, s);
+    launch_apply<1>(A, t, 0, 0, 0, max_trail, s);
+    launch_apply<2>(A, t, 0, 0, 0, max_trail, s);
   }
   HIF_HIP(hipGetLastError());
 }

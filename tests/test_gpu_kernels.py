@@ -32,6 +32,23 @@ def test_row_compression_tree_edges(m, n):
         _check_id(Y, tol, True, sk.numpy(), rd.numpy(), T.numpy(), osk, oT)
 
 
+@pytest.mark.parametrize("m,n", [(128, 40), (129, 40),                      # a chunk by 2 waves, by 4
+                                 (1024, 40), (1025, 40), (2048, 40), (2049, 40),  # stacks of 4, 5, 8 and 9 chunk factors
+                                 (16384, 33), (16385, 33)])                    # roots of 4 and 5 groups
+def test_row_compression_node_waves(m, n):
+    # The waves of a tree node follow from the tallest problem of a batch; one
+    # of nearly its height and one of a third share it here.
+    rng = np.random.default_rng(m + n)
+    cases = []
+    for mm in (m, m - 1, m // 3 + n):
+        cases.append(rng.standard_normal((mm, n)) * (10.0 ** (-9.0 * np.arange(n) / n))[rng.permutation(n)])
+    tol = 1e-6
+    out = hif.id_batched([torch.tensor(Y) for Y in cases], [tol] * len(cases))
+    for Y, (sk, rd, T) in zip(cases, out):
+        osk, _, oT = interp_decomp(Y, tol)
+        _check_id(Y, tol, True, sk.numpy(), rd.numpy(), T.numpy(), osk, oT)
+
+
 @pytest.mark.parametrize("sizes", [
     [(64, 64), (65, 65), (16, 16), (17, 3), (1, 1)],       # one panel, a column past it
     [(130, 64), (130, 65), (128, 63), (200, 129)],         # panels that end at, past and short of 64 columns
