@@ -4,19 +4,19 @@
 // the candidates and the problem sizes of each bucket.
 //
 // Medians (ms):
-//   ID, 4096 problems of 33-64 columns: 4 waves 0.851, 8 waves 0.915, 16 waves 1.033
-//   ID, 2048 problems of 97-128 columns: 4 waves 3.013, 8 waves 2.362, 16 waves 2.730
-//   ID, 1024 problems of 161-192 columns: 8 waves 4.344, 16 waves 3.403
-//   LU, 256 blocks of 257-512 rows: 256 threads 3.092, 512 threads 2.959, 1024 threads 3.158
-//   LU, 64 blocks of 513-1024 rows: 512 threads 6.269, 1024 threads 6.340
-//   8-RHS solve of a 384 x 384 factorization: 64 threads 5.562, 128 threads 5.234, 256 threads 5.116
+//   ID, 4096 problems of 33-64 columns: 4 waves 0.846, 8 waves 0.909, 16 waves 1.028
+//   ID, 2048 problems of 97-128 columns: 4 waves 2.986, 8 waves 2.333, 16 waves 2.740
+//   ID, 1024 problems of 161-192 columns: 8 waves 4.296, 16 waves 3.365
+//   LU, 256 blocks of 257-512 rows: 256 threads 1.530, 512 threads 1.553, 1024 threads 1.735
+//   LU, 64 blocks of 513-1024 rows: 512 threads 2.863, 1024 threads 3.238
+//   8-RHS solve of a 384 x 384 factorization: 64 threads 1.463, 128 threads 1.361, 256 threads 1.318
 #pragma once
 
 // waves per problem of the register-resident pivoted QR, problems of at most
 // 64, 128 and 192 columns
 #define HIF_TUNED_ID_REG_WAVES {4, 8, 16}
 // threads of the register-resident LU panel, panels of at most 512 and 1024 rows
-#define HIF_TUNED_LU_PANEL_THREADS {512, 512}
+#define HIF_TUNED_LU_PANEL_THREADS {256, 512}
 // no effect: the row compression's trailing update has one shape
 #define HIF_TUNED_ROWQR_UPDATE_WAVES 8
 #define HIF_TUNED_ROWQR_UPDATE_KIND 1
