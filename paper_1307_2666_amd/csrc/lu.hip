@@ -39,21 +39,24 @@ __device__ __forceinline__ double pick16(const double (&y)[kNb], int j) {
   return r;
 }
 
+// Best candidate of a workgroup of 256 threads (NaN is none); lane reductions
+// in the vector ALU.
 __device__ AM block_argmax256(AM x) {
   __shared__ double sv[4];
   __shared__ int si[4];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    AM y{__shfl_xor(x.v, o, 64), __shfl_xor(x.i, o, 64)};
-    x = am_better(x, y);
+  const double v = fmax(x.v, -1.0), mx = wave_max(v);
+  const int mi = wave_min(v == mx ? x.i : INT_MAX);
+  if (lane == 0) {
+    sv[wv] = mx;
+    si[wv] = mi;
   }
-  if (lane == 0) { sv[wv] = x.v; si[wv] = x.i; }
   __syncthreads();
-  AM r{-1.0, INT_MAX};
-  for (int k = 0; k < 4; ++k) r = am_better(r, AM{sv[k], si[k]});
+  AM r[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) r[k] = AM{sv[k], si[k]};
   __syncthreads();
-  return r;
+  return am_better(am_better(r[0], r[1]), am_better(r[2], r[3]));
 }
 
 // ---------------------------------------------------------------------------
@@ -314,8 +317,18 @@ __global__ __launch_bounds__(256) void k_lum_step(LuBatch A, LuPanelState P, int
   const int tid = threadIdx.x;
   const int64_t cur = int64_t(jj & 1) * A.nprob * P.nblk, nxt = int64_t((jj + 1) & 1) * A.nprob * P.nblk;
   const int nbr = (r - j0 + kLmRows - 1) / kLmRows;  // blocks holding candidate rows
-  AM loc{-1.0, INT_MAX};
-  for (int b = tid; b < nbr; b += 256) loc = am_better(loc, AM{P.pv[cur + q * P.nblk + b], P.pi[cur + q * P.nblk + b]});
+  // the block maxima, and the workgroup's rows, on their way while the pivot is
+  // found: a 6255-unknown block's LU 51.7 ms when they were read after it and the
+  // candidates compared by shuffles, 48.2 so
+  const int64_t c0 = cur + q * P.nblk;
+  AM loc{P.pv[c0 + min(tid, nbr - 1)], P.pi[c0 + min(tid, nbr - 1)]};
+  const int i = rb0 + tid, ic = min(i, n - 1);
+  double* row = M + int64_t(ic) * n + j0;
+  double y[kNb];
+#pragma unroll
+  for (int c = 0; c < kNb; ++c) y[c] = (c >= jj && c < jb) ? row[c] : 0.0;
+  const int done = P.flag[q * P.fstride + (ic - j0)];
+  for (int b = tid + 256; b < nbr; b += 256) loc = am_better(loc, AM{P.pv[c0 + b], P.pi[c0 + b]});
   const AM best = block_argmax256(loc);
   if (!(best.v > 0.0)) {
     if (blk == 0 && tid == 0) atomicOr(A.status, 1);
@@ -326,13 +339,8 @@ __global__ __launch_bounds__(256) void k_lum_step(LuBatch A, LuPanelState P, int
   if (tid < kNb) sp[tid] = tid < jb ? M[int64_t(rp) * n + j0 + tid] : 0.0;
   __syncthreads();
   if (blk == 0 && tid == 0) P.prow[q * kNb + jj] = rp;
-  const int i = rb0 + tid;
   AM nx{-1.0, INT_MAX};
-  if (i < n && i != rp && P.flag[q * P.fstride + (i - j0)] < 0) {
-    double* row = M + int64_t(i) * n + j0;
-    double y[kNb];
-#pragma unroll
-    for (int c = 0; c < kNb; ++c) y[c] = (c >= jj && c < jb) ? row[c] : 0.0;
+  if (i < n && i != rp && done < 0) {
     const double l = pick16(y, jj) / sp[jj];
 #pragma unroll
     for (int c = 0; c < kNb; ++c) {
