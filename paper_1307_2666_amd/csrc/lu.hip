@@ -738,10 +738,11 @@ void launch_lu_batched(const LuBatch& A, int max_r, int max_n, hipStream_t s) {
       else
         hipLaunchKernelGGL(k_lu_panel<1024>, dim3(np), dim3(1024), 0, s, A, J);
     }
-    // every problem has at most max_n columns; its panel may end short of 64
+    // every problem has at most max_n columns; whether one has any outside its
+    // panel does not follow from the maxima (blocks of 64 and of 20 columns, the
+    // second over its first 5: they would be taken for two whole panels)
     const unsigned tiles = unsigned((max_n + kNo - 1) / kNo);
-    if (tiles > 1 || max_r < max_n)
-      hipLaunchKernelGGL(k_lu_swap, dim3(tiles, np), dim3(256), kSwapLds, s, A, J);
+    hipLaunchKernelGGL(k_lu_swap, dim3(tiles, np), dim3(256), kSwapLds, s, A, J);
     const int rem = max_n - J - 1;
     if (rem > 0) {
       const unsigned ut = unsigned((rem + 63) / 64);

@@ -83,6 +83,16 @@ def test_lu_batched_panel_edges(sizes):
         assert np.abs(L[:r]).max() <= 1 + 2 * u
 
 
+@pytest.mark.parametrize("sizes", [
+    [(64, 64), (20, 5)], [(30, 30), (30, 10)], [(16, 16), (17, 3), (17, 17)],  # all columns of one, few of another
+    [(40, 1), (64, 64), (64, 63)], [(2, 1), (2, 2)],
+])
+def test_lu_batched_small_blocks_of_unequal_depth(sizes):
+    # blocks of one panel: the interchanges and U12 of a block eliminated in
+    # part, beside one eliminated whole
+    test_lu_batched_panel_edges(sizes)
+
+
 def test_lu_batched_singular_panel_reports_and_stays_in_bounds():
     # a zero column inside the second panel: the status is set, and the
     # panels after it find only interchanges within the block
