@@ -331,8 +331,14 @@ __global__ __launch_bounds__(256) void k_lum_step(LuBatch A, LuPanelState P, int
   for (int b = tid + 256; b < nbr; b += 256) loc = am_better(loc, AM{P.pv[c0 + b], P.pi[c0 + b]});
   const AM best = block_argmax256(loc);
   if (!(best.v > 0.0)) {
-    if (blk == 0 && tid == 0) atomicOr(A.status, 1);
-    return;  // P.prow stays at the step's own row (k_lum_init)
+    // P.prow stays at the step's own row (k_lum_init); the slot the next step
+    // reads is undefined memory or an earlier step's until it is written
+    if (tid == 0) {
+      P.pv[nxt + q * P.nblk + blk] = -1.0;
+      P.pi[nxt + q * P.nblk + blk] = INT_MAX;
+      if (blk == 0) atomicOr(A.status, 1);
+    }
+    return;
   }
   const int rp = best.i;
   __shared__ double sp[kNb];
@@ -368,7 +374,7 @@ __device__ void lum_perm(const LuPanelState& P, int q, int j0, int jb, int* s_ds
   if (threadIdx.x >= 64) return;
   int dst = lane < jb ? j0 + lane : -1, src = dst, na = jb;
   for (int jj = 0; jj < jb; ++jj) {
-    const int rp = P.prow[q * kNb + jj];
+    const int rp = P.prow[q * kNb + jj];  // a row of the panel: every slot k_lum_step reads has been written
     const unsigned long long hit = __ballot(src == rp);
     int ap;
     if (hit) {

@@ -102,6 +102,24 @@ def test_lu_batched_singular_panel_reports_and_stays_in_bounds():
     assert zero
 
 
+@pytest.mark.parametrize("n,col,value", [(2100, 0, 0.0), (2305, 0, np.nan), (2100, 17, 0.0), (2100, 18, 0.0)])
+def test_lu_batched_tall_singular_panel_reports_and_stays_in_bounds(n, col, value):
+    # a column without a pivot in a panel over many workgroups, the first
+    # column of all among them (nothing is left of an earlier step then): the
+    # status is set, every interchange is one within the block, and the block
+    # beside it is factored as beside a nonsingular one
+    rng = np.random.default_rng(n + col)
+    whole, good = rng.standard_normal((n, n)), rng.standard_normal((2200, 2200))
+    bad = whole.copy()
+    bad[:, col] = value
+    out, pv, zero = hif.lu_batched([torch.tensor(bad), torch.tensor(good)], [600, 600])
+    assert zero
+    assert np.all((pv[0].numpy() >= 0) & (pv[0].numpy() < 600))
+    ref, pvr, zero = hif.lu_batched([torch.tensor(whole), torch.tensor(good)], [600, 600])
+    assert not zero
+    assert torch.equal(out[1], ref[1]) and torch.equal(pv[1], pvr[1])
+
+
 @pytest.mark.parametrize("m,n,decay,tol", [
     (128, 128, 5.0, 1e-3), (140, 129, 12.0, 1e-9),   # one and two chunks; several Gram matrices
     (300, 1024, 9.0, 1e-6), (300, 1025, 9.0, 1e-6),  # the last width with the Cholesky rows in registers
