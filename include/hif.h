@@ -220,7 +220,8 @@ hif_status hif_solve_T(hif_handle h, const double* f, double* u, int64_t nrhs, h
  * (kernel nodes only) and instantiates the graph; hif_graph_launch replays it
  * on a stream, reading f and writing u at the addresses given at capture.
  * f, u: [nrhs][n] device arrays that must stay valid while the graph is used;
- * f == u allowed.  The graph uses the handle's factors and sweep scratch:
+ * f == u allowed.  The graph uses the handle's factors and keeps the sweep
+ * scratch it was recorded with (a later call that needs more takes another):
  * free the graph before the handle, and do not overlap replays (or other
  * sweeps) of one handle on different streams.  hif_solve_graph is
  * host-blocking and allocates the sweep scratch before capturing;

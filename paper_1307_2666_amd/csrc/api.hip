@@ -24,6 +24,7 @@ struct hif_graph_s {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hif_factor_s* h = nullptr;  // the handle whose factors the graph reads
+  std::shared_ptr<hif::DBuf<double>> work;  // the scratch its kernels use
 };
 
 namespace hif {
@@ -578,7 +579,11 @@ hif_status hif_solve_graph(hif_handle h, const double* f, double* u, int64_t nrh
     return fail(HIF_EDEVICE, "creating the capture stream failed");
   std::unique_ptr<hif_graph_s> g(new (std::nothrow) hif_graph_s());
   if (g) g->h = h;
-  hif_status st = g ? guarded(cs, [&] { graph_solve_impl(h, f, u, nrhs, cs, &g->graph, &g->exec); })
+  hif_status st = g ? guarded(cs,
+                              [&] {
+                                graph_solve_impl(h, f, u, nrhs, cs, &g->graph, &g->exec);
+                                g->work = h->work;
+                              })
                     : fail(HIF_ENOMEM, "host allocation failed");
   (void)hipStreamSynchronize(cs);
   dbuf_retire_stream(cs);
@@ -599,6 +604,8 @@ void hif_graph_free(hif_graph g) {
   wait_uses(g->h);  // its replays are recorded on the handle, which outlives the graph
   if (g->exec) (void)hipGraphExecDestroy(g->exec);
   if (g->graph) (void)hipGraphDestroy(g->graph);
+  StreamScope scope(nullptr);
+  ReleaseIdle idle;  // waited on above: its scratch, if no longer the handle's, is idle
   delete g;
 }
 

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -244,8 +245,9 @@ struct hif_factor_s {
   hif::DBuf<int32_t> top_iarena;
   hif::DBuf<int64_t> top_woff;
   hif::DBuf<double> top_dinv;  // its diagonal-block inverses, as SubLevel::dinv
-  // Sweep scratch.
-  hif::DBuf<double> work;
+  // Sweep scratch, grown on use (sweep_scratch); a recorded solve shares it and
+  // keeps the block its kernels were recorded with.
+  std::shared_ptr<hif::DBuf<double>> work = std::make_shared<hif::DBuf<double>>();
   // Ticket counter of the chained triangular solves (sweep.hip), cleared by
   // each pass before use.
   hif::DBuf<uint32_t> sync;

@@ -1804,10 +1804,21 @@ void prepare_sweeps(hif_factor_s* H, hipStream_t s) {
   HIF_HIP(hipGetLastError());
 }
 
+// The handle's scratch, of at least need doubles.  A block that a recorded solve
+// writes to on every replay is left to it, not released to the next allocation.
+static double* sweep_scratch(hif_factor_s* H, int64_t need) {
+  if (H->work.use_count() > 1 && int64_t(H->work->n) < need) {
+    auto w = std::make_shared<DBuf<double>>();
+    w->ensure(need, &H->mem);
+    H->work = std::move(w);
+  }
+  H->work->ensure(need, &H->mem);
+  return H->work->p;
+}
+
 void sweep_impl(hif_factor_s* H, int op, const double* x, double* y, int64_t nrhs, hipStream_t s) {
   const int64_t need = sweep_work(H, nrhs);
-  H->work.ensure(need, &H->mem);
-  sweep_run(H, op, x, y, nrhs, s, H->work.p, need);
+  sweep_run(H, op, x, y, nrhs, s, sweep_scratch(H, need), need);
 }
 
 // The launches of one solve u = F^{-1} f recorded into a HIP graph by stream
@@ -1816,12 +1827,15 @@ void sweep_impl(hif_factor_s* H, int op, const double* x, double* y, int64_t nrh
 void graph_solve_impl(hif_factor_s* H, const double* f, double* u, int64_t nrhs, hipStream_t cs,
                       hipGraph_t* graph, hipGraphExec_t* exec) {
   const int64_t need = sweep_work(H, nrhs);
-  H->work.ensure(need, &H->mem);
+  // a block that is outgrown here is released on cs: sweeps queued on other
+  // streams have to be done with it
+  if (int64_t(H->work->n) < need) wait_uses(H);
+  double* work = sweep_scratch(H, need);
   allow_large_lds();
   HIF_HIP(hipStreamSynchronize(cs));
   HIF_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
   try {
-    sweep_run(H, 0, f, u, nrhs, cs, H->work.p, need);
+    sweep_run(H, 0, f, u, nrhs, cs, work, need);
   } catch (...) {
     hipGraph_t g = nullptr;
     (void)hipStreamEndCapture(cs, &g);

@@ -240,3 +240,40 @@ def test_padded_blocks_as_assembled(n):
     x = torch.tensor(np.random.default_rng(n).standard_normal((2, n * n)), device="cuda:0")
     assert (torch.linalg.norm(F.solve(F.apply(x)) - x) / torch.linalg.norm(x)).item() <= 1e-10
     F.free()
+
+
+@pytest.mark.parametrize("n,d,leaf", [(32, 2, 16), (96, 2, 64), (12, 3, 64)])  # small records, a chained top, one over half
+def test_recorded_solve_keeps_its_scratch(n, d, leaf):
+    # A solve recorded with one right-hand side, then a solve of the same
+    # handle with eight (more scratch than was recorded), another factorization
+    # (which takes what was released) and a second recorded solve: the replays
+    # still give the eager solves, and leave the other factorization alone.
+    rng = np.random.default_rng(n + d)
+    g = (np.arange(n) + 0.5) / n
+    pts = torch.tensor(np.stack(np.meshgrid(*[g] * d, indexing="ij"), -1).reshape(-1, d), device="cuda:0")
+    N = n ** d
+    t = lambda v: torch.tensor(v, device="cuda:0")  # noqa: E731
+    one = torch.ones(N, dtype=torch.float64, device="cuda:0")
+    F = hif.factor(pts, 1e-6, leaf, a=one, h=1.0 / n)
+    f1, f8 = t(rng.standard_normal((1, N))), t(rng.standard_normal((8, N)))
+    u1, u8 = torch.empty_like(f1), torch.empty_like(f8)
+    g1 = F.solve_graph(f1, u1)
+    ref8 = F.solve(f8)
+    g8 = F.solve_graph(f8, u8)
+    G = hif.factor(pts, 1e-6, leaf, a=2.0 * one, h=1.0 / n)
+    other = G.solve(f1)
+    for _ in range(3):
+        f1.copy_(t(rng.standard_normal((1, N))))
+        ref1 = F.solve(f1)
+        want = G.solve(f1)
+        for gr in (g1, g8):
+            gr.launch()
+        torch.cuda.synchronize()
+        assert torch.equal(u1, ref1) and torch.equal(u8, ref8)
+        assert torch.equal(G.solve(f1), want)
+    g1.free()
+    assert torch.equal(F.solve(f8), ref8)
+    g8.free()
+    G.free()
+    F.free()
+    assert torch.isfinite(other).all()
