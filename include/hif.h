@@ -184,7 +184,9 @@ hif_status hif_opts_default(hif_opts* opts);
  *   out:  receives the handle (set to NULL on error).
  * Host-blocking: sizes that depend on the ranks are read back once per
  * sub-level.  Coincident points, non-finite values or points outside the
- * unit box give HIF_EINVAL; a singular B_rr or top block HIF_ESINGULAR.
+ * unit box give HIF_EINVAL; a singular B_rr or top block HIF_ESINGULAR.  A
+ * group whose compressed block has more than 65536 rows and more than 65536
+ * columns gives HIF_EUNSUPPORTED (of one or the other, any number is taken).
  */
 hif_status hif_factor(const double* points, int64_t n, int dim, const hif_kernel* k,
                       const double* a, const double* b, const double* c,

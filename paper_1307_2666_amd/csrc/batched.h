@@ -30,12 +30,14 @@ void launch_rowqr_split(double* base, const std::vector<int64_t>& moff, const st
                         hipStream_t s);
 
 // Communication-avoiding panels of the row compression (tsqr.hip): panel
-// width, rows per chunk, chunk factors per group, and the tallest problem.
+// width, rows per chunk, chunk factors per group, the tallest problem, and the
+// tallest panel its three tree levels take.
 constexpr int kTsqrNb = 32;
 constexpr int kTsqrRows = 256;
 constexpr int kTsqrFan = 16;
 constexpr int kTsqrMaxRows = 32768;
-static_assert(kTsqrMaxRows <= kTsqrRows * kTsqrFan * kTsqrFan, "three tree levels");
+constexpr int kTsqrPanelRows = kTsqrRows * kTsqrFan * kTsqrFan;
+static_assert(kTsqrMaxRows <= kTsqrPanelRows, "three tree levels");
 __host__ __device__ inline int tsqr_chunks(int mp) { return (mp + kTsqrRows - 1) / kTsqrRows; }
 __host__ __device__ inline int tsqr_groups(int nck) { return (nck + kTsqrFan - 1) / kTsqrFan; }
 // Problems of at most kTsqrMaxRows rows.

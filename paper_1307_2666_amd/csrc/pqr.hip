@@ -33,7 +33,7 @@ namespace {
 constexpr int kPb = kTsqrNb;            // steps per block
 constexpr double kPqRefresh = 1e-6;     // of the squared norm
 constexpr int kPqT = 1024;              // threads of the pivot choice
-constexpr int kPqMaxCols = 16 * kPqT;
+constexpr int kPqRegCols = 16 * kPqT;   // columns whose norms and positions fit in its registers
 
 struct PqCtl {
   int k;      // columns factored
@@ -53,6 +53,7 @@ struct PqState {
   double* d;        // [nprob][stride] squared norms, by column of G
   int32_t* pos;     // [nprob][stride] present position of column g of G, -1 once chosen
   double* Rc;       // [nprob][kPb][stride] Cholesky rows of the open block
+  int32_t* key;     // [nprob][stride] original column of column g of G (k_pq_select_wide only)
   int32_t* cp;      // [nprob][stride] original column at each position
   int32_t* sw;      // [nprob][4 kPb + 1] dst, src, count of the block's moves
   double* alpha;    // [nprob][stride] R_ii
@@ -96,6 +97,32 @@ __global__ __launch_bounds__(256) void k_pq_gram(IdArgs A, PqState S) {
   }
 }
 
+// The moves that bring the nb chosen columns to the front, and what the block's
+// other kernels read; the first wave of the pivot choice.
+__device__ __forceinline__ void pq_close(const PqState& S, int q, int k, int n, int nb, int g0, int need, double gmax,
+                                         const int* s_swap) {
+  const int lane = threadIdx.x & 63;
+  PqCtl* C = S.ctl + q;
+  int32_t* sw = S.sw + q * (4 * kPb + 1);
+  __shared__ int s_dst[2 * kPb], s_src[2 * kPb], s_na;
+  compose_swaps(s_swap, k, nb, n, s_dst, s_src, &s_na);
+  __builtin_amdgcn_wave_barrier();
+  if (lane < 2 * kPb && lane < s_na) {
+    sw[lane] = s_dst[lane];
+    sw[2 * kPb + lane] = s_src[lane];
+  }
+  if (lane == 0) {
+    sw[4 * kPb] = s_na;
+    C->nb = nb;
+    C->g0 = g0;
+    C->gram = 0;
+    C->need = need;
+    C->gmax = gmax;
+    S.j0v[q] = k;
+    S.jbv[q] = nb;
+  }
+}
+
 // The pivots of the next block of problem blockIdx.x.  Thread t owns columns
 // t + 1024 u of G (u < U): their squared norms and positions and, with U = 1,
 // their Cholesky rows in registers (in memory otherwise).  One barrier a step:
@@ -106,7 +133,7 @@ template <int U>
 __global__ __launch_bounds__(kPqT) void k_pq_select(IdArgs A, PqState S) {
   constexpr int NW = kPqT / 64;
   const int q = blockIdx.x;
-  PqCtl* C = S.ctl + q;
+  const PqCtl* C = S.ctl + q;
   if (C->done) {
     if (threadIdx.x == 0) S.jbv[q] = 0;
     return;
@@ -243,26 +270,108 @@ __global__ __launch_bounds__(kPqT) void k_pq_select(IdArgs A, PqState S) {
     }
   }
   __syncthreads();
-  if (wv == 0) {
-    int32_t* sw = S.sw + q * (4 * kPb + 1);
-    __shared__ int s_dst[2 * kPb], s_src[2 * kPb], s_na;
-    compose_swaps(s_swap, k, nb, n, s_dst, s_src, &s_na);
-    __builtin_amdgcn_wave_barrier();
-    if (lane < 2 * kPb && lane < s_na) {
-      sw[lane] = s_dst[lane];
-      sw[2 * kPb + lane] = s_src[lane];
-    }
-    if (lane == 0) {
-      sw[4 * kPb] = s_na;
-      C->nb = nb;
-      C->g0 = g0;
-      C->gram = 0;
-      C->need = need;
-      C->gmax = gmax;
-      S.j0v[q] = k;
-      S.jbv[q] = nb;
-    }
+  if (wv == 0) pq_close(S, q, k, n, nb, g0, need, gmax, s_swap);
+}
+
+// The same choice for any number of columns, their norms, positions and Cholesky
+// rows in memory: one pass over them a step, which also finds the best column of
+// the next step.
+__global__ __launch_bounds__(kPqT) void k_pq_select_wide(IdArgs A, PqState S) {
+  constexpr int NW = kPqT / 64;
+  const int q = blockIdx.x;
+  const PqCtl* C = S.ctl + q;
+  if (C->done) {
+    if (threadIdx.x == 0) S.jbv[q] = 0;
+    return;
   }
+  const int n = A.cols[q], m = A.rows[q], ld = A.ld[q];
+  const int k = C->k, fresh = C->gram;
+  const int g0 = fresh ? k : C->g0, ng = n - g0;
+  const double tol = A.tol[q], r00 = C->r00;
+  const int nmax = min(kPb, min(m, n) - k);
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const double* G = S.G + S.goff[q];
+  double* dq = S.d + q * S.stride;
+  int32_t *posq = S.pos + q * S.stride, *keyq = S.key + q * S.stride;
+  double* Rc = S.Rc + q * kPb * S.stride;
+  __shared__ double s_val[2][NW], s_r[2][NW][kPb];
+  __shared__ int s_key[2][NW], s_g[2][NW], s_pos[2][NW], s_occ[kPb], s_swap[kPb];
+  double bv = -1.0;  // this thread's best column
+  int bk = INT_MAX, bg = 0, bp = -1;
+  auto offer = [&](double d, int key, int g, int pos) {
+    const double v = fmax(d, -1.0);  // NaN is never chosen
+    if (v > bv || (v == bv && key < bk)) {
+      bv = v;
+      bk = key;
+      bg = g;
+      bp = pos;
+    }
+  };
+  for (int g = tid; g < ng; g += kPqT) {
+    const int pos = fresh ? g0 + g : posq[g];
+    if (fresh) posq[g] = pos;
+    if (pos < 0) continue;
+    const double d = fresh ? G[int64_t(g) * ld + g] : dq[g];
+    const int key = S.cp[q * S.stride + pos];
+    dq[g] = d;
+    keyq[g] = key;
+    if (pos < k + kPb) s_occ[pos - k] = g;
+    offer(d, key, g, pos);
+  }
+  double gmax = C->gmax;
+  int nb = 0, need = 0;
+  for (int i = 0; i < nmax; ++i) {
+    const int b = i & 1;
+    const double wm = wave_max(bv);
+    const int wk = wave_min(bv == wm ? bk : INT_MAX);
+    if (bv == wm && bk == wk && (wk != INT_MAX || lane == 0)) {
+      s_val[b][wv] = wk == INT_MAX ? -1.0 : wm;
+      s_key[b][wv] = wk;
+      s_g[b][wv] = bg;
+      s_pos[b][wv] = bp;
+#pragma unroll 8
+      for (int l = 0; l < i; ++l) s_r[b][wv][l] = Rc[l * S.stride + bg];
+    }
+    __syncthreads();
+    const double wvl = s_val[b][lane & (NW - 1)];
+    const int wkl = s_key[b][lane & (NW - 1)];
+    const double dp = group_max<NW>(wvl);
+    const int kp = group_min<NW>(wvl == dp ? wkl : INT_MAX);
+    const bool first = i == 0 && fresh;
+    if (first) gmax = dp;
+    if (!(dp > 0.0) || (!first && dp <= kPqRefresh * gmax)) {
+      need = !first;
+      break;
+    }
+    if (sqrt(dp) <= 0.5 * tol * r00) break;
+    const int w = __ffsll(__ballot(wvl == dp && wkl == kp)) - 1;
+    const int p = s_g[b][w], ppos = s_pos[b][w], other = s_occ[i], pt = p >> 6;
+    const double inv = 1.0 / sqrt(dp);
+    bv = -1.0;
+    bk = INT_MAX;
+    for (int g = tid; g < ng; g += kPqT) {
+      double x = (g >> 6) >= pt ? G[int64_t(p) * ld + g] : G[int64_t(g) * ld + p];
+#pragma unroll 8
+      for (int l = 0; l < i; ++l) x -= Rc[l * S.stride + g] * s_r[b][w][l];
+      x *= inv;
+      Rc[i * S.stride + g] = x;
+      int pos = posq[g];
+      if (g == p) {
+        pos = posq[g] = -1;
+      } else if (g == other) {
+        pos = posq[g] = ppos;
+        if (ppos < k + kPb) s_occ[ppos - k] = g;
+      }
+      if (pos < 0) continue;
+      const double d = fmax(dq[g] - x * x, 0.0);
+      dq[g] = d;
+      offer(d, keyq[g], g, pos);
+    }
+    if (tid == 0) s_swap[i] = ppos;
+    nb = i + 1;
+  }
+  __syncthreads();
+  if (wv == 0) pq_close(S, q, k, n, nb, g0, need, gmax, s_swap);
 }
 
 // Moves the chosen columns to the front of the trailing ones, in all rows: a
@@ -391,7 +500,6 @@ __global__ void k_pq_iota(int32_t* p, int n) {
 
 void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t s) {
   if (A0.nprob == 0) return;
-  HIF_REQUIRE(max_cols <= kPqMaxCols, HIF_EUNSUPPORTED, "ID problem with more than 16384 columns");
   // The problems move to a copy whose rows start on 128-byte lines (row stride
   // padded to 16 doubles); only rows 0..k-1 (R11 and T) are copied back.
   const int np = A0.nprob;
@@ -399,10 +507,13 @@ void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
   HIF_HIP(hipMemcpyAsync(hr.data(), A0.rows, sizeof(int32_t) * np, hipMemcpyDeviceToHost, s));
   HIF_HIP(hipMemcpyAsync(hcl.data(), A0.cols, sizeof(int32_t) * np, hipMemcpyDeviceToHost, s));
   HIF_HIP(hipStreamSynchronize(s));
-  const bool tall = max_rows > kTsqrMaxRows;  // than the panels' tree: the R factor has the same ID
-  std::vector<int64_t> off(size_t(4) * np);   // offsets of Z, G and the panels' scratch, and zeros
+  // Problems with more rows than columns and than the row compression's tree
+  // takes: the R factor has the same ID.  What is then left to the panels of the
+  // pivoted QR has at most kTsqrPanelRows rows.
+  const bool tall = max_rows > kTsqrMaxRows;
+  std::vector<int64_t> off(size_t(5) * np);   // offsets of Z, G, the panels' and the tall problems' scratch, and zeros
   std::vector<int32_t> num(size_t(2) * np);   // leading dimensions and rows
-  int64_t zt = 0, gt = 0, st = 0;
+  int64_t zt = 0, gt = 0, st = 0, qt = 0;
   for (int q = 0; q < np; ++q) {
     const int ld = (hcl[q] + 15) & ~15, rows = tall ? std::min(hr[q], hcl[q]) : hr[q];
     num[q] = ld;
@@ -410,13 +521,15 @@ void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
     off[q] = zt;
     off[np + q] = gt;
     off[2 * np + q] = st;
-    off[3 * np + q] = 0;
+    off[3 * np + q] = qt;
+    off[4 * np + q] = 0;
+    if (tall && hr[q] > hcl[q]) qt += rowqr_scratch(hr[q], hcl[q]);
     zt += int64_t(hr[q]) * ld;
     gt += int64_t(hcl[q]) * ld;
     st += tsqr_layout(rows).total;
   }
   IdArgs A = A0;
-  DBuf<double> Z, Gm, scratch, vec;
+  DBuf<double> Z, Gm, scratch, vec, qr;
   DBuf<int64_t> doff;
   DBuf<int32_t> dnum, ints;
   DBuf<PqCtl> ctl;
@@ -431,15 +544,30 @@ void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
   hipLaunchKernelGGL(k_pq_copy, dim3(unsigned((max_rows + 7) / 8), unsigned(np)), dim3(256), 0, s, A0, A);
   A.rows = dnum.p + np;
   if (tall) {
-    launch_rowqr_split(Z.p, std::vector<int64_t>(off.begin(), off.begin() + np),
-                       std::vector<int32_t>(num.begin(), num.begin() + np), hr, hcl, nullptr, s);
+    if (rowqr_split_fits(max_rows, max_cols)) {
+      launch_rowqr_split(Z.p, std::vector<int64_t>(off.begin(), off.begin() + np),
+                         std::vector<int32_t>(num.begin(), num.begin() + np), hr, hcl, nullptr, s);
+    } else if (qt > 0) {  // over 16384 columns
+      qr.alloc(qt, nullptr);
+      QrBatch T{};
+      T.base = Z.p;
+      T.moff = A.moff;
+      T.ld = A.ld;
+      T.rows = A0.rows;
+      T.cols = A.cols;
+      T.scratch = qr.p;
+      T.soff = doff.p + 3 * np;
+      T.nprob = np;
+      launch_qr_batched(T, max_rows, max_cols, s);
+    }
     max_rows = *std::max_element(num.begin() + np, num.end());
   }
+  HIF_REQUIRE(max_rows <= kTsqrPanelRows, HIF_EUNSUPPORTED, "ID problem with more than 65536 rows and columns");
   const int64_t stride = (max_cols + 15) & ~15, tot = stride * np;
   Gm.alloc(gt + 16, nullptr);
   scratch.alloc(st + 1, nullptr);
   vec.alloc(size_t(tot) * (kPb + 2), nullptr);
-  ints.alloc(size_t(tot) * 2 + size_t(np) * (4 * kPb + 3), nullptr);
+  ints.alloc(size_t(tot) * 3 + size_t(np) * (4 * kPb + 3), nullptr);
   ctl.alloc(np, nullptr);
   PqState S{};
   S.G = Gm.p;
@@ -449,7 +577,8 @@ void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
   S.Rc = vec.p + 2 * tot;
   S.pos = ints.p;
   S.cp = ints.p + tot;
-  S.sw = ints.p + 2 * tot;
+  S.key = ints.p + 2 * tot;
+  S.sw = ints.p + 3 * tot;
   S.j0v = S.sw + size_t(np) * (4 * kPb + 1);
   S.jbv = S.j0v + np;
   S.ctl = ctl.p;
@@ -478,8 +607,10 @@ void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
       hipLaunchKernelGGL(k_pq_select<1>, dim3(up), dim3(kPqT), 0, s, A, S);
     else if (max_cols <= 4 * kPqT)
       hipLaunchKernelGGL(k_pq_select<4>, dim3(up), dim3(kPqT), 0, s, A, S);
-    else
+    else if (max_cols <= kPqRegCols)
       hipLaunchKernelGGL(k_pq_select<16>, dim3(up), dim3(kPqT), 0, s, A, S);
+    else
+      hipLaunchKernelGGL(k_pq_select_wide, dim3(up), dim3(kPqT), 0, s, A, S);
     hipLaunchKernelGGL(k_pq_swap, dim3(unsigned((max_rows + 31) / 32), up), dim3(256), 0, s, A, S);
     launch_tsqr_panel(Q, std::max(1, max_rows - kmin), trail, s);
     hipLaunchKernelGGL(k_pq_rank, dim3(up), dim3(64), 0, s, A, S);
@@ -504,7 +635,7 @@ void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
   IdArgs AT = A;
   hipLaunchKernelGGL(k_pq_iota, dim3(unsigned((max_cols + 255) / 256)), dim3(256), 0, s, S.cp, max_cols);
   AT.perm = S.cp;
-  AT.poff = doff.p + 3 * np;
+  AT.poff = doff.p + 4 * np;
   launch_id_T(AT, S.alpha, stride, kmax, max_cols, s);
   hipLaunchKernelGGL(k_pq_out, dim3(unsigned((kmax + 7) / 8 + 1), up), dim3(256), 0, s, A, A0, S);
   launch_id_Tcopy(A0, max_cols, s);

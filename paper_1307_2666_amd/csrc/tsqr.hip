@@ -48,7 +48,7 @@ __device__ __forceinline__ bool panel_geom(const QrBatch& A, int q, int& j0, Pan
   return true;
 }
 __device__ __forceinline__ int part_lo(int i, int total, int parts) {
-  return int(unsigned(i) * unsigned(total) / unsigned(parts));  // total <= 32768 rows, i <= parts <= 128
+  return int(unsigned(i) * unsigned(total) / unsigned(parts));  // total <= 65536 rows, i <= parts <= 256
 }
 
 // LDS of a panel factorization by NW waves.

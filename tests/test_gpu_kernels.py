@@ -277,3 +277,24 @@ def test_recorded_solve_keeps_its_scratch(n, d, leaf):
     G.free()
     F.free()
     assert torch.isfinite(other).all()
+
+
+def test_group_of_more_columns_than_the_pivot_choice_holds():
+    # One leaf of 128 x 129 = 16512 points beside three of 16: its ID has more
+    # columns than the pivot choice keeps in registers, and few rows.  A is the
+    # identity plus a small integral operator, so apply error and solve
+    # residual against the exact product are within 10 eps.
+    eps, h = 1e-6, 0.5 / 129
+    big = np.stack(np.meshgrid((np.arange(128) + 0.5) * h, (np.arange(129) + 0.5) * h, indexing="ij"), -1).reshape(-1, 2)
+    few = np.stack(np.meshgrid(*[(np.arange(4) + 0.5) / 8] * 2, indexing="ij"), -1).reshape(-1, 2)
+    pts = np.concatenate([big] + [few + np.array(o) for o in ((0.5, 0.0), (0.0, 0.5), (0.5, 0.5))])
+    P = torch.tensor(pts, device="cuda:0")
+    a = torch.ones(pts.shape[0], dtype=torch.float64, device="cuda:0")
+    F = hif.factor(P, eps, 16512, a=a, h=h)
+    st = F.stats()
+    assert st["top_size"] < 1000
+    x = torch.tensor(np.random.default_rng(6).standard_normal((2, pts.shape[0])), device="cuda:0")
+    rel = lambda v, w: (torch.linalg.norm(v - w, dim=1) / torch.linalg.norm(w, dim=1)).max().item()  # noqa: E731
+    assert rel(F.apply(x), hif.matvec(P, x, a=a, h=h)) <= 10 * eps
+    assert rel(hif.matvec(P, F.solve(x), a=a, h=h), x) <= 10 * eps
+    F.free()
