@@ -93,6 +93,10 @@ typedef struct {
  *  n_proxy:      proxy points, 0 = 64 (2D circle) / 512 (3D sphere) (Section 3.3).
  *  proxy_radius: proxy radius in units of the cell width, 0 = 1.5 (Section 3.3).
  *  max_bytes:    cap on device memory the factorization may hold, 0 = none.
+ *                Not counted: while the IDs of at most 512 blocks of 128
+ *                columns or more run, a copy of each block (min(m, n) x n, or
+ *                m x n without row compression) and an n x n matrix, of fewer
+ *                blocks at a time where the device has no room for all.
  *  row_compression: how the IDs of a sub-level with few large problems run
  *                (Section 2.2 leaves the QR organization open):
  *                1 = Householder QR of Y first, then the pivoted QR of its

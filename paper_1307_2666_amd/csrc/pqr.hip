@@ -498,8 +498,8 @@ __global__ void k_pq_iota(int32_t* p, int n) {
 
 }  // namespace
 
-void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t s) {
-  if (A0.nprob == 0) return;
+// All problems of A0 together.  Every allocation comes before the first output.
+static void id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t s) {
   // The problems move to a copy whose rows start on 128-byte lines (row stride
   // padded to 16 doubles); only rows 0..k-1 (R11 and T) are copied back.
   const int np = A0.nprob;
@@ -641,6 +641,32 @@ void launch_id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
   launch_id_Tcopy(A0, max_cols, s);
   HIF_HIP(hipGetLastError());
   HIF_HIP(hipStreamSynchronize(s));  // the working copy is released on return
+}
+
+void launch_id_blocked(const IdArgs& A, int max_rows, int max_cols, hipStream_t s) {
+  if (A.nprob == 0) return;
+  // A Gram matrix takes n x n doubles beside the copy of the problem: where the
+  // device does not hold those of all problems, half of them at a time.
+  try {
+    id_blocked(A, max_rows, max_cols, s);
+    return;
+  } catch (const Error& e) {
+    if (e.status != HIF_ENOMEM || A.nprob == 1) throw;
+  }
+  const int h = A.nprob / 2;
+  for (int q0 : {0, h}) {
+    IdArgs P = A;
+    P.moff += q0;
+    P.ld += q0;
+    P.rows += q0;
+    P.cols += q0;
+    P.tol += q0;
+    P.rank += q0;
+    P.poff += q0;
+    if (P.toff) P.toff += q0;
+    P.nprob = q0 ? A.nprob - h : h;
+    launch_id_blocked(P, max_rows, max_cols, s);
+  }
 }
 
 bool id_blocked_fits(int nprob, int max_rows, int max_cols) {

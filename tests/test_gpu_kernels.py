@@ -1,4 +1,7 @@
 """GPU kernels at the sizes where their tiling and dispatch change, against the oracle."""
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -298,3 +301,43 @@ def test_group_of_more_columns_than_the_pivot_choice_holds():
     assert rel(F.apply(x), hif.matvec(P, x, a=a, h=h)) <= 10 * eps
     assert rel(hif.matvec(P, F.solve(x), a=a, h=h), x) <= 10 * eps
     F.free()
+
+
+_SCARCE = """
+import sys
+import numpy as np, torch
+import paper_1307_2666_amd as hif
+rng = np.random.default_rng(2)
+cols = lambda n: (10.0 ** (-6.0 * np.arange(n) / n))[rng.permutation(n)]
+hif.id_batched([torch.tensor(rng.standard_normal((100, 130)))], [1e-3])  # the library's code on the device
+mats = [torch.tensor(rng.standard_normal((500, 4096)) * cols(4096)) for _ in range(int(sys.argv[1]))]
+tols = [1e-3] * len(mats)
+new = lambda mib: torch.empty(mib << 20, dtype=torch.uint8, device="cuda")
+keep = new(2048)  # for the call's own tensors
+rest = [new((torch.cuda.mem_get_info()[0] >> 20) - 4096)]
+while True:  # what the device really has left
+    try:
+        rest.append(new(256))
+    except torch.OutOfMemoryError:
+        break
+print("blocks", len(rest), flush=True)
+del rest[1:5]
+torch.cuda.empty_cache()
+del keep
+few = hif.id_batched(mats, tols)
+del rest
+torch.cuda.empty_cache()
+many = hif.id_batched(mats, tols)
+for x, y in zip(few, many):
+    assert all(torch.equal(p, q) for p, q in zip(x, y)) and x[0].numel() > 32
+print("equal", len(few))
+"""
+
+
+@pytest.mark.parametrize("count", [8, 9])
+def test_blocked_pivoted_qr_where_memory_is_short(count):
+    # 1 GiB of device memory left for 8 or 9 Gram matrices of 128 MiB and their
+    # problems: they go through in parts, with the results of all together.  A
+    # process of its own, whose allocator holds no blocks of earlier calls.
+    r = subprocess.run([sys.executable, "-c", _SCARCE, str(count)], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and f"equal {count}" in r.stdout, r.stdout + r.stderr
