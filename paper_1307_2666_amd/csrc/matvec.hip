@@ -59,7 +59,8 @@ __device__ __forceinline__ double log_pos(double x, const LogCoef& L) {
 
 // G(r) without its constant factor from the squared distance: log r^2 (2D) or
 // 1 / r (3D).  1 / r: the hardware's estimate (2^-24 or better) and one
-// third-order step; r = 0 keeps the estimate's infinity.
+// third-order step; where r^2 is zero or overflows (their product is 0 times
+// infinity) the estimate stands.
 template <int D>
 struct Green;
 template <>
@@ -72,10 +73,10 @@ template <>
 struct Green<3> {
   static constexpr double factor = kInv4Pi;
   __device__ __forceinline__ double operator()(double r2) const {
-    const double y = __builtin_amdgcn_rsq(r2);
-    const double e = fma(-r2 * y, y, 1.0);
+    const double y = __builtin_amdgcn_rsq(r2), r = r2 * y;
+    const double e = fma(-r, y, 1.0);
     const double v = fma(y * e, fma(e, 0.375, 0.5), y);
-    return r2 > 0.0 ? v : y;
+    return r == r ? v : y;
   }
 };
 
@@ -124,8 +125,10 @@ __global__ __launch_bounds__(64 * NW) void k_matvec(const double* __restrict__ p
 #pragma unroll
       for (int v = 0; v < NR; ++v) src[D + v] = wc * x[v * ldx + j];
     } else {
+      // Weight 0, anywhere: in 2D G is finite also at a target; in 3D the pair
+      // is dropped below.
 #pragma unroll
-      for (int k = 0; k < D; ++k) src[k] = 2.0 + k;  // far away, weight 0
+      for (int k = 0; k < D; ++k) src[k] = 2.0 + k;
 #pragma unroll
       for (int v = 0; v < NR; ++v) src[D + v] = 0.0;
     }
@@ -137,7 +140,9 @@ __global__ __launch_bounds__(64 * NW) void k_matvec(const double* __restrict__ p
     for (int k = 0; k < D + NR; ++k) st[wv][lane][k] = src[k];
     if (j0 + 64 * NW < n) fetch(j0 + 64 * NW);
     __builtin_amdgcn_wave_barrier();
-    auto pass = [&](auto self_tile) {
+    const int cnt = int(n - j0 < 64 ? n - j0 : 64);  // sources of the tile
+    const int self0 = int(i0 - j0 > -4096 ? i0 - j0 : -4096);  // of the tile's first source; any far off will do
+    auto pass = [&](auto some_dropped) {
 #pragma unroll 2
       for (int t = 0; t < 64; t += SPL) {
         double s[WS];
@@ -157,10 +162,11 @@ __global__ __launch_bounds__(64 * NW) void k_matvec(const double* __restrict__ p
             r2 = k == 0 ? dd * dd : fma(dd, dd, r2);
           }
           double g;
-          if constexpr (decltype(self_tile)::value) {  // the self pair is dropped by a select
-            const bool self = j0 + t + sl == i0 + u * L + tl;
-            g = green(self ? 1.0 : r2);
-            g = self ? 0.0 : g;
+          if constexpr (decltype(some_dropped)::value) {  // by a select: the self pair, in 3D also what is past n
+            bool drop = j0 + t + sl == i0 + u * L + tl;
+            if constexpr (D == 3) drop = t + sl == self0 + u * L + tl || t + sl >= cnt;
+            g = green(drop ? 1.0 : r2);
+            g = drop ? 0.0 : g;
           } else {
             g = green(r2);
           }
@@ -169,7 +175,7 @@ __global__ __launch_bounds__(64 * NW) void k_matvec(const double* __restrict__ p
         }
       }
     };
-    if (j0 < i0 + L * TPT && j0 + 64 > i0)
+    if ((j0 < i0 + L * TPT && j0 + 64 > i0) || (D == 3 && cnt < 64))
       pass(std::true_type{});
     else
       pass(std::false_type{});

@@ -188,6 +188,31 @@ def test_matvec_sizes_and_right_hand_sides(d, n, nrhs):
         assert np.all(np.abs(y[:, i] - ref) <= (2 * n * u + 16 * u) * mag)
 
 
+@pytest.mark.parametrize("n", [3, 64, 65, 40000])  # one, both and neither of the splits' last tiles full
+@pytest.mark.parametrize("d", [2, 3])
+def test_matvec_points_outside_the_unit_box(d, n):
+    # The product checks no coordinates: points anywhere give the formula's
+    # sum, at (2, 3) and (2, 3, 4) as elsewhere, and in 3D a pair whose squared
+    # distance overflows counts as infinitely far.  Tolerance of
+    # test_matvec_sizes_and_right_hand_sides, all weights one.
+    gen = np.random.default_rng(n + d)
+    pts = gen.random((n, d))
+    pts[0] = 2.0 + np.arange(d)
+    if d == 3:
+        pts[1] = (1e200, 0.5, 0.5)
+    x = gen.standard_normal((2, n))
+    t = lambda v: torch.tensor(v, device="cuda:0")  # noqa: E731
+    y = hif.matvec(t(pts), t(x), weights=t(np.ones(n)), selfk=t(np.ones(n))).cpu().numpy()
+    u = np.finfo(float).eps / 2
+    for i in {0, 1, 2, n - 1}:
+        with np.errstate(over="ignore"):
+            r = np.sqrt(((pts[i] - pts) ** 2).sum(1))
+        r[i] = 1.0
+        K = -np.log(r) / (2 * np.pi) if d == 2 else 1.0 / (4 * np.pi * r)
+        K[i] = 1.0
+        assert np.all(np.abs(y[:, i] - (K * x).sum(1)) <= (2 * n * u + 16 * u) * (np.maximum(np.abs(K), 1e-3) * np.abs(x)).sum(1))
+
+
 @pytest.mark.parametrize("n,d,leaf,eps", [(16, 2, 64, 1e-9), (28, 2, 64, 1e-9), (40, 2, 16, 1e-9), (64, 2, 64, 1e-10),
                                           (12, 3, 64, 1e-6), (20, 3, 64, 1e-6)])
 def test_sweeps_top_sizes_and_right_hand_sides(n, d, leaf, eps):
