@@ -465,6 +465,11 @@ __device__ __forceinline__ void l_solve(const double* __restrict__ LU, int n, do
   const int nblk = (n + kNbT - 1) / kNbT;
   for (int jb = 0; jb < nblk; ++jb) {
     const int j0 = (kFwd ? jb : nblk - 1 - jb) * kNbT, nb = min(kNbT, n - j0), row = min(lane, nb - 1);
+    double d = 1.0, di = 1.0;
+    if constexpr (kUp) {
+      d = tri[tri_at<true>(nb, row, row)];
+      di = 1.0 / d;
+    }
     // a wave takes right-hand sides v and v + nw together: one read of each
     // entry of the triangle for both
     for (int v = wv; v < nv; v += 2 * nw) {
@@ -472,11 +477,6 @@ __device__ __forceinline__ void l_solve(const double* __restrict__ LU, int n, do
         constexpr bool TWO = decltype(two_c)::value;
         double xi = x[v * xs + j0 + row], xj = TWO ? x[(v + nw) * xs + j0 + row] : 0.0;
         // a quotient is a product with the reciprocal and one correction
-        double d = 1.0, di = 1.0;
-        if constexpr (kUp) {
-          d = tri[tri_at<true>(nb, row, row)];
-          di = 1.0 / d;
-        }
         auto quot = [&](double b) {
           const double q = b * di;
           return __builtin_fma(__builtin_fma(-q, d, b), di, q);
@@ -514,15 +514,35 @@ __device__ __forceinline__ void l_solve(const double* __restrict__ LU, int n, do
               }
             }
         }
+        if constexpr (kUp) {
+          // Not so where the reciprocal is no normal number or its product with
+          // an entry is infinite (the correction then makes NaN): those blocks
+          // are done again.
+          const bool fine = __builtin_amdgcn_class(di, 0x108) && __builtin_fabs(xi) < __builtin_inf() &&
+                            (!TWO || __builtin_fabs(xj) < __builtin_inf());
+          if (!__all(fine)) return false;
+        }
         if (lane < nb) {
           x[v * xs + j0 + lane] = xi;
           if constexpr (TWO) x[(v + nw) * xs + j0 + lane] = xj;
         }
+        return true;
       };
-      if (v + nw < nv)
-        pass(std::true_type{});
-      else
-        pass(std::false_type{});
+      if (v + nw < nv ? pass(std::true_type{}) : pass(std::false_type{})) [[likely]]
+        continue;
+      if constexpr (kUp)
+        for (int w = v; w < min(nv, v + 2 * nw); w += nw) {  // by divisions
+          double xi = x[w * xs + j0 + row];
+#pragma clang loop unroll(disable)
+          for (int u = 0; u < nb; ++u) {
+            const int c = kFwd ? u : nb - 1 - u;
+            const double m = tri[kFwd ? tri_at<true>(nb, c, max(row, c)) : tri_at<true>(nb, min(row, c), c)];
+            if (lane == c) xi = xi / d;
+            const double xc = lane_value(xi, c);
+            if (kFwd ? lane > c : lane < c) xi -= m * xc;
+          }
+          if (lane < nb) x[w * xs + j0 + lane] = xi;
+        }
     }
     __syncthreads();
     if (jb + 1 < nblk) {

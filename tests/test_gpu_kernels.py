@@ -307,6 +307,42 @@ def test_recorded_solve_keeps_its_scratch(n, d, leaf):
     assert torch.isfinite(other).all()
 
 
+@pytest.mark.parametrize("a,f,u", [
+    (3.0, 1.0, 1.0 / 3.0), (2.0, np.inf, np.inf), (-2.0, np.inf, -np.inf), (1e-10, 1e308, np.inf),
+    (3e-310, 1e-310, 1e-310 / 3e-310), (-3e-310, 0.0, 0.0), (1.7e308, 1e308, 1e308 / 1.7e308), (3.0, -np.inf, -np.inf),
+])
+def test_small_solves_divide_as_division_does(a, f, u):
+    # One unknown with A = a: the quotient at the ends of the range, where a
+    # product with the reciprocal would give NaN, in both solves and for each
+    # number of right-hand sides a wave takes.
+    t = lambda v: torch.tensor(v, dtype=torch.float64, device="cuda:0")  # noqa: E731
+    F = hif.factor(t([[0.5, 0.5]]), 1e-6, 1, a=t([a]), weights=t([0.0]), selfk=t([0.0]))
+    for nrhs in (1, 3, 8):
+        x = torch.full((nrhs, 1), f, dtype=torch.float64, device="cuda:0")
+        for y in (F.solve(x), F.solve_T(x)):
+            assert y.cpu().numpy().ravel().tolist() == [u] * nrhs
+    F.free()
+
+
+@pytest.mark.parametrize("n", [8, 11])  # one diagonal block of 64, two
+def test_small_solves_beside_a_subnormal_pivot(n):
+    # A dense diagonal block (one leaf, no levels, no weights) whose last entry
+    # is subnormal: each unknown is its quotient, within the two roundings of a
+    # corrected product with the reciprocal.
+    N = n * n
+    rng = np.random.default_rng(n)
+    a = 1.0 + rng.random(N)
+    a[-1] = 3e-310
+    f = rng.standard_normal((5, N))
+    f[:, -1] *= 1e-310
+    t = lambda v: torch.tensor(v, device="cuda:0")  # noqa: E731
+    zero = t(np.zeros(N))
+    F = hif.factor(t(grid_points(n, 2)), 1e-6, N, a=t(a), weights=zero, selfk=zero)
+    for y in (F.solve(t(f)), F.solve_T(t(f))):
+        assert np.all(np.abs(y.cpu().numpy() - f / a) <= 2 * np.finfo(float).eps * np.abs(f / a))
+    F.free()
+
+
 def test_group_of_more_columns_than_the_pivot_choice_holds():
     # One leaf of 128 x 129 = 16512 points beside three of 16: its ID has more
     # columns than the pivot choice keeps in registers, and few rows.  A is the
