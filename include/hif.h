@@ -93,6 +93,9 @@ typedef struct {
  *  n_proxy:      proxy points, 0 = 64 (2D circle) / 512 (3D sphere) (Section 3.3).
  *  proxy_radius: proxy radius in units of the cell width, 0 = 1.5 (Section 3.3).
  *  max_bytes:    cap on device memory the factorization may hold, 0 = none.
+ *                The solves of a top block of 128 unknowns or more keep about
+ *                1 KiB per unknown of it beside the factors where the cap has
+ *                room, and take one workgroup where it has not.
  *                Not counted: while the IDs of at most 512 blocks of 128
  *                columns or more run, a copy of each block (min(m, n) x n, or
  *                m x n without row compression) and an n x n matrix, of fewer
@@ -200,9 +203,10 @@ hif_status hif_factor(const double* points, int64_t n, int dim, const hif_kernel
 /*
  * The four factored sweeps.  x, y (f, u): [nrhs][n] device, caller's point
  * order, nrhs >= 1; in place (x == y) allowed.  Stream-ordered and
- * asynchronous; the first call of a handle may allocate sweep scratch
- * (nrhs * n doubles, kept until hif_free).  HIF_EINVAL on a NULL handle or
- * vector or nrhs < 1.
+ * asynchronous; a call of a handle may allocate sweep scratch, kept until
+ * hif_free: min(nrhs, 8) * n doubles, or where the top block is more than
+ * half of the unknowns up to twice that, if max_bytes leaves room.  HIF_EINVAL
+ * on a NULL handle or vector or nrhs < 1.
  */
 /* y = F x (generalized FMM; eqn hifie2/hifie3 first line: the product of the
  * factors U_l^{-*}, D, V_l^{-1} of Lemma 2.4 / eqn rskelf). */

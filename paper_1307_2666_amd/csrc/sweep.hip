@@ -727,6 +727,30 @@ __global__ __launch_bounds__(1024) void k_top_lds(const double* LU, const int32_
   }
 }
 
+// The same for a top block of any size, on the vectors where they stand (two of
+// them with the scratch): one workgroup, for handles whose memory cap left no
+// room for what the many-workgroup solves keep.
+__global__ __launch_bounds__(1024) void k_top(const double* LU, const int32_t* piv, int n, const int32_t* idx, double* u,
+                                              double* work, int64_t N, int nrhs, int op) {
+  if (op == 0) {
+    swaps_fwd(piv, n, idx, u, N, nrhs);
+    solve_L(LU, n, idx, u, N, nrhs);
+    solve_U(LU, n, idx, u, N, nrhs);
+  } else if (op == 1) {
+    solve_UT(LU, n, idx, u, N, nrhs);
+    solve_LT(LU, n, idx, u, N, nrhs);
+    swaps_rev(piv, n, idx, u, N, nrhs);
+  } else if (op == 2) {
+    tri_mul(LU, n, idx, u, work, N, nrhs, 0);
+    tri_mul(LU, n, idx, u, work, N, nrhs, 1);
+    swaps_rev(piv, n, idx, u, N, nrhs);
+  } else {
+    swaps_fwd(piv, n, idx, u, N, nrhs);
+    tri_mul(LU, n, idx, u, work, N, nrhs, 2);
+    tri_mul(LU, n, idx, u, work, N, nrhs, 3);
+  }
+}
+
 // Gather form of the row interchanges j <-> piv[j], j = 0..n-1 (in order).
 constexpr int kPermLds = 8192;
 __device__ void make_perm(const int32_t* piv, int32_t* perm, int n) {
@@ -1586,11 +1610,14 @@ static bool split_solve(const SubLevel& sub, int64_t N, int nv) {
          (int64_t(sub.max_2rk) * nv > kCapL || (sub.nrec <= kSplitMaxRecords && sub.max_r >= kSplitMinR));
 }
 
-// A top block is solved like a large record with no skeleton through the
-// many-workgroup triangular solves.
-static bool top_split_solve(const hif_factor_s* H) { return H->ntop >= kTopSplitMin; }
+// A top block of some size is solved like a large record with no skeleton
+// through the many-workgroup triangular solves, if its solve record was built.
+static bool top_split_solve(const hif_factor_s* H) { return H->top_dinv.p != nullptr; }
 
-// Scratch of a sweep over nrhs right-hand sides, in doubles.
+// Scratch of a sweep over nrhs right-hand sides, in doubles: what it needs, and
+// what it takes where there is that much (two vectors of a top block of more
+// than half of the unknowns).
+static int64_t sweep_work_min(const hif_factor_s* H, int64_t nrhs) { return std::min<int64_t>(nrhs, kMaxV) * H->n; }
 static int64_t sweep_work(const hif_factor_s* H, int64_t nrhs) {
   return std::min<int64_t>(nrhs, kMaxV) * std::max<int64_t>(H->n, top_split_solve(H) ? 2 * H->ntop : 0);
 }
@@ -1643,7 +1670,7 @@ static void colmv(const SpArgs& P, dim3 g, hipStream_t s, int src, int dst) {
   });
 }
 
-// The sweeps proper.  work: wcap >= min(nrhs, 8) * N doubles of scratch, reused
+// The sweeps proper.  work: wcap >= sweep_work_min doubles of scratch, reused
 // by every group of 8 right-hand sides (all launches are ordered on s).
 static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64_t nrhs, hipStream_t s,
                       double* work, int64_t wcap) {
@@ -1745,13 +1772,8 @@ static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64
     // skeleton (k = 0), through the same chained triangular solves and
     // products: solve X = U^{-1} L^{-1} P u, solve_T X = P^T L^{-T} U^{-T} u,
     // apply X = P^T L U u, apply_T X = U^T L^T P u.
-    const bool top_split = top_split_solve(H);
-    HIF_REQUIRE(!top_split || 2 * int64_t(nv) * H->ntop <= wcap, HIF_EDEVICE,
-                "the top block is larger than the sweep's scratch");  // its matrix would fill the device many times
-    if (top_split) {
+    if (top_split_solve(H) && 2 * int64_t(nv) * H->ntop <= wcap) {
       const int r = int(H->ntop);
-      HIF_REQUIRE(H->top_rec.p && H->top_dinv.p && H->sync.p, HIF_EDEVICE,
-                  "the top block's solve record was not built with the factors");
       const int nbk = (r + kNbT - 1) / kNbT;
       SpArgs P{H->top_rec.p, H->top_iarena.p, H->top_lu.p,  H->top_woff.p, u, wk, wk + int64_t(nv) * r, N, nv,
                H->top_dinv.p, nbk};
@@ -1776,6 +1798,9 @@ static void sweep_run(hif_factor_s* H, int op, const double* x, double* y, int64
         colmv<2, false>(P, gu, s, kInPu, kInX);
         colmv<3, false>(P, gu, s, kInX, kInU);
       }
+    } else if (H->ntop >= kTopSplitMin) {
+      hipLaunchKernelGGL(k_top, dim3(1), dim3(1024), 0, s, H->top_lu.p, H->top_piv.p, int(H->ntop), H->top_idx.p, u, wk,
+                         N, nv, op);
     } else if (H->ntop > 0) {
       hipLaunchKernelGGL(k_top_lds, dim3(1), dim3(1024), 0, s, H->top_lu.p, H->top_perm.p, int(H->ntop),
                          H->top_idx.p, u, N, nv, op);
@@ -1805,40 +1830,66 @@ static void build_dinv(hif_factor_s* H, hipStream_t s) {
 
 void prepare_sweeps(hif_factor_s* H, hipStream_t s) {
   build_dinv(H, s);
+  // the top block's solve record, where the memory cap has room for it
+  const int r = int(H->ntop), nbk = (r + kNbT - 1) / kNbT;
+  if (H->ntop >= kTopSplitMin && !H->top_dinv.p) {
+    try {
+      H->top_iarena.alloc(size_t(3) * r, &H->mem);
+      H->top_rec.alloc(1, &H->mem);
+      H->top_woff.alloc(1, &H->mem);
+      H->sync.alloc(2, &H->mem);
+      H->top_dinv.alloc(size_t(nbk) * 2 * kNbT * kNbT, &H->mem);
+    } catch (const Error& e) {
+      if (e.status != HIF_ENOMEM) throw;
+      H->top_iarena.release();
+      H->top_rec.release();
+      H->top_woff.release();
+      H->sync.release();
+    }
+  }
+  if (top_split_solve(H)) {
+    hipLaunchKernelGGL(k_top_record, dim3(unsigned((r + 255) / 256)), dim3(256), 0, s, H->top_idx.p, H->top_piv.p,
+                       H->top_perm.p, r, H->top_iarena.p, H->top_rec.p, H->top_woff.p);
+    SpArgs P{H->top_rec.p, H->top_iarena.p, H->top_lu.p, H->top_woff.p, nullptr, nullptr, nullptr, H->n, 1,
+             nullptr, nbk};
+    hipLaunchKernelGGL(k_sp_dinv, dim3(unsigned(nbk), 1), dim3(128), 0, s, P, H->top_dinv.p);
+    HIF_HIP(hipGetLastError());
+  }
   // the ticket counters of the chained triangular solves
-  bool chained = top_split_solve(H);
+  bool chained = false;
   for (const SubLevel& sub : H->subs) chained = chained || sub.dinv.p != nullptr;
   if (chained && !H->sync.p) H->sync.alloc(2, &H->mem);
-  if (!top_split_solve(H) || H->top_rec.p) return;
-  const int r = int(H->ntop);
-  H->top_iarena.alloc(size_t(3) * r, &H->mem);
-  H->top_rec.alloc(1, &H->mem);
-  H->top_woff.alloc(1, &H->mem);
-  hipLaunchKernelGGL(k_top_record, dim3(unsigned((r + 255) / 256)), dim3(256), 0, s, H->top_idx.p, H->top_piv.p,
-                     H->top_perm.p, r, H->top_iarena.p, H->top_rec.p, H->top_woff.p);
-  const int nbk = (r + kNbT - 1) / kNbT;
-  H->top_dinv.alloc(size_t(nbk) * 2 * kNbT * kNbT, &H->mem);
-  SpArgs P{H->top_rec.p, H->top_iarena.p, H->top_lu.p, H->top_woff.p, nullptr, nullptr, nullptr, H->n, 1,
-           nullptr, nbk};
-  hipLaunchKernelGGL(k_sp_dinv, dim3(unsigned(nbk), 1), dim3(128), 0, s, P, H->top_dinv.p);
-  HIF_HIP(hipGetLastError());
 }
 
-// The handle's scratch, of at least need doubles.  A block that a recorded solve
-// writes to on every replay is left to it, not released to the next allocation.
-static double* sweep_scratch(hif_factor_s* H, int64_t need) {
-  if (H->work.use_count() > 1 && int64_t(H->work->n) < need) {
-    auto w = std::make_shared<DBuf<double>>();
-    w->ensure(need, &H->mem);
-    H->work = std::move(w);
+// The handle's scratch for nrhs right-hand sides (need: its doubles).  A block
+// that a recorded solve writes to on every replay is left to it, not released
+// to the next allocation.
+static double* sweep_scratch(hif_factor_s* H, int64_t nrhs, int64_t& need) {
+  auto get = [&](int64_t cnt) {
+    if (H->work.use_count() > 1 && int64_t(H->work->n) < cnt) {
+      auto w = std::make_shared<DBuf<double>>();
+      w->ensure(cnt, &H->mem);
+      H->work = std::move(w);
+    }
+    H->work->ensure(cnt, &H->mem);
+    need = cnt;
+    return H->work->p;
+  };
+  const int64_t most = sweep_work(H, nrhs), least = sweep_work_min(H, nrhs);
+  if (most > least) {
+    try {
+      return get(most);
+    } catch (const Error& e) {
+      if (e.status != HIF_ENOMEM) throw;
+    }
   }
-  H->work->ensure(need, &H->mem);
-  return H->work->p;
+  return get(least);
 }
 
 void sweep_impl(hif_factor_s* H, int op, const double* x, double* y, int64_t nrhs, hipStream_t s) {
-  const int64_t need = sweep_work(H, nrhs);
-  sweep_run(H, op, x, y, nrhs, s, sweep_scratch(H, need), need);
+  int64_t need = 0;
+  double* work = sweep_scratch(H, nrhs, need);
+  sweep_run(H, op, x, y, nrhs, s, work, need);
 }
 
 // The launches of one solve u = F^{-1} f recorded into a HIP graph by stream
@@ -1846,11 +1897,11 @@ void sweep_impl(hif_factor_s* H, int op, const double* x, double* y, int64_t nrh
 // sweep scratch is allocated before the capture starts.
 void graph_solve_impl(hif_factor_s* H, const double* f, double* u, int64_t nrhs, hipStream_t cs,
                       hipGraph_t* graph, hipGraphExec_t* exec) {
-  const int64_t need = sweep_work(H, nrhs);
   // a block that is outgrown here is released on cs: sweeps queued on other
   // streams have to be done with it
-  if (int64_t(H->work->n) < need) wait_uses(H);
-  double* work = sweep_scratch(H, need);
+  if (int64_t(H->work->n) < sweep_work(H, nrhs)) wait_uses(H);
+  int64_t need = 0;
+  double* work = sweep_scratch(H, nrhs, need);
   allow_large_lds();
   HIF_HIP(hipStreamSynchronize(cs));
   HIF_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));

@@ -343,6 +343,38 @@ def test_small_solves_beside_a_subnormal_pivot(n):
     F.free()
 
 
+@pytest.mark.parametrize("n", [12, 20, 25])
+def test_dense_factorization_under_a_tight_memory_cap(n):
+    # One leaf, no levels: 8 n^2 bytes of the block and a hundred an unknown
+    # (points, coefficients, indices) hold the factorization, 72 more the
+    # vectors of 8 right-hand sides.  From there up every cap is enough, with
+    # whatever the sweeps keep beside the factors, and the four sweeps are those
+    # of a factorization without a cap: to the rounding of two orders of
+    # summation, at most 4 N u of the operator's condition (below 50).
+    N = n * n
+    g = (np.arange(n) + 0.5) / n
+    pts = torch.tensor(np.stack(np.meshgrid(g, g, indexing="ij"), -1).reshape(-1, 2), device="cuda:0")
+    a = torch.ones(N, dtype=torch.float64, device="cuda:0")
+    x = torch.tensor(np.random.default_rng(n).standard_normal((9, N)), device="cuda:0")
+    kw = dict(a=a, b=1.0 + pts[:, 0], c=2.0 - pts[:, 1], h=1.0 / n)
+    F = hif.factor(pts, 1e-6, N, **kw)
+    ref = [F.solve(x), F.solve_T(x), F.apply(x), F.apply_T(x)]
+    F.free()
+    least = 8 * N * N + 172 * N
+    for extra in [0, 8, 64, 72 * N, 3 << 15, *range(1 << 16, 1 << 20, 1 << 16)]:
+        F = hif.factor(pts, 1e-6, N, max_bytes=least + extra, **kw)
+        for _ in range(2):
+            for f, r in zip((F.solve, F.solve_T, F.apply, F.apply_T), ref):
+                assert (torch.linalg.norm(f(x) - r) / torch.linalg.norm(r)).item() <= 50 * 4 * N * 2.0 ** -53, extra
+        u = torch.empty_like(x[:3])
+        gr = F.solve_graph(x[:3].clone(), u)
+        gr.launch()
+        torch.cuda.synchronize()
+        assert (torch.linalg.norm(u - ref[0][:3]) / torch.linalg.norm(u)).item() <= 50 * 4 * N * 2.0 ** -53, extra
+        gr.free()
+        F.free()
+
+
 def test_group_of_more_columns_than_the_pivot_choice_holds():
     # One leaf of 128 x 129 = 16512 points beside three of 16: its ID has more
     # columns than the pivot choice keeps in registers, and few rows.  A is the
