@@ -303,15 +303,16 @@ __device__ __forceinline__ void l_gemv_n_rc(const double* __restrict__ M, int nr
       const int v = lane >> 3;
       if ((lane & 7) == 0 && v < nv && i < nrow) y[v * ys + i] += sgn * t;
     };
-    for (int j0 = 0; j0 < ncol; j0 += 64 * C) {
+    // the columns that the triangle has in these rows
+    const int jb = TRI == 0 ? i0 & ~63 : 0, je = TRI == 1 ? min(ncol, i0 + (R - 1) * nw) : ncol;
+    for (int j0 = jb; j0 < je; j0 += 64 * C) {
       double m[R][C];
 #pragma unroll
       for (int q = 0; q < R; ++q)
 #pragma unroll
         for (int h = 0; h < C; ++h) {
           const int i = min(i0 + q * nw, nrow - 1), j = j0 + 64 * h + lane;
-          const double t = M[int64_t(i) * ld + min(j, ncol - 1)];
-          m[q][h] = j < ncol && (TRI != 0 || j >= i) && (TRI != 1 || j < i) ? t : 0.0;
+          m[q][h] = M[int64_t(i) * ld + min(j, je - 1)];
         }
 #pragma unroll
       for (int q = 0; q < R; ++q) {
@@ -322,8 +323,9 @@ __device__ __forceinline__ void l_gemv_n_rc(const double* __restrict__ M, int nr
           for (int v = 0; v < kMaxV; ++v) a[v] = 0.0;
 #pragma unroll
         for (int h = 0; h < C; ++h) {
-          const int j = j0 + 64 * h + lane;
-          if (j < ncol)
+          // (a select on the entry would put its load behind a branch of its own)
+          const int i = i0 + q * nw, j = j0 + 64 * h + lane;
+          if (j < je && (TRI != 0 || j >= i) && (TRI != 1 || j < i))
 #pragma unroll
             for (int v = 0; v < kMaxV; ++v)
               if (v < nv) a[v] += m[q][h] * x[v * xs + j];
@@ -382,10 +384,10 @@ __device__ __forceinline__ void l_gemv_t(const double* __restrict__ M, int nrow,
 #pragma unroll
       for (int u = 0; u < kU; ++u)
         if (i0 + u < ie) {
-          const double m = (TRI != 2 || i0 + u > j) && (TRI != 3 || i0 + u <= j) ? mv[u] : 0.0;
+          if ((TRI != 2 || i0 + u > j) && (TRI != 3 || i0 + u <= j))
 #pragma unroll
-          for (int v = 0; v < kMaxV; ++v)
-            if (v < nv) acc[v] += m * x[v * xs + i0 + u];
+            for (int v = 0; v < kMaxV; ++v)
+              if (v < nv) acc[v] += mv[u] * x[v * xs + i0 + u];
         }
     }
     if (!split)
@@ -465,11 +467,6 @@ __device__ __forceinline__ void l_solve(const double* __restrict__ LU, int n, do
   const int nblk = (n + kNbT - 1) / kNbT;
   for (int jb = 0; jb < nblk; ++jb) {
     const int j0 = (kFwd ? jb : nblk - 1 - jb) * kNbT, nb = min(kNbT, n - j0), row = min(lane, nb - 1);
-    double d = 1.0, di = 1.0;
-    if constexpr (kUp) {
-      d = tri[tri_at<true>(nb, row, row)];
-      di = 1.0 / d;
-    }
     // a wave takes right-hand sides v and v + nw together: one read of each
     // entry of the triangle for both
     for (int v = wv; v < nv; v += 2 * nw) {
@@ -477,6 +474,11 @@ __device__ __forceinline__ void l_solve(const double* __restrict__ LU, int n, do
         constexpr bool TWO = decltype(two_c)::value;
         double xi = x[v * xs + j0 + row], xj = TWO ? x[(v + nw) * xs + j0 + row] : 0.0;
         // a quotient is a product with the reciprocal and one correction
+        double d = 1.0, di = 1.0;
+        if constexpr (kUp) {
+          d = tri[tri_at<true>(nb, row, row)];
+          di = 1.0 / d;
+        }
         auto quot = [&](double b) {
           const double q = b * di;
           return __builtin_fma(__builtin_fma(-q, d, b), di, q);
@@ -532,6 +534,7 @@ __device__ __forceinline__ void l_solve(const double* __restrict__ LU, int n, do
         continue;
       if constexpr (kUp)
         for (int w = v; w < min(nv, v + 2 * nw); w += nw) {  // by divisions
+          const double d = tri[tri_at<true>(nb, row, row)];
           double xi = x[w * xs + j0 + row];
 #pragma clang loop unroll(disable)
           for (int u = 0; u < nb; ++u) {

@@ -247,6 +247,25 @@ def test_sweeps_top_sizes_and_right_hand_sides(n, d, leaf, eps):
     F.free()
 
 
+@pytest.mark.parametrize("n,leaf", [(16, 64), (20, 100), (24, 144), (32, 256), (40, 400), (46, 529)])
+def test_sweeps_of_large_records_in_one_workgroup(n, leaf):
+    # Four cells that hold most of the unknowns as redundant ones: records of up
+    # to 64, 128, 256 and more rows that are swept by one workgroup each, whose
+    # triangular products take only the columns their rows reach.  The checks
+    # are those of the other sizes, and the product is F's own: A x to 10 eps.
+    test_sweeps_top_sizes_and_right_hand_sides(n, 2, leaf, 1e-9)
+    pts = torch.tensor(grid_points(n, 2), device="cuda:0")
+    a = torch.ones(n * n, dtype=torch.float64, device="cuda:0")
+    c = 1.0 + pts[:, 1]
+    F = hif.factor(pts, 1e-9, leaf, a=a, c=c, h=1.0 / n)
+    x = torch.tensor(np.random.default_rng(n).standard_normal((3, n * n)), device="cuda:0")
+    Ax = hif.matvec(pts, x, a=a, c=c, h=1.0 / n)
+    ATx = hif.matvec(pts, x, a=a, b=c, h=1.0 / n)  # K is symmetric on a uniform grid
+    assert (torch.linalg.norm(F.apply(x) - Ax) / torch.linalg.norm(Ax)).item() <= 1e-8
+    assert (torch.linalg.norm(F.apply_T(x) - ATx) / torch.linalg.norm(ATx)).item() <= 1e-8
+    F.free()
+
+
 @pytest.mark.parametrize("n", [22, 26, 32])  # cells of 121, 169 and 256 columns: rows as they are, padded, and past 1 KiB
 def test_padded_blocks_as_assembled(n):
     # A group's block Y with rows padded in memory: the copy handed out has
