@@ -42,7 +42,7 @@ struct PqCtl {
   int gram;   // G is to be formed (from column k on)
   int need;   // the choice ended for want of accuracy
   int done;
-  int pad0, pad1;
+  unsigned long long left;  // largest squared norm of what is left (its bits), where G is to be formed again
   double gmax;  // largest squared norm when G was formed
   double r00;
 };
@@ -71,6 +71,51 @@ __global__ __launch_bounds__(256) void k_pq_init(IdArgs A, PqState S) {
     c.gram = 1;
     S.ctl[q] = c;
     S.jbv[q] = 0;
+  }
+}
+
+// The largest norm of the trailing columns of problems whose G is to be formed
+// again: 64 columns a workgroup, the rows over its waves.  Where it is within the
+// tolerance nothing is left to choose, and one pass over the block has saved the
+// Gram matrix, which costs all its columns' products (one 4096 x 4096 problem of
+// rank 8: 4.7 ms with the second one, 2.4 before there were any).
+__global__ __launch_bounds__(1024) void k_pq_left(IdArgs A, PqState S) {
+  constexpr int NW = 16;
+  const int q = blockIdx.y;
+  PqCtl* C = S.ctl + q;
+  if (C->done || !C->gram || C->k == 0) return;
+  const int n = A.cols[q], m = A.rows[q], ld = A.ld[q], c0 = C->k + int(blockIdx.x) * 64;
+  if (c0 >= n) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const double* Z = A.base + A.moff[q] + min(c0 + lane, n - 1);
+  double s0 = 0.0;
+  for (int r = C->k + wv; r < m; r += 8 * NW) {
+    double y[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) y[u] = Z[int64_t(min(r + NW * u, m - 1)) * ld];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s0 = r + NW * u < m ? fma(y[u], y[u], s0) : s0;
+  }
+  __shared__ double part[NW][64];
+  part[wv][lane] = s0;
+  __syncthreads();
+  if (wv) return;
+  double t = 0.0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) t += part[w][lane];
+  const double mx = wave_max(fmax(t, 0.0));  // a column of NaN is never chosen
+  if (lane == 0) atomicMax(&C->left, static_cast<unsigned long long>(__double_as_longlong(mx)));
+}
+// Such a problem is done if no pivot can pass the rank rule any more (the norms
+// are good to far better than the margin).
+__global__ void k_pq_end(IdArgs A, PqState S) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= A.nprob) return;
+  PqCtl* C = S.ctl + q;
+  if (C->done || !C->gram || C->k == 0) return;
+  if (sqrt(__longlong_as_double((long long)C->left)) <= A.tol[q] * C->r00 * (1.0 - 1e-10)) {
+    C->done = 1;
+    A.rank[q] = C->k;
   }
 }
 
@@ -430,6 +475,7 @@ __global__ __launch_bounds__(64) void k_pq_rank(IdArgs A, PqState S) {
     C->r00 = r00;
     C->done = done;
     C->gram = !done && C->need;
+    C->left = 0;
     if (done) A.rank[q] = kn;
   }
 }
@@ -598,9 +644,13 @@ static void id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
   hipLaunchKernelGGL(k_pq_init, dim3(unsigned((max_cols + 255) / 256), up), dim3(256), 0, s, A, S);
   std::vector<PqCtl> hc(np);
   int kmin = 0, gcols = max_cols, trail = max_cols;  // what is left of the widest problem
-  bool all = false;
+  bool all = false, again = false;  // again: a Gram matrix is to be formed once more
   // a block takes a step of each unfinished problem, or the next one does
   for (int blk = 0; blk <= 2 * max_cols + 2 && !all; ++blk) {
+    if (again) {
+      hipLaunchKernelGGL(k_pq_left, dim3(unsigned((trail + 63) / 64), up), dim3(1024), 0, s, A, S);
+      hipLaunchKernelGGL(k_pq_end, dim3(unsigned((np + 63) / 64)), dim3(64), 0, s, A, S);
+    }
     const unsigned gt64 = unsigned((gcols + 63) / 64);
     hipLaunchKernelGGL(k_pq_gram, dim3(gt64, gt64, up), dim3(256), 0, s, A, S);
     if (max_cols <= kPqT)
@@ -617,11 +667,13 @@ static void id_blocked(const IdArgs& A0, int max_rows, int max_cols, hipStream_t
     HIF_HIP(hipMemcpyAsync(hc.data(), ctl.p, sizeof(PqCtl) * np, hipMemcpyDeviceToHost, s));
     HIF_HIP(hipStreamSynchronize(s));
     all = true;
+    again = false;
     kmin = max_cols;
     gcols = trail = 1;
     for (int q = 0; q < np; ++q) {
       if (hc[q].done) continue;
       all = false;
+      again = again || (hc[q].gram && hc[q].k > 0);
       kmin = std::min(kmin, hc[q].k);
       gcols = std::max(gcols, hcl[q] - (hc[q].gram ? hc[q].k : hc[q].g0));
       trail = std::max(trail, hcl[q] - hc[q].k);

@@ -143,6 +143,25 @@ def test_blocked_pivoted_qr_edges(m, n, decay, tol):
         _check_id(Y, tol, True, sk.numpy(), rd.numpy(), T.numpy(), osk, oT)
 
 
+@pytest.mark.parametrize("m,n", [(200, 150), (64, 1100), (300, 4096)])
+@pytest.mark.parametrize("rank", [1, 31, 32, 33, 63])
+def test_blocked_pivoted_qr_of_low_rank(m, n, rank):
+    # Rank at, before and after the ends of blocks, the rest eight digits below
+    # the tolerance or zero: what is left then stops the choice.  The rank is the
+    # oracle's and T within its bounds.  Unequal ranks share the batch.
+    rng = np.random.default_rng(m + n + rank)
+    cases = []
+    for nn, r, noise in ((n, rank, 0.0), (max(128, n - 7), max(1, rank - 2), 1e-14), (n, min(rank + 40, 63), 1e-14)):
+        U = np.linalg.qr(rng.standard_normal((m, r)))[0]
+        Y = (U * 10.0 ** (-3.0 * np.arange(r) / r)) @ rng.standard_normal((r, nn))
+        cases.append(Y + noise * rng.standard_normal((m, nn)))
+    out = hif.id_batched([torch.tensor(Y) for Y in cases], [1e-6] * len(cases))
+    for Y, (sk, rd, T) in zip(cases, out):
+        osk, _, oT = interp_decomp(Y, 1e-6)
+        assert sk.numel() == len(osk)
+        _check_id(Y, 1e-6, False, sk.numpy(), rd.numpy(), T.numpy(), osk, oT)
+
+
 def test_blocked_pivoted_qr_zero_tied_and_nonfinite_columns():
     # Zero columns are never pivots; of equal columns the lowest is chosen
     # first and the others vanish; a column of NaN is never chosen and does not
