@@ -29,6 +29,14 @@ void launch_rowqr_split(double* base, const std::vector<int64_t>& moff, const st
                         const std::vector<int32_t>& rows, const std::vector<int32_t>& cols, MemTracker* mt,
                         hipStream_t s);
 
+// Householder reflectors of the row compression: a column whose squared norm is
+// below this is taken as zero.  2 / v^T v (and T, about that of two reflectors)
+// of a smaller one leaves the range of a double, and the block becomes NaN.  Such
+// columns arise from ordinary data: a chunk of a panel with fewer nonzero rows
+// than columns is left with rounding errors, then with the rounding errors of
+// these, 16 digits lower at every turn.
+constexpr double kReflectorMin = 0x1p-1000;
+
 // Communication-avoiding panels of the row compression (tsqr.hip): panel
 // width, rows per chunk, chunk factors per group, the tallest problem, and the
 // tallest panel its three tree levels take.

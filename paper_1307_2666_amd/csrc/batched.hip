@@ -71,10 +71,11 @@ __global__ __launch_bounds__(kQpThreads) void k_qr_panel(QrBatch A, int j0) {
     const int nc = jb - jj - 1;
     const double x0 = M[int64_t(j) * ld + j];
     const double nrm = sqrt(ss);
-    const double alpha = nrm > 0.0 ? -copysign(nrm, x0) : 0.0;
+    const bool live = ss >= kReflectorMin;
+    const double alpha = live ? -copysign(nrm, x0) : 0.0;
     const double v0 = x0 - alpha;
     const double vtv = ss - x0 * x0 + v0 * v0;
-    const double beta = vtv > 0.0 ? 2.0 / vtv : 0.0;
+    const double beta = live ? 2.0 / vtv : 0.0;
     double part[kNb];
 #pragma unroll
     for (int c = 0; c < kNb; ++c) part[c] = 0.0;

@@ -141,10 +141,11 @@ __device__ __forceinline__ void block_qr(double (&y)[16][2], int jb, FactLds<NW>
       const double x0 = L.row[b][jj], r0 = L.row[b][li], r1 = L.row[b][16 + li];
       const double ss = sj + x0 * x0;
       const double nrm = sqrt(ss);
-      const double alpha = nrm > 0.0 ? -copysign(nrm, x0) : 0.0;
+      const bool live = ss >= kReflectorMin;
+      const double alpha = live ? -copysign(nrm, x0) : 0.0;
       const double v0 = x0 - alpha;
       const double vtv = sj + v0 * v0;
-      const double beta = vtv > 0.0 ? 2.0 / vtv : 0.0;
+      const double beta = live ? 2.0 / vtv : 0.0;
       const double g0 = v0 * r0 + t0, g1 = v0 * r1 + t1;
       const double c0 = (li > jj && li < jb) ? beta * g0 : 0.0;
       const double c1 = (16 + li > jj && 16 + li < jb) ? beta * g1 : 0.0;

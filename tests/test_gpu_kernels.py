@@ -162,6 +162,31 @@ def test_blocked_pivoted_qr_of_low_rank(m, n, rank):
         _check_id(Y, 1e-6, False, sk.numpy(), rd.numpy(), T.numpy(), osk, oT)
 
 
+@pytest.mark.parametrize("m,n", [(600, 40), (600, 150), (600, 600), (4400, 300)])
+def test_reflectors_of_columns_whose_squares_underflow(m, n):
+    # In the first panel's chunks of rows: the second holds three rows of rank 1,
+    # so that after one column only rounding errors of rounding errors are left,
+    # the last four rows down to where squares underflow, and one column is as
+    # small altogether.  All of it is below the tolerance beside the other rows:
+    # skeleton and T are the oracle's.
+    rng = np.random.default_rng(m + n)
+    nck = (m + 255) // 256
+    cases = []
+    for _ in range(2):
+        Y = rng.standard_normal((m, n)) * (10.0 ** (-9.0 * np.arange(n) / n))[rng.permutation(n)]
+        lo, hi, last = m // nck, 2 * m // nck, (nck - 1) * m // nck
+        Y[lo:hi] = 0.0
+        Y[lo + 50:lo + 53] = 1e-30 * rng.standard_normal((3, 1)) * rng.standard_normal(n)
+        Y[last:] = 0.0
+        Y[last + 40:last + 44] = np.array([1e-40, 1e-90, 1e-145, 1e-157])[:, None] * rng.standard_normal((4, n))
+        Y[:, n // 3] = 1e-158 * rng.standard_normal(m)
+        cases.append(Y)
+    out = hif.id_batched([torch.tensor(Y) for Y in cases], [1e-6] * len(cases))
+    for Y, (sk, rd, T) in zip(cases, out):
+        osk, _, oT = interp_decomp(Y, 1e-6)
+        _check_id(Y, 1e-6, True, sk.numpy(), rd.numpy(), T.numpy(), osk, oT)
+
+
 def test_blocked_pivoted_qr_zero_tied_and_nonfinite_columns():
     # Zero columns are never pivots; of equal columns the lowest is chosen
     # first and the others vanish; a column of NaN is never chosen and does not
