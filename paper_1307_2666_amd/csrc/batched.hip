@@ -1,11 +1,10 @@
-// Per-panel batched kernels for the coarse sub-levels, where a few large
-// problems would leave most compute units idle if each ran in one workgroup:
-// the row compression before the ID (blocked Householder QR) and the partial
-// LU of the elimination (and of the top block) are split into a panel kernel
-// (one workgroup per problem) and a trailing-update kernel (one workgroup per
-// 64-column tile per problem) launched once per panel of 16 columns.  The
-// updates run on the matrix cores (v_mfma_f64_16x16x4f64) with operands read
-// straight from device memory in the instruction's lane layout.
+// Batched kernels for the coarse sub-levels, where a few large problems would
+// leave most compute units idle if each ran in one workgroup: the dispatch of
+// the row compression before the ID (the tree of tsqr.hip; above 32768 rows row
+// blocks, or panels of 16 columns by one workgroup per problem with a
+// trailing-update kernel of one workgroup per 64 columns), and general products
+// by 64 x 64 tiles.  The updates run on the matrix cores (v_mfma_f64_16x16x4f64)
+// with operands read straight from device memory in the instruction's lane layout.
 #include <algorithm>
 #include <climits>
 #include <vector>

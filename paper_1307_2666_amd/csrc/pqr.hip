@@ -78,7 +78,8 @@ __global__ __launch_bounds__(256) void k_pq_init(IdArgs A, PqState S) {
 // again: 64 columns a workgroup, the rows over its waves.  Where it is within the
 // tolerance nothing is left to choose, and one pass over the block has saved the
 // Gram matrix, which costs all its columns' products (one 4096 x 4096 problem of
-// rank 8: 4.7 ms with the second one, 2.4 before there were any).
+// rank 8: 4.7 ms where it is formed for that, 2.8 so).  16 waves: with 4 the
+// chain of a wave's rows slowed the factorizations by 1%.
 __global__ __launch_bounds__(1024) void k_pq_left(IdArgs A, PqState S) {
   constexpr int NW = 16;
   const int q = blockIdx.y;
